@@ -46,7 +46,7 @@ struct hpacml_model_s {
     Variant variant = Variant::Generic;
     float *gen_buf = nullptr;   // generic-kernel weights and biases
     DevModel gen{};
-    float *f32_img = nullptr;   // packed LDS image of the fp32 kernel
+    float *f32_img = nullptr;   // the fp32 kernel's packed image
     F32Packed f32{};
     uint16_t *bf16_frags = nullptr;  // packed fragments of the bf16 kernel
     BF16Packed bf16{};
@@ -606,8 +606,8 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
         }
 
         if (f32_fast_supported(n_layers, fd, compute)) {
-            std::vector<float> img(f32_image_floats(n_layers, fd), 0.f);
-            f32_pack(n_layers, fd, fW, fb, img.data());
+            std::vector<float> img(f32_image_floats(n_layers, fd));
+            m->f32.plain = !f32_pack(n_layers, fd, fW, fb, img.data());
             s = upload(&m->f32_img, img.data(), img.size());
             if (s != HPACML_OK) {
                 hpacml_model_destroy(m);
@@ -617,10 +617,14 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
             m->f32.n_hidden = n_layers - 2;
             m->f32.ks1 = (fd[0] + 1) / 2;
             m->f32.f_out = fd[n_layers];
+            m->f32.relu = 0;
             for (int l = 0; l < n_layers; ++l)
-                m->f32.act[l] = act[l];
-            m->f32.lds_bytes = (int32_t)(img.size() * sizeof(float));
+                m->f32.relu |= act[l] == HPACML_ACT_RELU ? 1u << l : 0u;
             m->f32.image = m->f32_img;
+            for (int l = 0; l <= n_layers; ++l)
+                m->f32.dims[l] = dims[l];
+            for (int l = 0; l < n_layers; ++l)
+                m->f32.W[l] = m->gen.W[l];
             m->variant = Variant::F32;
             m->fast_name = f32_variant_name(m->f32);
         } else if (bf16r_supported(n_layers, fd, act, compute)) {

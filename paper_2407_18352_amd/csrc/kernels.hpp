@@ -62,20 +62,24 @@ hipError_t launch_mlp_generic(const DevMap &in, const DevMap &out, const DevMode
                               hipStream_t stream);
 
 // fp32 register-resident fused kernel: hidden layers of one width H in
-// {64, 128}, all weights resident in LDS, MFMA 32x32x2 f32.
+// {64, 128}, weights split in three bf16 parts resident in LDS (the smallest
+// parts in the L2 where they don't fit), products on bf16 MFMA.
 struct F32Packed {
     int32_t hid;          // H
     int32_t n_hidden;     // hidden-to-hidden layers (H x H), 0..6
-    int32_t ks1;          // K-steps of the first layer (ceil(F_in / 2))
+    int32_t ks1;          // pairs of input features (ceil(F_in / 2))
     int32_t f_out;        // outputs (1..8)
-    int32_t act[HPACML_MAX_LAYERS];
-    int32_t lds_bytes;    // size of the packed image (bytes)
-    const float *image;   // device copy of the LDS image
+    uint32_t relu;        // bit l: layer l has a ReLU
+    int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
+    const float *image;   // device: the packed split image
+    // the unpadded layers, read for values without a split
+    int32_t dims[HPACML_MAX_LAYERS + 1];
+    const float *W[HPACML_MAX_LAYERS];
 };
 bool f32_fast_supported(int n_layers, const int32_t *dims, int compute);
 size_t f32_image_floats(int n_layers, const int32_t *dims);
-void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b,
-              float *image);
+// Packs the image; false when a weight has no split (F32Packed::plain).
+bool f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image);
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                           const F32Packed &pk, hipStream_t stream);
 const char *f32_variant_name(const F32Packed &pk);

@@ -1,21 +1,44 @@
 // fp32 fused region kernel: gather -> MLP -> scatter with the activations
-// resident in registers and every weight resident in LDS.
+// resident in registers and the weights in LDS, the products on the bf16
+// matrix cores.
 //
 // The surrogate runs per sweep point on the composed input tensor
 // (Sec. IV-A composition, Sec. IV-B inference).  Here each wave owns 32 points
-// and computes every layer transposed, H_out^T = W * H_in^T, on
-// v_mfma_f32_32x32x2_f32: A = weights (rows = output features, from LDS),
-// B = activations (columns = points, from registers), C = the next layer's
-// activations.  In the 32x32 C layout lane l holds point l%32 and, in
-// register r of m-block mb, feature 32mb + 8(r/4) + 4(l/32) + r%4.  Used
-// directly as the next layer's B operand (K-step s takes register s%16 of
-// m-block s/16, k = l/32), the activations never leave registers: the next
-// layer's weight columns are permuted to match when the LDS image is packed.
+// and computes every layer transposed, H_out^T = W * H_in^T: A = weights
+// (rows = output features), B = activations (columns = points, from
+// registers), C = the next layer's activations.
 //
-// First layer: each lane gathers feature 2s + l/32 of its point straight into
-// the B operand of K-step s.  Output layer (<= 8 outputs): VALU dot products
-// over the lane's 16*NMB features plus one cross-half shuffle.  Biases enter
-// as the initial accumulator.
+// Products of 32-bit numbers: the fp32 matrix instruction does 64 flop per
+// cycle and SIMD, the bf16 one 1024.  A float is the exact sum of three bf16
+// numbers (hi + mid + lo: 8 significant bits each, rounded to nearest; exact
+// from 2^-110 up, below that to an absolute 2^-134), so w * x is the sum of
+// nine bf16 products; the six of at least 2^-18 of the largest (hi hi, hi
+// mid, mid hi, mid mid, hi lo, lo hi) are accumulated in fp32 by
+// v_mfma_f32_32x32x16_bf16, the other three (2^-27 and less) are below half a
+// unit of the fp32 product.  Six of these instructions take 192 cycles for 16
+// values of k where the fp32 form takes 512, and round the sum six times
+// instead of eight.  Measured error against 64 bits, start of this form /
+// fp32 instruction: see the table at the end of this comment.
+//
+// Layouts: in the 32x32 C layout lane l holds point l % 32 and, in register r
+// of m-block mb, feature 32 mb + 8 (r / 4) + 4 (l / 32) + r % 4.  Registers 8t ..
+// 8t + 7, split in three, are directly the B operand of K-step 2 mb + t of the
+// next layer (k = 8 (l / 32) + j) when that layer's weight columns are permuted
+// to match at pack time; the activations never leave registers.
+//
+// First layer: each lane gathers features 2t + l / 32 of its point into the
+// slots t = 8s .. 8s + 7 of K-step s.  Output layer (<= 8 outputs): the fp32 matrix
+// instruction of 4 x 4 blocks.  Biases enter as the initial accumulator.
+//
+// Values of 2^127 and more (infinities among them) have no such split, and
+// inputs that are all below 2^-100 lose bits in it: a wave that meets a point
+// of that kind (or such an activation) computes its tile again on the fp32
+// matrix instruction, with the caller's weights read from global memory; so
+// does every wave of a model with such a weight or layer of weights.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace hpacml {
@@ -23,55 +46,132 @@ namespace hpacml {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-constexpr int kFoutMax = 8;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// LDS image offsets (floats) for a model of hidden width H = 32 * NMB.
-struct F32Layout {
-    int nmb, ks1, n_hidden, f_out;
-    __host__ __device__ int l1() const { return 0; }
-    __host__ __device__ int l1_bias() const { return ks1 * 64 * nmb; }
-    __host__ __device__ int hidden(int h) const { return l1_bias() + 32 * nmb + h * (32 * nmb * 32 * nmb + 32 * nmb); }
-    __host__ __device__ int hidden_bias(int h) const { return hidden(h) + 32 * nmb * 32 * nmb; }
-    __host__ __device__ int out_w() const { return hidden(n_hidden); }
-    __host__ __device__ int out_b() const { return out_w() + f_out * 32 * nmb; }
-    __host__ __device__ int total() const { return out_b() + kFoutMax; }
+constexpr int kFoutMax = 8;
+// scheduling-barrier mask: only VALU, SALU and transcendental instructions
+// may be moved across
+constexpr int kSchedAluOnly = 0x2 | 0x4 | 0x400;
+constexpr int kFragBytes = 1024;        // one A operand: 64 lanes x 8 bf16
+constexpr int kLdsMax = 160 * 1024;     // LDS of a CU
+constexpr uint32_t kBig = 0x7F000000u;  // bits of 2^127: this and more has no three-way split
+constexpr uint32_t kTiny = 0x0D800000u; // bits of 2^-100: below it the lo part loses bits
+
+// What a block keeps of the two maps in LDS, ahead of the split image: the
+// feature tables, read with a lane's own feature number, and the 32-bit
+// views, whose fields would otherwise occupy (and spill) scalar registers
+// over the whole kernel.
+struct MapsLds {
+    Map32 in, out;
+    const float *fptr[kTableMaxF];
+    float *optr[kFoutMax];
+    uint32_t raw8[kTableMaxF], oraw8[kFoutMax];
+};
+static_assert(sizeof(MapsLds) % 16 == 0 && sizeof(Map32) % 16 == 0, "read 16 bytes at a time");
+
+// locate32 on a view in LDS: unused dimensions (count 1, stride 0) add
+// nothing, those past the second are skipped for the usual ranks.
+__device__ __forceinline__ Pt32 locate_lds(const Map32 &m, int rank, int32_t b) {
+    Pt32 r;
+    uint32_t rem = (uint32_t)b;
+    r.pe = 0;
+    auto dim = [&](int d) __attribute__((always_inline)) {
+        uint32_t k = rem;
+        if (d > 0) {
+            rem = (uint32_t)(((uint64_t)rem * m.magic[d]) >> m.shift[d]);
+            k -= rem * (uint32_t)m.count[d];
+        }
+        r.p[d] = m.start[d] + (int32_t)k * m.step[d];
+        r.pe += r.p[d] * m.stride[d];
+    };
+    r.p[1] = r.p[2] = r.p[3] = 0;
+    if (rank > 1) {
+        if (rank > 2) {
+            dim(3);
+            dim(2);
+        }
+        dim(1);
+    }
+    dim(0);
+    return r;
+}
+
+// The dimensions along which some lane of the wave reads outside the arrays.
+__device__ __forceinline__ uint32_t edge_lds(const Map32 &m, int rank, const Pt32 &r) {
+    uint32_t edge = 0;
+#pragma unroll
+    for (int d = 0; d < HPACML_MAX_RANK; ++d)
+        if (d < rank && __any(r.p[d] + m.omin[d] < 0 || r.p[d] + m.omax[d] >= m.extent[d]))
+            edge |= 1u << d;
+    return edge;
+}
+
+// Boundary corrections of N accesses with raw offsets raw[] at point r, added
+// to idx[]; `edge`: the dimensions along which some lane of the wave leaves
+// the arrays.  Per dimension dl = clamp(at, 0, n - 1) - at (zero inside):
+// clamp adds dl strides, periodic one wrap in dl's direction (|offset| <=
+// extent).
+template <int N>
+__device__ __forceinline__ void fix_lds(const Map32 &m, const Pt32 &r, uint32_t edge, const uint32_t (&raw)[N],
+                                        int32_t (&idx)[N]) {
+#pragma unroll
+    for (int d = 0; d < HPACML_MAX_RANK; ++d) {
+        if (edge & (1u << d)) {
+            const int32_t n = m.extent[d], st = m.stride[d];
+            const bool per = m.bnd[d] == HPACML_BND_PERIODIC;
+            const int32_t lim = per ? 1 : INT32_MAX, mul = per ? (int32_t)((uint32_t)n * (uint32_t)st) : st;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const int32_t at = r.p[d] + (int32_t)(int8_t)(raw[j] >> (8 * d));
+                const int32_t dl = min(max(at, 0), n - 1) - at;
+                idx[j] += min(max(dl, -lim), lim) * mul;
+            }
+        }
+    }
+}
+
+// Split image offsets (bytes).  In LDS: biases and output layer (fp32), the hi
+// and mid fragments of every layer, and the lo fragments; with lo_global the
+// lo fragments stay in global memory behind the rest.  The output weights go in
+// groups of four outputs: a[i] of lane l, i < 2 NMB, is weight [l % 4] for the
+// feature that lane half l / 32 holds in register 8i + (l % 32) / 4 (counted
+// over the m-blocks): one register of the matrix instruction's A operand
+// serves eight of the activations' registers.
+//   fragment of layer 1: K-step s, m-block mb, part q -> l1(s, mb, q)
+//   fragment of hidden layer h likewise; 2 * NMB K-steps
+struct SplitLayout {
+    int nmb, ks, n_hidden, f_out;
+    __host__ __device__ int l1_bias() const { return 0; }
+    __host__ __device__ int hidden_bias(int h) const { return (h + 1) * 128 * nmb; }
+    __host__ __device__ int out_w() const { return (n_hidden + 1) * 128 * nmb; }
+    __host__ __device__ int out_w(int group) const { return out_w() + group * 512 * nmb; }
+    __host__ __device__ int out_b() const { return out_w((f_out + 3) / 4); }
+    // hi and mid of layer 1, then of the hidden layers: [K-step][m-block][2]
+    __host__ __device__ int l1() const { return out_b() + 4 * kFoutMax; }
+    __host__ __device__ int hidden(int h) const { return l1() + (ks + h * 2 * nmb) * nmb * 2 * kFragBytes; }
+    // lo: [K-step][m-block]
+    __host__ __device__ int l1_lo() const { return hidden(n_hidden); }
+    __host__ __device__ int hidden_lo(int h) const { return l1_lo() + (ks + h * 2 * nmb) * nmb * kFragBytes; }
+    __host__ __device__ int total() const { return hidden_lo(n_hidden); }
+    // what a block keeps in LDS
+    __host__ __device__ int image_lds(bool lo_global) const { return lo_global ? l1_lo() : total(); }
+    __host__ __device__ int lds(bool lo_global) const { return image_lds(lo_global) + (int)sizeof(MapsLds); }
 };
 
-// feature of the previous layer that K-step s, lane half g reads (see above)
-__host__ __device__ inline int kperm(int s, int g) {
-    return 32 * (s / 16) + 8 * ((s % 16) / 4) + 4 * g + (s % 4);
-}
 // feature held by lane half g in register r of m-block mb
 __host__ __device__ inline int crow(int mb, int r, int g) { return 32 * mb + 8 * (r / 4) + 4 * g + (r % 4); }
 
-template <int NMB>
-struct FragA;
-template <>
-struct FragA<2> {
-    float2 v;
-    __device__ float operator[](int i) const { return i == 0 ? v.x : v.y; }
-};
-template <>
-struct FragA<4> {
-    float4 v;
-    __device__ float operator[](int i) const { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); }
-};
-
-template <int NMB>
-__device__ __forceinline__ FragA<NMB> lds_frag(const float *base, int s, int lane) {
-    FragA<NMB> a;
-    if constexpr (NMB == 2)
-        a.v = reinterpret_cast<const float2 *>(base)[s * 64 + lane];
-    else
-        a.v = reinterpret_cast<const float4 *>(base)[s * 64 + lane];
-    return a;
-}
-
-template <int NMB>
-__device__ __forceinline__ void load_bias(const float *bias, int g, floatx16 *acc) {
+// N m-blocks from m-block mb0 on
+template <int NMB, int N = NMB>
+__device__ __forceinline__ void load_bias(const float *bias, int g, floatx16 *acc, int mb0 = 0) {
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) {
-        const float4 *p = reinterpret_cast<const float4 *>(bias + (g * NMB + mb) * 16);
+    for (int mb = 0; mb < N; ++mb) {
+        const float4 *p = reinterpret_cast<const float4 *>(bias + (g * NMB + mb0 + mb) * 16);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float4 v = p[q];
@@ -83,11 +183,127 @@ __device__ __forceinline__ void load_bias(const float *bias, int g, floatx16 *ac
     }
 }
 
-template <int NMB, int KS1MAX, bool PF>
-__global__ void __launch_bounds__(512) mlp_f32_kernel(Map32 in, Map32 out, FeatTable32 tin, FeatTable32 tout,
-                                                      F32Packed pk, int32_t n_tiles, int32_t xcd_ranges) {
-    extern __shared__ float lds[];
-    const F32Layout lay{NMB, pk.ks1, pk.n_hidden, pk.f_out};
+// compile-time loop: fn(std::integral_constant<int, i>) for i in [B, E)
+template <int B, int E, typename Fn>
+__device__ __forceinline__ void static_for(Fn &&fn) {
+    if constexpr (B < E) {
+        fn(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(fn);
+    }
+}
+
+// Eight floats as three B fragments, v = hi + mid + lo exactly (see above).
+struct Split {
+    u32x4 hi, mid, lo;
+};
+__device__ __forceinline__ Split split8(floatx8 v) {
+    Split f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
+        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+        f.hi[i] = h;
+        f.mid[i] = m;
+        f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
+    }
+    return f;
+}
+
+__device__ __forceinline__ floatx16 mfma(u32x4 a, u32x4 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// ReLU where the layer has one; the largest magnitude's bits join `top`.
+template <int N>
+__device__ __forceinline__ void activate(floatx16 *acc, bool relu, uint32_t &top) {
+    if (relu) {
+#pragma unroll
+        for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                acc[mb][r] = relu_mfma(acc[mb][r]);
+                acc[mb][r + 1] = relu_mfma(acc[mb][r + 1]);
+                top = max(max(top, __float_as_uint(acc[mb][r])), __float_as_uint(acc[mb][r + 1]));
+            }
+    } else {
+#pragma unroll
+        for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                top = max(top, __float_as_uint(acc[mb][r]) & 0x7FFFFFFFu);
+    }
+}
+
+// Every layer but the output on the fp32 matrix instruction, with the
+// caller's weights in global memory ([out][in], unpadded: rows and columns
+// past them are zero) and the biases in LDS; input(s) = feature 2s + g of the
+// lane's point.
+template <int NMB, typename In>
+__device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *lds, const SplitLayout &lay, In &&input,
+                                             int lane, floatx16 *acc) {
+    const int g = lane >> 5;
+    auto weight = [&](int l, int mb, int k) __attribute__((always_inline)) {
+        const int row = 32 * mb + (lane & 31), n_in = pk.dims[l];
+        const bool in = row < pk.dims[l + 1] && k < n_in;
+        const float w = ldg(pk.W[l] + (in ? row * n_in + k : 0));
+        return in ? w : 0.f;
+    };
+    uint32_t unused = 0;
+    load_bias<NMB>(reinterpret_cast<const float *>(lds + lay.l1_bias()), g, acc);
+#pragma unroll 1
+    for (int s = 0; s < pk.ks1; ++s) {
+        const float x = input(s);
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb)
+            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, mb, 2 * s + g), x, acc[mb], 0, 0, 0);
+    }
+    activate<NMB>(acc, pk.relu & 1, unused);
+    for (int h = 0; h < pk.n_hidden; ++h) {
+        floatx16 hin[NMB];
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb)
+            hin[mb] = acc[mb];
+        load_bias<NMB>(reinterpret_cast<const float *>(lds + lay.hidden_bias(h)), g, acc);
+#pragma unroll 1
+        for (int q = 0; q < NMB; ++q) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                // register r of m-block q holds feature crow(q, r, g)
+#pragma unroll
+                for (int mb = 0; mb < NMB; ++mb)
+                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(h + 1, mb, crow(q, r, g)), hin[0][r], acc[mb],
+                                                                   0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i + 1 < NMB; ++i)
+                hin[i] = hin[i + 1];
+        }
+        activate<NMB>(acc, pk.relu >> (h + 1) & 1, unused);
+    }
+}
+
+// KS1: K-steps of the first layer (16 features each).
+// LOG: the lo fragments are read from global memory (the L2), not LDS.
+template <int NMB, int KS1, bool LOG>
+__global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 in, Map32 out, FeatTable32 tin, FeatTable32 tout,
+                                                      F32Packed pk, int32_t n_tiles, int32_t windowed,
+                                                      int32_t out_offsets, int32_t xcd_ranges) {
+    extern __shared__ u32x4 smem[];
+    MapsLds &tab0 = *reinterpret_cast<MapsLds *>(smem);
+    // the maps through an address the compiler doesn't know: what is read
+    // through it is read there, not held in registers over the whole loop
+    auto maps = [&]() __attribute__((always_inline)) -> const MapsLds & {
+        int z = 0;
+        asm volatile("" : "+v"(z));
+        return *reinterpret_cast<const MapsLds *>(smem + z);
+    };
+    u32x4 *lds4 = smem + sizeof(MapsLds) / 16;
+    const char *lds = reinterpret_cast<const char *>(lds4);
+    constexpr int XS = 8 * KS1;      // input slots of a lane
+    const SplitLayout lay{NMB, KS1, pk.n_hidden, pk.f_out};
     const int lane = threadIdx.x & 63;
     const int g = lane >> 5;
     const int col = lane & 31;
@@ -111,158 +327,283 @@ __global__ void __launch_bounds__(512) mlp_f32_kernel(Map32 in, Map32 out, FeatT
         n_waves = nb * waves_per_block;
         t_end = n_tiles;
     }
-    const int F = in.n_features;
+    const int F = in.n_features, n_points = in.n_points, rank_in = in.rank, rank_out = out.rank;
 
-    // ---- gather: lane (col, g) loads feature 2s+g of its point for K-step
-    //      s.  The two feature pointers of a K-step come from the kernel
-    //      arguments (entries past the last feature repeat it, so the loads
-    //      are unconditional and their count fixed); only the dimensions where
-    //      the wave touches an edge get a boundary fix-up.  The loads of the
-    //      wave's next tile are issued before the current tile's layers run.
-    float xn[KS1MAX];
-    bool nvalid = false;
-    auto gather = [&](int tile) {
-        const int b = tile * 32 + col;
-        nvalid = b < in.n_points;
-        const Pt32 pt = locate32(in, nvalid ? b : in.n_points - 1);
-        const uint32_t edge = edge_dims32(in, pt);
-#pragma unroll
-        for (int s = 0; s < KS1MAX; ++s) {
-            const float *p = g ? tin.fptr[2 * s + 1] : tin.fptr[2 * s];
-            int32_t idx = pt.pe;
-            if (edge)
-                idx += edge_fix32(in, pt, g ? tin.raw8[2 * s + 1] : tin.raw8[2 * s], edge);
-            // (with PF the load count is fixed, so waiting for this tile's
-            // loads never waits for the next tile's)
-            xn[s] = (PF || s < pk.ks1) ? ldg(p + idx) : 0.f;
-            if (s % 8 == 7)
-                __builtin_amdgcn_sched_barrier(0);   // bound the live addresses
-        }
-    };
-    // (without PF -- a wave with a single tile, or the widest variant, which
-    // has no registers for a second set -- each tile is gathered just before
-    // its use)
-    constexpr bool kPrefetch = PF && !(NMB == 4 && KS1MAX == 32);
-    // the first tile's loads go out before the weights are staged (their
-    // latencies overlap) where registers allow -- H = 64, or at most 16
-    // inputs (wider H = 128 variants would spill) -- and, without prefetch,
-    // when it is the wave's only tile
-    constexpr bool kEarly = NMB == 2 || KS1MAX <= 8;
-    bool gathered = false;
-    if (kEarly && wave_id < t_end && (kPrefetch || wave_id + n_waves >= t_end)) {
-        gather(wave_id);
-        gathered = true;
-    }
-
-    // stage the packed weights once per block
     {
-        const float4 *src = reinterpret_cast<const float4 *>(pk.image);
-        float4 *dstl = reinterpret_cast<float4 *>(lds);
-        const int n4 = pk.lds_bytes / 16;
-        for (int i = threadIdx.x; i < n4; i += blockDim.x)
-            dstl[i] = src[i];
+        const int t = threadIdx.x;
+        constexpr int kWords = (int)(sizeof(Map32) / 4);
+        static_assert(kWords <= 64, "one word per thread");
+        if (t < kTableMaxF) {
+            tab0.fptr[t] = tin.fptr[t];
+            tab0.raw8[t] = tin.raw8[t];
+        } else if (t < 64 + kFoutMax) {
+            tab0.optr[t - 64] = const_cast<float *>(tout.fptr[t - 64]);
+            tab0.oraw8[t - 64] = tout.raw8[t - 64];
+        } else if (t >= 128 && t < 128 + kWords) {
+            ((int32_t *)&tab0.in)[t - 128] = ((const int32_t *)&in)[t - 128];
+        } else if (t >= 192 && t < 192 + kWords) {
+            ((int32_t *)&tab0.out)[t - 192] = ((const int32_t *)&out)[t - 192];
+        }
     }
     __syncthreads();
-    if (kPrefetch && !gathered && wave_id < t_end)
-        gather(wave_id);
+
+    // ---- gather: lane (col, g) loads features 2t + g of its point through the
+    //      table's entry of that feature (entries past the last feature repeat
+    //      it).  Eight slots at a time: table entries, boundary fix-ups along
+    //      the dimensions where the wave touches an edge, then all the loads;
+    //      the last four slots are left out where no feature reaches them.
+    auto gather = [&](int tile, float (&x)[XS]) __attribute__((always_inline)) {
+        const int b = tile * 32 + col;
+        const MapsLds &tab = maps();
+        const Pt32 pt = locate_lds(tab.in, rank_in, b < n_points ? b : n_points - 1);
+        const uint32_t edge = windowed ? edge_lds(tab.in, rank_in, pt) : 0u;
+        static_for<0, 2 * KS1>([&](auto q) __attribute__((always_inline)) {
+            constexpr int s0 = 4 * q;
+            if (q < 2 * KS1 - 1 || s0 < pk.ks1) {
+                int32_t idx[4] = {pt.pe, pt.pe, pt.pe, pt.pe};
+                if (edge) {
+                    const uint32_t raw[4] = {tab.raw8[2 * s0 + g], tab.raw8[2 * s0 + 2 + g], tab.raw8[2 * s0 + 4 + g],
+                                             tab.raw8[2 * s0 + 6 + g]};
+                    fix_lds<4>(tab.in, pt, edge, raw, idx);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[s0 + j] = ldg(tab.fptr[2 * (s0 + j) + g] + idx[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[s0 + j] = 0.f;
+            }
+        });
+    };
+    float xn[XS];
+    // the first tile's loads go out before the weights are staged
+    if (wave_id < t_end)
+        gather(wave_id, xn);
+
+    // stage the split weights once per block
+    {
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(pk.image);
+        const int n4 = lay.image_lds(LOG) / 16;
+        for (int i = threadIdx.x; i < n4; i += blockDim.x)
+            lds4[i] = src[i];
+    }
+    __syncthreads();
 
     for (int tile = wave_id; tile < t_end; tile += n_waves) {
         const int b = tile * 32 + col;
-        if (!kPrefetch && !gathered)
-            gather(tile);
-        gathered = false;
-        const bool valid = nvalid;
-        float x[KS1MAX];
-#pragma unroll
-        for (int s = 0; s < KS1MAX; ++s)
-            x[s] = xn[s];
-        if (kPrefetch)
-            gather(tile + n_waves < t_end ? tile + n_waves : tile);
-#pragma unroll
-        for (int s = 0; s < KS1MAX; ++s)
-            x[s] = (valid && 2 * s + g < F) ? x[s] : 0.f;
-
+        const bool valid = b < n_points;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // nothing read from LDS is held from one tile to the next
+        uint32_t top = pk.plain ? kBig : 0;   // the largest magnitude met
+        Split b1[KS1];
         floatx16 acc[NMB];
-        // ---- first layer: K = 2 * ks1 (zero-padded features)
-        load_bias<NMB>(lds + lay.l1_bias(), g, acc);
+        const u32x4 *fl = lds4 + ln;                                        // this lane's part of the LDS fragments
+        const u32x4 *gl = reinterpret_cast<const u32x4 *>(pk.image) + ln;   // ... of the global ones
+        // One layer: B fragments b[K-step], weights' hi and mid fragments at
+        // byte `hm`, lo at `lw`, bias at `bias`; two m-blocks at a time (with
+        // independent accumulators, which keeps the matrix core busy).  Of the
+        // six products hi hi goes into `main` and the small ones into `sub`, so
+        // that a sum of its final size is rounded once per K-step, not six
+        // times.  A K-step has three phases -- the hi, mid and lo fragments'
+        // products, 6, 4 and 2 matrix instructions -- and each fragment pair
+        // is read two phases ahead of its own (global ones a K-step more).
+        // prepare() runs once the first fragments are on their way.
+        auto layer = [&](auto &b, auto ksteps, int hm, int lw, int bias, bool relu,
+                         auto &&prepare) __attribute__((always_inline)) {
+            constexpr int K = decltype(ksteps)::value, Q = K * (NMB / 2);
+            u32x4 h[2], m[2], l[2][2];
+            const int hb = hm / 16, lb = lw / 16;
+            auto at = [&](int q, int i) __attribute__((always_inline)) { return (q % K) * NMB + 2 * (q / K) + i; };
+            auto read_h = [&](int q) __attribute__((always_inline)) {
+                h[0] = fl[hb + at(q, 0) * 128];
+                h[1] = fl[hb + at(q, 1) * 128];
+            };
+            auto read_m = [&](int q) __attribute__((always_inline)) {
+                m[0] = fl[hb + at(q, 0) * 128 + 64];
+                m[1] = fl[hb + at(q, 1) * 128 + 64];
+            };
+            auto read_l = [&](int q, u32x4 (&d)[2]) __attribute__((always_inline)) {
+                d[0] = (LOG ? gl : fl)[lb + at(q, 0) * 64];
+                d[1] = (LOG ? gl : fl)[lb + at(q, 1) * 64];
+            };
+            if (LOG)
+                read_l(0, l[0]);
+            read_h(0);
+            read_m(0);
+            __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+            prepare();
+            floatx16 main[2], sub[2];
+            static_for<0, Q>([&](auto q) __attribute__((always_inline)) {
+                constexpr int s = q % K, p = q / K;
+                if (s == 0)
+                    load_bias<NMB, 2>(reinterpret_cast<const float *>(lds + bias), ln >> 5, main, 2 * p);
+                if (!LOG)
+                    read_l(q, l[0]);
+                else if (q + 1 < Q)
+                    read_l(q + 1, l[(q + 1) % 2]);
+                __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+                const floatx16 zero = {};
+                sub[0] = mfma(h[0], b[s].mid, s == 0 ? zero : sub[0]);
+                sub[1] = mfma(h[1], b[s].mid, s == 0 ? zero : sub[1]);
+                sub[0] = mfma(h[0], b[s].lo, sub[0]);
+                sub[1] = mfma(h[1], b[s].lo, sub[1]);
+                main[0] = mfma(h[0], b[s].hi, main[0]);
+                main[1] = mfma(h[1], b[s].hi, main[1]);
+                if (q + 1 < Q)
+                    read_h(q + 1);
+                __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+                sub[0] = mfma(m[0], b[s].hi, sub[0]);
+                sub[1] = mfma(m[1], b[s].hi, sub[1]);
+                sub[0] = mfma(m[0], b[s].mid, sub[0]);
+                sub[1] = mfma(m[1], b[s].mid, sub[1]);
+                if (q + 1 < Q)
+                    read_m(q + 1);
+                __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+                sub[0] = mfma(l[LOG ? q % 2 : 0][0], b[s].hi, sub[0]);
+                sub[1] = mfma(l[LOG ? q % 2 : 0][1], b[s].hi, sub[1]);
+                if (s == K - 1) {
 #pragma unroll
-        for (int s = 0; s < KS1MAX; ++s) {
-            if (s < pk.ks1) {
-                FragA<NMB> a = lds_frag<NMB>(lds + lay.l1(), s, lane);
+                    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int mb = 0; mb < NMB; ++mb)
-                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb], x[s], acc[mb], 0, 0, 0);
-            }
-        }
-        if (pk.act[0] == HPACML_ACT_RELU) {
+                        for (int r = 0; r < 16; ++r)
+                            main[i][r] += sub[i][r];
+                    activate<2>(main, relu, top);
+                    acc[2 * p] = main[0];
+                    acc[2 * p + 1] = main[1];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        };
+        // ---- first layer
+        layer(b1, std::integral_constant<int, KS1>{}, lay.l1(), lay.l1_lo(), lay.l1_bias(), pk.relu & 1, [&]() {
+            static_for<0, KS1>([&](auto s) __attribute__((always_inline)) {
+                floatx8 v;
 #pragma unroll
-            for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[mb][r] = relu_mfma(acc[mb][r]);
-        }
+                for (int j = 0; j < 8; ++j) {
+                    // zero where there is no feature (only in the last K-step)
+                    v[j] = s < KS1 - 1 || 2 * (8 * s + j) + g < F ? xn[8 * s + j] : 0.f;
+                    top = max(top, __float_as_uint(v[j]) & 0x7FFFFFFFu);
+                }
+                b1[s] = split8(v);
+            });
+            const auto sw = __builtin_amdgcn_permlane32_swap(top, top, false, false);
+            const uint32_t largest = max(sw[0], sw[1]);   // of the point's inputs
+            if (largest - 1u < kTiny - 1u)
+                top = kBig;
+        });
 
         // ---- hidden layers H -> H
-        for (int h = 0; h < pk.n_hidden; ++h) {
-            floatx16 hin[NMB];
+        auto hidden = [&](int h) __attribute__((always_inline)) {
+            Split bs[2 * NMB];
+            layer(bs, std::integral_constant<int, 2 * NMB>{}, lay.hidden(h), lay.hidden_lo(h), lay.hidden_bias(h),
+                  pk.relu >> (h + 1) & 1, [&]() __attribute__((always_inline)) {
+                      static_for<0, 2 * NMB>([&](auto s) __attribute__((always_inline)) {
+                          floatx8 v;
 #pragma unroll
-            for (int mb = 0; mb < NMB; ++mb)
-                hin[mb] = acc[mb];
-            load_bias<NMB>(lds + lay.hidden_bias(h), g, acc);
-            const float *wl = lds + lay.hidden(h);
-#pragma unroll
-            for (int s = 0; s < 16 * NMB; ++s) {
-                FragA<NMB> a = lds_frag<NMB>(wl, s, lane);
-                const float bv = hin[s / 16][s % 16];
-#pragma unroll
-                for (int mb = 0; mb < NMB; ++mb)
-                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb], bv, acc[mb], 0, 0, 0);
-            }
-            if (pk.act[h + 1] == HPACML_ACT_RELU) {
-#pragma unroll
-                for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        acc[mb][r] = relu_mfma(acc[mb][r]);
-            }
+                          for (int j = 0; j < 8; ++j)
+                              v[j] = acc[s / 2][8 * (s % 2) + j];
+                          bs[s] = split8(v);
+                      });
+                  });
+        };
+        for (int h = 0; h < pk.n_hidden; ++h)
+            hidden(h);
+        if (__any(top >= kBig)) {
+            // a value without a split: this tile again on the fp32 instruction
+            const MapsLds &tab = maps();
+            const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
+            layers_plain<NMB>(pk, lds, lay, [&](int s) __attribute__((always_inline)) {
+                const int f = 2 * s + g;
+                const uint32_t raw[1] = {tab.raw8[f]};
+                int32_t idx[1] = {pt.pe};
+                fix_lds<1>(tab.in, pt, 15u, raw, idx);
+                const float v = ldg(tab.fptr[f] + idx[0]);
+                return f < F ? v : 0.f;
+            }, lane, acc);
         }
 
-        // ---- output layer (VALU) + scatter through the `from` map
-        const Pt32 po = locate32(out, valid ? b : in.n_points - 1);
-        const uint32_t oedge = edge_dims32(out, po);
-        const bool orelu = pk.act[pk.n_hidden + 1] == HPACML_ACT_RELU;
-        for (int go = 0; go < pk.f_out; ++go) {
-            const float *w = lds + lay.out_w() + (go * 2 + g) * (16 * NMB);
-            float part = 0.f;
+        // the next tile's inputs are requested here, where the activations'
+        // splits are free; they arrive during the output layer and the other
+        // wave's work
+        if (tile + n_waves < t_end) {
+            gather(tile + n_waves, xn);
+        } else {
 #pragma unroll
-            for (int mb = 0; mb < NMB; ++mb)
+            for (int s = 0; s < XS; ++s)
+                xn[s] = 0.f;   // (keeps the old values from living through the tile)
+        }
+
+        // ---- output layer + scatter through the `from` map: four outputs by
+        //      sixteen 4 x 4 blocks of the fp32 matrix instruction, one k each
+        //      (v_mfma_f32_4x4x1_16b_f32): block l / 4 holds the points of lanes
+        //      4 (l / 4) .., and the eight blocks of a lane half share the A
+        //      operand of block `abid` (cbsz 3).  Each half sums its own
+        //      features; swapping halves leaves output 2i in lanes 0..31 and
+        //      2i + 1 in lanes 32..63.
+        const MapsLds &tab = maps();
+        const Pt32 po = locate_lds(tab.out, rank_out, valid ? b : n_points - 1);
+        const uint32_t oedge = out_offsets ? edge_lds(tab.out, rank_out, po) : 0u;
+        const bool orelu = pk.relu >> (pk.n_hidden + 1) & 1;
+        for (int go = 0; go < pk.f_out; go += 4) {
+            const float4 *wq = reinterpret_cast<const float4 *>(lds + lay.out_w(go / 4)) + ln;
+            float a[2 * NMB];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 wv = reinterpret_cast<const float4 *>(w + mb * 16)[q];
-                    part = fmaf(acc[mb][4 * q + 0], wv.x, part);
-                    part = fmaf(acc[mb][4 * q + 1], wv.y, part);
-                    part = fmaf(acc[mb][4 * q + 2], wv.z, part);
-                    part = fmaf(acc[mb][4 * q + 3], wv.w, part);
+            for (int i = 0; i < NMB / 2; ++i) {
+                const float4 w = wq[i * 64];
+                a[4 * i] = w.x;
+                a[4 * i + 1] = w.y;
+                a[4 * i + 2] = w.z;
+                a[4 * i + 3] = w.w;
+            }
+            floatx4 y[NMB];
+            static_for<0, 16 * NMB>([&](auto k) __attribute__((always_inline)) {
+                // m-blocks in turn: independent accumulators
+                constexpr int mb = k % NMB, r = k / NMB, i = (16 * mb + r) / 8;
+                const floatx4 zero = {};
+                y[mb] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[i], acc[mb][r], r == 0 ? zero : y[mb], 3, r % 8, 0);
+            });
+            floatx4 sum = y[0];
+#pragma unroll
+            for (int mb = 1; mb < NMB; ++mb)
+                sum += y[mb];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int o = go + 2 * i + g;
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[2 * i]), __float_as_uint(sum[2 * i + 1]),
+                                                                 false, false);
+                float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+                if (o < pk.f_out) {
+                    v += reinterpret_cast<const float *>(lds + lay.out_b())[o];
+                    if (orelu)
+                        v = fmaxf(v, 0.f);
+                    int32_t idx[1] = {po.pe};
+                    if (oedge) {
+                        const uint32_t raw[1] = {tab.oraw8[o]};
+                        fix_lds<1>(tab.out, po, oedge, raw, idx);
+                    }
+                    if (valid)
+                        stg(tab.optr[o] + idx[0], v);
                 }
-            part += __shfl_xor(part, 32);
-            float y = part + lds[lay.out_b() + go];
-            if (orelu)
-                y = fmaxf(y, 0.f);
-            if (g == 0 && valid)
-                stg(const_cast<float *>(tout.fptr[go]) + (po.pe + (oedge ? edge_fix32(out, po, tout.raw8[go], oedge) : 0)), y);
+            }
         }
     }
 }
 
-template <int NMB, int KS1MAX>
+SplitLayout split_layout(const F32Packed &pk) {
+    return SplitLayout{pk.hid / 32, (pk.ks1 + 7) / 8, pk.n_hidden, pk.f_out};
+}
+
+template <int NMB, int KS1, bool LOG>
 hipError_t launch_t(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                     const F32Packed &pk, hipStream_t stream) {
     const int32_t n_tiles = (in.n_points + 31) / 32;
     const int threads = NMB == 4 ? 512 : 256;
     const int waves = threads / 64;
-    const size_t lds = (size_t)pk.lds_bytes;
-    int per_cu = (int)(163840 / (lds + 1024));
-    per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
+    const size_t lds = (size_t)split_layout(pk).lds(LOG);
+    // blocks per CU: by registers, one of 8 waves (H = 128) or three of 4; by LDS
+    int per_cu = NMB == 4 ? 1 : 3;
+    per_cu = std::max(1, std::min(per_cu, (int)(kLdsMax / (lds + 1024))));
     int64_t grid = 256LL * per_cu;
     const int64_t need = (n_tiles + waves - 1) / waves;
     if (grid > need)
@@ -271,17 +612,32 @@ hipError_t launch_t(const Map32 &in, const Map32 &out, const FeatTable32 &tin, c
     bool window = false;
     for (int d = 0; d < in.rank; ++d)
         window = window || in.omin[d] != 0 || in.omax[d] != 0;
+    bool offsets = false;   // of the `from` map
+    for (int d = 0; d < out.rank; ++d)
+        offsets = offsets || out.omin[d] != 0 || out.omax[d] != 0;
     const int32_t xcd_ranges = window && grid % 8 == 0;
-    // prefetch only when waves take more than one tile
-    const int64_t per_wave = xcd_ranges ? (n_tiles + 7) / 8 : n_tiles, waves_each = xcd_ranges ? grid / 8 * waves : grid * waves;
-    auto kern = per_wave > waves_each ? mlp_f32_kernel<NMB, KS1MAX, true> : mlp_f32_kernel<NMB, KS1MAX, false>;
+    auto kern = mlp_f32_kernel<NMB, KS1, LOG>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, stream, in, out, tin, tout, pk, n_tiles,
-                       xcd_ranges);
+                       (int32_t)window, (int32_t)offsets, xcd_ranges);
     return hipGetLastError();
 }
+
+template <int NMB, int KS1>
+hipError_t launch_k(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
+                    const F32Packed &pk, hipStream_t stream) {
+    return split_layout(pk).lds(false) <= kLdsMax ? launch_t<NMB, KS1, false>(in, out, tin, tout, pk, stream)
+                                                  : launch_t<NMB, KS1, true>(in, out, tin, tout, pk, stream);
+}
+
+// rounded to nearest even, as the device's conversion (finite values)
+inline uint16_t rne(float x) {
+    uint32_t u = __builtin_bit_cast(uint32_t, x);
+    return (uint16_t)((u + 0x7FFFu + (u >> 16 & 1u)) >> 16);
+}
+inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
 }  // namespace
 
@@ -296,69 +652,98 @@ bool f32_fast_supported(int n_layers, const int32_t *dims, int compute) {
             return false;
     if (dims[0] > 64 || dims[n_layers] > kFoutMax)
         return false;
-    return f32_image_floats(n_layers, dims) * 4 <= 150 * 1024;
+    return SplitLayout{H / 32, (dims[0] + 15) / 16, n_layers - 2, dims[n_layers]}.lds(true) <= kLdsMax;
 }
 
 size_t f32_image_floats(int n_layers, const int32_t *dims) {
-    F32Layout lay{dims[1] / 32, (dims[0] + 1) / 2, n_layers - 2, dims[n_layers]};
-    size_t n = (size_t)lay.total();
-    return (n + 3) & ~size_t(3);
+    return (size_t)SplitLayout{dims[1] / 32, (dims[0] + 15) / 16, n_layers - 2, dims[n_layers]}.total() / 4;
 }
 
-// Host packing of the LDS image (see F32Layout): A fragments in the order the
-// lanes read them, biases and output weights in the C-fragment order.
-void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b,
-              float *img) {
-    const int H = dims[1], NMB = H / 32, Fin = dims[0], Fout = dims[n_layers];
-    F32Layout lay{NMB, (Fin + 1) / 2, n_layers - 2, Fout};
-    for (int i = 0; i < lay.total(); ++i)
-        img[i] = 0.f;
-    auto put_bias = [&](int off, const float *bias) {
+// Host packing of the split image (see SplitLayout): A fragments in the order
+// the lanes read them, biases and output weights in the C-fragment order.
+// Returns whether every weight has a three-way split.
+bool f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *img) {
+    const int H = dims[1], NMB = H / 32, Fin = dims[0], Fout = dims[n_layers], NH = n_layers - 2;
+    const SplitLayout sl{NMB, (Fin + 15) / 16, NH, Fout};
+    std::fill(img, img + sl.total() / 4, 0.f);
+    auto put_bias = [&](float *dst, const float *bias) {
         for (int g = 0; g < 2; ++g)
             for (int mb = 0; mb < NMB; ++mb)
                 for (int r = 0; r < 16; ++r)
-                    img[off + (g * NMB + mb) * 16 + r] = bias[crow(mb, r, g)];
+                    dst[(g * NMB + mb) * 16 + r] = bias[crow(mb, r, g)];
     };
-    // first layer: K-step s, lane l -> W1[32mb + l%32][2s + l/32]
-    for (int s = 0; s < lay.ks1; ++s)
-        for (int l = 0; l < 64; ++l)
+    bool fine = true;
+    auto in_range = [&](int l) {   // the layer's weights: zero, or the largest splits exactly
+        float top = 0.f;
+        for (int64_t i = 0; i < (int64_t)dims[l] * dims[l + 1]; ++i)
+            top = std::max(top, std::fabs(W[l][i]));
+        return top == 0.f || top >= 0x1p-100f;
+    };
+    // one layer's fragments: K-step s, m-block mb, lane l, element j is
+    // weight [32 mb + l % 32][feature(s, l / 32, j)]
+    auto put_layer = [&](const float *Wl, int K, int steps, int hm, int lo, auto &&feature) {
+        uint16_t *d = reinterpret_cast<uint16_t *>(img);
+        for (int s = 0; s < steps; ++s)
             for (int mb = 0; mb < NMB; ++mb) {
-                const int k = 2 * s + l / 32, o = 32 * mb + l % 32;
-                img[lay.l1() + (s * 64 + l) * NMB + mb] = k < Fin ? W[0][(size_t)o * Fin + k] : 0.f;
+                uint16_t *qh = d + (hm + (s * NMB + mb) * 2 * kFragBytes) / 2, *qm = qh + kFragBytes / 2;
+                uint16_t *ql = d + (lo + (s * NMB + mb) * kFragBytes) / 2;
+                for (int l = 0; l < 64; ++l)
+                    for (int j = 0; j < 8; ++j) {
+                        const int k = feature(s, l / 32, j);
+                        const float w = k < K ? Wl[(size_t)(32 * mb + l % 32) * K + k] : 0.f;
+                        if (!(std::fabs(w) < 0x1p127f)) {
+                            fine = false;
+                            continue;
+                        }
+                        const uint16_t h = rne(w);
+                        const float r = w - bf16_float(h);
+                        const uint16_t m = rne(r);
+                        qh[l * 8 + j] = h;
+                        qm[l * 8 + j] = m;
+                        ql[l * 8 + j] = rne(r - bf16_float(m));
+                    }
             }
-    put_bias(lay.l1_bias(), b[0]);
-    for (int h = 0; h < lay.n_hidden; ++h) {
-        const float *Wh = W[h + 1];
-        for (int s = 0; s < 16 * NMB; ++s)
-            for (int l = 0; l < 64; ++l)
-                for (int mb = 0; mb < NMB; ++mb) {
-                    const int k = kperm(s, l / 32), o = 32 * mb + l % 32;
-                    img[lay.hidden(h) + (s * 64 + l) * NMB + mb] = Wh[(size_t)o * H + k];
-                }
-        put_bias(lay.hidden_bias(h), b[h + 1]);
+    };
+    for (int l = 0; l + 1 < n_layers; ++l)
+        fine = fine && in_range(l);
+    put_layer(W[0], Fin, sl.ks, sl.l1(), sl.l1_lo(), [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
+    put_bias(img + sl.l1_bias() / 4, b[0]);
+    for (int h = 0; h < NH; ++h) {
+        // element j of K-step s is register 8 (s % 2) + j of m-block s / 2
+        put_layer(W[h + 1], H, 2 * NMB, sl.hidden(h), sl.hidden_lo(h),
+                  [](int s, int g, int j) { return crow(s / 2, 8 * (s % 2) + j, g); });
+        put_bias(img + sl.hidden_bias(h) / 4, b[h + 1]);
     }
     const float *Wo = W[n_layers - 1];
+    for (int o = 0; o < Fout; ++o)
+        for (int i = 0; i < 2 * NMB; ++i)
+            for (int g = 0; g < 2; ++g)
+                for (int bb = 0; bb < 8; ++bb) {
+                    const int r = 8 * i + bb, lane = 32 * g + 4 * bb + o % 4;
+                    img[sl.out_w(o / 4) / 4 + (i / 4 * 64 + lane) * 4 + i % 4] = Wo[(size_t)o * H + crow(r / 16, r % 16, g)];
+                }
     for (int go = 0; go < Fout; ++go)
-        for (int g = 0; g < 2; ++g)
-            for (int mb = 0; mb < NMB; ++mb)
-                for (int r = 0; r < 16; ++r)
-                    img[lay.out_w() + (go * 2 + g) * 16 * NMB + mb * 16 + r] =
-                        Wo[(size_t)go * H + crow(mb, r, g)];
-    for (int go = 0; go < Fout; ++go)
-        img[lay.out_b() + go] = b[n_layers - 1][go];
+        img[sl.out_b() / 4 + go] = b[n_layers - 1][go];
+    return fine;
 }
 
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                           const F32Packed &pk, hipStream_t stream) {
     if (in.n_points == 0)
         return hipSuccess;
-    if (pk.hid == 128)
-        return pk.ks1 <= 8 ? launch_t<4, 8>(in, out, tin, tout, pk, stream)
-                           : (pk.ks1 <= 20 ? launch_t<4, 20>(in, out, tin, tout, pk, stream)
-                                           : launch_t<4, 32>(in, out, tin, tout, pk, stream));
-    return pk.ks1 <= 8 ? launch_t<2, 8>(in, out, tin, tout, pk, stream)
-                       : (pk.ks1 <= 20 ? launch_t<2, 20>(in, out, tin, tout, pk, stream)
-                                       : launch_t<2, 32>(in, out, tin, tout, pk, stream));
+    const int ks = (pk.ks1 + 7) / 8;
+#define HPACML_F32(NMB)                                                                     \
+    switch (ks) {                                                                           \
+    case 1: return launch_k<NMB, 1>(in, out, tin, tout, pk, stream);                        \
+    case 2: return launch_k<NMB, 2>(in, out, tin, tout, pk, stream);                        \
+    case 3: return launch_k<NMB, 3>(in, out, tin, tout, pk, stream);                        \
+    default: return launch_k<NMB, 4>(in, out, tin, tout, pk, stream);                       \
+    }
+    if (pk.hid == 128) {
+        HPACML_F32(4)
+    }
+    HPACML_F32(2)
+#undef HPACML_F32
 }
 
 const char *f32_variant_name(const F32Packed &pk) {
