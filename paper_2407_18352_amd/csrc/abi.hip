@@ -48,6 +48,8 @@ struct hpacml_model_s {
     DevModel gen{};
     float *f32_img = nullptr;   // the fp32 kernel's packed image
     F32Packed f32{};
+    F32WPacked f32w{};               // fp32 models outside the uniform widths whose weights fit in LDS
+    bool wide = false;               // f32w serves 32-bit maps in place of the layer-by-layer path
     uint16_t *bf16_frags = nullptr;  // packed fragments of the bf16 kernel
     BF16Packed bf16{};
     uint8_t *bf16r_buf = nullptr;    // weight stream, output fragments, biases of the register-resident bf16 kernel
@@ -657,6 +659,24 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
             m->variant = Variant::BF16;
             m->fast_name = bf16_variant_name(m->bf16);
         }
+        if (m->variant == Variant::Generic && f32w_supported(n_layers, dims, compute)) {
+            std::vector<float> img(f32w_image_floats(n_layers, dims));
+            m->f32w.plain = !f32w_pack(n_layers, dims, W, b, img.data(), &m->f32w);
+            s = upload(&m->f32_img, img.data(), img.size());
+            if (s != HPACML_OK) {
+                hpacml_model_destroy(m);
+                return s;
+            }
+            m->f32w.relu = 0;
+            for (int l = 0; l < n_layers; ++l) {
+                m->f32w.relu |= act[l] == HPACML_ACT_RELU ? 1u << l : 0u;
+                m->f32w.W[l] = m->gen.W[l];
+            }
+            for (int l = 0; l <= n_layers; ++l)
+                m->f32w.dims[l] = dims[l];
+            m->f32w.image = m->f32_img;
+            m->wide = true;
+        }
         if (m->variant == Variant::Generic)
             m->padded = false;
         else if (m->padded)
@@ -1012,7 +1032,8 @@ bool snapshot_t32(const hpacml_map *in) {
 const char *kernel_name(const hpacml_model *model, bool fast, int64_t n_points) {
     if (fast && model->variant != Variant::Generic)
         return model->fast_name.c_str();
-    if (layers_ready(model->layers, n_points))
+    // (the layer-by-layer path's name too where all layers run in one kernel)
+    if ((fast && model->wide) || layers_ready(model->layers, n_points))
         return layers_name(model->layers);
     return model->compute == HPACML_BF16 ? "mlp_generic_bf16" : "mlp_generic_f32";
 }
@@ -1158,7 +1179,10 @@ hpacml_status hpacml_infer(const hpacml_model *model, const hpacml_map *in, cons
     case Variant::F32: e = launch_mlp_f32(in->m32, out->m32, in->tab, out->tab, model->f32, st); break;
     case Variant::BF16: e = launch_mlp_bf16(in->m32, out->m32, in->tab, out->tab, model->bf16, st); break;
     case Variant::BF16R: e = launch_mlp_bf16r(in->m32, out->m32, in->tab, out->tab, model->bf16r, st); break;
-    default: e = launch_general(model, in->dev, out->dev, st); break;
+    default:
+        e = fast && model->wide ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
+                                : launch_general(model, in->dev, out->dev, st);
+        break;
     }
     return hip_status(e);
 }
@@ -1183,7 +1207,10 @@ hpacml_status hpacml_infer_noalloc(const hpacml_model *model, const hpacml_map *
         case Variant::F32: e = launch_mlp_f32(in->m32, out->m32, in->tab, out->tab, model->f32, st); break;
         case Variant::BF16: e = launch_mlp_bf16(in->m32, out->m32, in->tab, out->tab, model->bf16, st); break;
         case Variant::BF16R: e = launch_mlp_bf16r(in->m32, out->m32, in->tab, out->tab, model->bf16r, st); break;
-        default: e = launch_mlp_generic(in->dev, out->dev, model->gen, st); break;
+        default:
+            e = fast && model->wide ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
+                                    : launch_mlp_generic(in->dev, out->dev, model->gen, st);
+            break;
         }
         return hip_status(e);
     }

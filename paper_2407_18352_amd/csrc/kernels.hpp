@@ -84,6 +84,25 @@ hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &
                           const F32Packed &pk, hipStream_t stream);
 const char *f32_variant_name(const F32Packed &pk);
 
+// fp32 fused kernel for one or two hidden layers of any widths whose weights
+// fit in LDS (F_in <= 48, F_out <= 8).
+struct F32WPacked {
+    int32_t nb1, nb2;     // blocks of 32 neurons of the hidden layers (nb2 0: one hidden layer)
+    int32_t f_out;
+    uint32_t relu;        // bit l: layer l has a ReLU
+    int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
+    const float *image;   // device: the packed split image
+    int32_t dims[4];
+    const float *W[3];    // the caller's layers, read for values without a split
+};
+bool f32w_supported(int n_layers, const int32_t *dims, int compute);
+size_t f32w_image_floats(int n_layers, const int32_t *dims);
+// Packs the image and sets nb1, nb2, f_out; false when a weight has no split.
+bool f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
+               F32WPacked *pk);
+hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
+                           const F32WPacked &pk, hipStream_t stream);
+
 // bf16 fused kernel: hidden layers of one width H in {256, 512}; activations
 // in LDS, weights streamed from L2 as prepacked MFMA fragments.
 struct BF16Packed {

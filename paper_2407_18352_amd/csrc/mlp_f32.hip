@@ -41,105 +41,11 @@
 // of that kind (or such an activation) computes its tile again on the fp32
 // matrix instruction, with the caller's weights read from global memory; so
 // does every wave of a model with such a weight or layer of weights.
-#include <algorithm>
-#include <cmath>
-#include <type_traits>
-
-#include "kernels.hpp"
+#include "mlp_f32.hpp"
 
 namespace hpacml {
 
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx8 __attribute__((ext_vector_type(8)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kFoutMax = 8;
-// scheduling-barrier mask: only VALU, SALU and transcendental instructions
-// may be moved across
-constexpr int kSchedAluOnly = 0x2 | 0x4 | 0x400;
-constexpr int kFragBytes = 1024;        // one A operand: 64 lanes x 8 bf16
-constexpr int kLdsMax = 160 * 1024;     // LDS of a CU
-constexpr uint32_t kBig = 0x7F000000u;  // bits of 2^127: this and more has no three-way split
-constexpr uint32_t kTiny = 0x0D800000u; // bits of 2^-100: below it the lo part loses bits
-
-// What a block keeps of the two maps in LDS, ahead of the split image: the
-// feature tables, read with a lane's own feature number, and the 32-bit
-// views, whose fields would otherwise occupy (and spill) scalar registers
-// over the whole kernel.
-struct MapsLds {
-    Map32 in, out;
-    const float *fptr[kTableMaxF];
-    float *optr[kFoutMax];
-    uint32_t raw8[kTableMaxF], oraw8[kFoutMax];
-};
-static_assert(sizeof(MapsLds) % 16 == 0 && sizeof(Map32) % 16 == 0, "read 16 bytes at a time");
-
-// locate32 on a view in LDS: unused dimensions (count 1, stride 0) add
-// nothing, those past the second are skipped for the usual ranks.
-__device__ __forceinline__ Pt32 locate_lds(const Map32 &m, int rank, int32_t b) {
-    Pt32 r;
-    uint32_t rem = (uint32_t)b;
-    r.pe = 0;
-    auto dim = [&](int d) __attribute__((always_inline)) {
-        uint32_t k = rem;
-        if (d > 0) {
-            rem = (uint32_t)(((uint64_t)rem * m.magic[d]) >> m.shift[d]);
-            k -= rem * (uint32_t)m.count[d];
-        }
-        r.p[d] = m.start[d] + (int32_t)k * m.step[d];
-        r.pe += r.p[d] * m.stride[d];
-    };
-    r.p[1] = r.p[2] = r.p[3] = 0;
-    if (rank > 1) {
-        if (rank > 2) {
-            dim(3);
-            dim(2);
-        }
-        dim(1);
-    }
-    dim(0);
-    return r;
-}
-
-// The dimensions along which some lane of the wave reads outside the arrays.
-__device__ __forceinline__ uint32_t edge_lds(const Map32 &m, int rank, const Pt32 &r) {
-    uint32_t edge = 0;
-#pragma unroll
-    for (int d = 0; d < HPACML_MAX_RANK; ++d)
-        if (d < rank && __any(r.p[d] + m.omin[d] < 0 || r.p[d] + m.omax[d] >= m.extent[d]))
-            edge |= 1u << d;
-    return edge;
-}
-
-// Boundary corrections of N accesses with raw offsets raw[] at point r, added
-// to idx[]; `edge`: the dimensions along which some lane of the wave leaves
-// the arrays.  Per dimension dl = clamp(at, 0, n - 1) - at (zero inside):
-// clamp adds dl strides, periodic one wrap in dl's direction (|offset| <=
-// extent).
-template <int N>
-__device__ __forceinline__ void fix_lds(const Map32 &m, const Pt32 &r, uint32_t edge, const uint32_t (&raw)[N],
-                                        int32_t (&idx)[N]) {
-#pragma unroll
-    for (int d = 0; d < HPACML_MAX_RANK; ++d) {
-        if (edge & (1u << d)) {
-            const int32_t n = m.extent[d], st = m.stride[d];
-            const bool per = m.bnd[d] == HPACML_BND_PERIODIC;
-            const int32_t lim = per ? 1 : INT32_MAX, mul = per ? (int32_t)((uint32_t)n * (uint32_t)st) : st;
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const int32_t at = r.p[d] + (int32_t)(int8_t)(raw[j] >> (8 * d));
-                const int32_t dl = min(max(at, 0), n - 1) - at;
-                idx[j] += min(max(dl, -lim), lim) * mul;
-            }
-        }
-    }
-}
 
 // Split image offsets (bytes).  In LDS: biases and output layer (fp32), the hi
 // and mid fragments of every layer, and the lo fragments; with lo_global the
@@ -169,80 +75,6 @@ struct SplitLayout {
     __host__ __device__ int lds(bool lo_global) const { return image_lds(lo_global) + (int)sizeof(MapsLds); }
 };
 
-// feature held by lane half g in register r of m-block mb
-__host__ __device__ inline int crow(int mb, int r, int g) { return 32 * mb + 8 * (r / 4) + 4 * g + (r % 4); }
-
-// N m-blocks from m-block mb0 on
-template <int NMB, int N = NMB>
-__device__ __forceinline__ void load_bias(const float *bias, int g, floatx16 *acc, int mb0 = 0) {
-#pragma unroll
-    for (int mb = 0; mb < N; ++mb) {
-        const float4 *p = reinterpret_cast<const float4 *>(bias + (g * NMB + mb0 + mb) * 16);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float4 v = p[q];
-            acc[mb][4 * q + 0] = v.x;
-            acc[mb][4 * q + 1] = v.y;
-            acc[mb][4 * q + 2] = v.z;
-            acc[mb][4 * q + 3] = v.w;
-        }
-    }
-}
-
-// compile-time loop: fn(std::integral_constant<int, i>) for i in [B, E)
-template <int B, int E, typename Fn>
-__device__ __forceinline__ void static_for(Fn &&fn) {
-    if constexpr (B < E) {
-        fn(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(fn);
-    }
-}
-
-// Eight floats as three B fragments, v = hi + mid + lo exactly (see above).
-struct Split {
-    u32x4 hi, mid, lo;
-};
-__device__ __forceinline__ Split split8(floatx8 v) {
-    Split f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
-        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
-        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
-        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
-        f.hi[i] = h;
-        f.mid[i] = m;
-        f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
-    }
-    return f;
-}
-
-__device__ __forceinline__ floatx16 mfma(u32x4 a, u32x4 b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-// ReLU where the layer has one; the largest magnitude's bits join `top`.
-template <int N>
-__device__ __forceinline__ void activate(floatx16 *acc, bool relu, uint32_t &top) {
-    if (relu) {
-#pragma unroll
-        for (int mb = 0; mb < N; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                acc[mb][r] = relu_mfma(acc[mb][r]);
-                acc[mb][r + 1] = relu_mfma(acc[mb][r + 1]);
-                top = max(max(top, __float_as_uint(acc[mb][r])), __float_as_uint(acc[mb][r + 1]));
-            }
-    } else {
-#pragma unroll
-        for (int mb = 0; mb < N; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                top = max(top, __float_as_uint(acc[mb][r]) & 0x7FFFFFFFu);
-    }
-}
-
 // Every layer but the output on the fp32 matrix instruction, with the
 // caller's weights in global memory ([out][in], unpadded: rows and columns
 // past them are zero) and the biases in LDS; input(s) = feature 2s + g of the
@@ -257,7 +89,6 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
         const float w = ldg(pk.W[l] + (in ? row * n_in + k : 0));
         return in ? w : 0.f;
     };
-    uint32_t unused = 0;
     load_bias<NMB>(reinterpret_cast<const float *>(lds + lay.l1_bias()), g, acc);
 #pragma unroll 1
     for (int s = 0; s < pk.ks1; ++s) {
@@ -266,7 +97,7 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
         for (int mb = 0; mb < NMB; ++mb)
             acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, mb, 2 * s + g), x, acc[mb], 0, 0, 0);
     }
-    activate<NMB>(acc, pk.relu & 1, unused);
+    activate_plain<NMB>(acc, pk.relu & 1);
     for (int h = 0; h < pk.n_hidden; ++h) {
         floatx16 hin[NMB];
 #pragma unroll
@@ -287,7 +118,7 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
             for (int i = 0; i + 1 < NMB; ++i)
                 hin[i] = hin[i + 1];
         }
-        activate<NMB>(acc, pk.relu >> (h + 1) & 1, unused);
+        activate_plain<NMB>(acc, pk.relu >> (h + 1) & 1);
     }
 }
 
@@ -313,79 +144,19 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
     const int lane = threadIdx.x & 63;
     const int g = lane >> 5;
     const int col = lane & 31;
-    const int waves_per_block = blockDim.x >> 6;
-    // XCD-aware order (blocks of one XCD, hardware id % 8, share an L2).
-    // Pointwise maps: each round of the grid takes adjacent tiles per XCD.
-    // Windowed maps (xcd_ranges, grid a multiple of 8): each XCD walks one
-    // contiguous eighth of the tiles, so the rows a window shares with the
-    // tiles before it are still in that XCD's L2.
-    const int nb = gridDim.x;
-    int wave_id, n_waves, t_end;
-    if (xcd_ranges) {
-        const int per = (n_tiles + 7) / 8;
-        const int x = blockIdx.x % 8;
-        wave_id = x * per + (blockIdx.x / 8) * waves_per_block + (threadIdx.x >> 6);
-        n_waves = (nb / 8) * waves_per_block;
-        t_end = (x + 1) * per < n_tiles ? (x + 1) * per : n_tiles;
-    } else {
-        const int lb = (nb % 8 == 0) ? (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8 : blockIdx.x;
-        wave_id = lb * waves_per_block + (threadIdx.x >> 6);
-        n_waves = nb * waves_per_block;
-        t_end = n_tiles;
-    }
+    const TileOrder order(n_tiles, xcd_ranges);
     const int F = in.n_features, n_points = in.n_points, rank_in = in.rank, rank_out = out.rank;
 
-    {
-        const int t = threadIdx.x;
-        constexpr int kWords = (int)(sizeof(Map32) / 4);
-        static_assert(kWords <= 64, "one word per thread");
-        if (t < kTableMaxF) {
-            tab0.fptr[t] = tin.fptr[t];
-            tab0.raw8[t] = tin.raw8[t];
-        } else if (t < 64 + kFoutMax) {
-            tab0.optr[t - 64] = const_cast<float *>(tout.fptr[t - 64]);
-            tab0.oraw8[t - 64] = tout.raw8[t - 64];
-        } else if (t >= 128 && t < 128 + kWords) {
-            ((int32_t *)&tab0.in)[t - 128] = ((const int32_t *)&in)[t - 128];
-        } else if (t >= 192 && t < 192 + kWords) {
-            ((int32_t *)&tab0.out)[t - 192] = ((const int32_t *)&out)[t - 192];
-        }
-    }
+    stage_maps(tab0, in, out, tin, tout);
     __syncthreads();
 
-    // ---- gather: lane (col, g) loads features 2t + g of its point through the
-    //      table's entry of that feature (entries past the last feature repeat
-    //      it).  Eight slots at a time: table entries, boundary fix-ups along
-    //      the dimensions where the wave touches an edge, then all the loads;
-    //      the last four slots are left out where no feature reaches them.
     auto gather = [&](int tile, float (&x)[XS]) __attribute__((always_inline)) {
-        const int b = tile * 32 + col;
-        const MapsLds &tab = maps();
-        const Pt32 pt = locate_lds(tab.in, rank_in, b < n_points ? b : n_points - 1);
-        const uint32_t edge = windowed ? edge_lds(tab.in, rank_in, pt) : 0u;
-        static_for<0, 2 * KS1>([&](auto q) __attribute__((always_inline)) {
-            constexpr int s0 = 4 * q;
-            if (q < 2 * KS1 - 1 || s0 < pk.ks1) {
-                int32_t idx[4] = {pt.pe, pt.pe, pt.pe, pt.pe};
-                if (edge) {
-                    const uint32_t raw[4] = {tab.raw8[2 * s0 + g], tab.raw8[2 * s0 + 2 + g], tab.raw8[2 * s0 + 4 + g],
-                                             tab.raw8[2 * s0 + 6 + g]};
-                    fix_lds<4>(tab.in, pt, edge, raw, idx);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[s0 + j] = ldg(tab.fptr[2 * (s0 + j) + g] + idx[j]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[s0 + j] = 0.f;
-            }
-        });
+        gather_inputs<KS1>(maps(), rank_in, n_points, windowed, pk.ks1, tile * 32 + col, g, x);
     };
     float xn[XS];
     // the first tile's loads go out before the weights are staged
-    if (wave_id < t_end)
-        gather(wave_id, xn);
+    if (order.first < order.end)
+        gather(order.first, xn);
 
     // stage the split weights once per block
     {
@@ -396,12 +167,12 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
     }
     __syncthreads();
 
-    for (int tile = wave_id; tile < t_end; tile += n_waves) {
+    for (int tile = order.first; tile < order.end; tile += order.step) {
         const int b = tile * 32 + col;
         const bool valid = b < n_points;
         int ln = lane;
         asm volatile("" : "+v"(ln));   // nothing read from LDS is held from one tile to the next
-        uint32_t top = pk.plain ? kBig : 0;   // the largest magnitude met
+        float top = pk.plain ? kBig : 0.f;   // the largest magnitude met
         Split b1[KS1];
         floatx16 acc[NMB];
         const u32x4 *fl = lds4 + ln;                                        // this lane's part of the LDS fragments
@@ -474,7 +245,7 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
 #pragma unroll
                         for (int r = 0; r < 16; ++r)
                             main[i][r] += sub[i][r];
-                    activate<2>(main, relu, top);
+                    activate<2>(main, act_floor(relu), top);
                     acc[2 * p] = main[0];
                     acc[2 * p + 1] = main[1];
                     __builtin_amdgcn_sched_barrier(0);
@@ -489,13 +260,11 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
                 for (int j = 0; j < 8; ++j) {
                     // zero where there is no feature (only in the last K-step)
                     v[j] = s < KS1 - 1 || 2 * (8 * s + j) + g < F ? xn[8 * s + j] : 0.f;
-                    top = max(top, __float_as_uint(v[j]) & 0x7FFFFFFFu);
-                }
+                    }
+                top = max_abs(v[0], v[1], max_abs(v[2], v[3], max_abs(v[4], v[5], max_abs(v[6], v[7], top))));
                 b1[s] = split8(v);
             });
-            const auto sw = __builtin_amdgcn_permlane32_swap(top, top, false, false);
-            const uint32_t largest = max(sw[0], sw[1]);   // of the point's inputs
-            if (largest - 1u < kTiny - 1u)
+            if (tiny_inputs(top))
                 top = kBig;
         });
 
@@ -532,8 +301,8 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         // the next tile's inputs are requested here, where the activations'
         // splits are free; they arrive during the output layer and the other
         // wave's work
-        if (tile + n_waves < t_end) {
-            gather(tile + n_waves, xn);
+        if (tile + order.step < order.end) {
+            gather(tile + order.step, xn);
         } else {
 #pragma unroll
             for (int s = 0; s < XS; ++s)
@@ -548,9 +317,7 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         //      features; swapping halves leaves output 2i in lanes 0..31 and
         //      2i + 1 in lanes 32..63.
         const MapsLds &tab = maps();
-        const Pt32 po = locate_lds(tab.out, rank_out, valid ? b : n_points - 1);
-        const uint32_t oedge = out_offsets ? edge_lds(tab.out, rank_out, po) : 0u;
-        const bool orelu = pk.relu >> (pk.n_hidden + 1) & 1;
+        const OutPoint po(tab, rank_out, out_offsets, valid ? b : n_points - 1);
         for (int go = 0; go < pk.f_out; go += 4) {
             const float4 *wq = reinterpret_cast<const float4 *>(lds + lay.out_w(go / 4)) + ln;
             float a[2 * NMB];
@@ -573,25 +340,8 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
 #pragma unroll
             for (int mb = 1; mb < NMB; ++mb)
                 sum += y[mb];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int o = go + 2 * i + g;
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[2 * i]), __float_as_uint(sum[2 * i + 1]),
-                                                                 false, false);
-                float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-                if (o < pk.f_out) {
-                    v += reinterpret_cast<const float *>(lds + lay.out_b())[o];
-                    if (orelu)
-                        v = fmaxf(v, 0.f);
-                    int32_t idx[1] = {po.pe};
-                    if (oedge) {
-                        const uint32_t raw[1] = {tab.oraw8[o]};
-                        fix_lds<1>(tab.out, po, oedge, raw, idx);
-                    }
-                    if (valid)
-                        stg(tab.optr[o] + idx[0], v);
-                }
-            }
+            po.store(tab, sum, go, pk.f_out, g, reinterpret_cast<const float *>(lds + lay.out_b()),
+                     pk.relu >> (pk.n_hidden + 1) & 1, valid);
         }
     }
 }
@@ -638,13 +388,6 @@ hipError_t launch_k(const Map32 &in, const Map32 &out, const FeatTable32 &tin, c
                                                   : launch_t<NMB, KS1, true>(in, out, tin, tout, pk, stream);
 }
 
-// rounded to nearest even, as the device's conversion (finite values)
-inline uint16_t rne(float x) {
-    uint32_t u = __builtin_bit_cast(uint32_t, x);
-    return (uint16_t)((u + 0x7FFFu + (u >> 16 & 1u)) >> 16);
-}
-inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
-
 }  // namespace
 
 bool f32_fast_supported(int n_layers, const int32_t *dims, int compute) {
@@ -678,46 +421,19 @@ bool f32_pack(int n_layers, const int32_t *dims, const float *const *W, const fl
                 for (int r = 0; r < 16; ++r)
                     dst[(g * NMB + mb) * 16 + r] = bias[crow(mb, r, g)];
     };
-    bool fine = true;
-    auto in_range = [&](int l) {   // the layer's weights: zero, or the largest splits exactly
-        float top = 0.f;
-        for (int64_t i = 0; i < (int64_t)dims[l] * dims[l + 1]; ++i)
-            top = std::max(top, std::fabs(W[l][i]));
-        return top == 0.f || top >= 0x1p-100f;
-    };
-    // one layer's fragments: K-step s, m-block mb, lane l, element j is
-    // weight [32 mb + l % 32][feature(s, l / 32, j)]
-    auto put_layer = [&](const float *Wl, int K, int steps, int hm, int lo, auto &&feature) {
-        uint16_t *d = reinterpret_cast<uint16_t *>(img);
-        for (int s = 0; s < steps; ++s)
-            for (int mb = 0; mb < NMB; ++mb) {
-                uint16_t *qh = d + (hm + (s * NMB + mb) * 2 * kFragBytes) / 2, *qm = qh + kFragBytes / 2;
-                uint16_t *ql = d + (lo + (s * NMB + mb) * kFragBytes) / 2;
-                for (int l = 0; l < 64; ++l)
-                    for (int j = 0; j < 8; ++j) {
-                        const int k = feature(s, l / 32, j);
-                        const float w = k < K ? Wl[(size_t)(32 * mb + l % 32) * K + k] : 0.f;
-                        if (!(std::fabs(w) < 0x1p127f)) {
-                            fine = false;
-                            continue;
-                        }
-                        const uint16_t h = rne(w);
-                        const float r = w - bf16_float(h);
-                        const uint16_t m = rne(r);
-                        qh[l * 8 + j] = h;
-                        qm[l * 8 + j] = m;
-                        ql[l * 8 + j] = rne(r - bf16_float(m));
-                    }
-            }
-    };
-    for (int l = 0; l + 1 < n_layers; ++l)
-        fine = fine && in_range(l);
-    put_layer(W[0], Fin, sl.ks, sl.l1(), sl.l1_lo(), [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
+    bool fine = put_layer(
+        reinterpret_cast<char *>(img), W[0], H, Fin, sl.ks, NMB,
+        [&](int s, int mb) { return sl.l1() + (s * NMB + mb) * 2 * kFragBytes; },
+        [&](int s, int mb) { return sl.l1_lo() + (s * NMB + mb) * kFragBytes; },
+        [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
     put_bias(img + sl.l1_bias() / 4, b[0]);
     for (int h = 0; h < NH; ++h) {
         // element j of K-step s is register 8 (s % 2) + j of m-block s / 2
-        put_layer(W[h + 1], H, 2 * NMB, sl.hidden(h), sl.hidden_lo(h),
-                  [](int s, int g, int j) { return crow(s / 2, 8 * (s % 2) + j, g); });
+        fine &= put_layer(
+            reinterpret_cast<char *>(img), W[h + 1], H, H, 2 * NMB, NMB,
+            [&](int s, int mb) { return sl.hidden(h) + (s * NMB + mb) * 2 * kFragBytes; },
+            [&](int s, int mb) { return sl.hidden_lo(h) + (s * NMB + mb) * kFragBytes; },
+            [](int s, int g, int j) { return crow(s / 2, 8 * (s % 2) + j, g); });
         put_bias(img + sl.hidden_bias(h) / 4, b[h + 1]);
     }
     const float *Wo = W[n_layers - 1];

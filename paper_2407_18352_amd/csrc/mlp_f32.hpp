@@ -1,0 +1,358 @@
+// Device parts shared by the fp32 fused kernels (three-way bf16 splits of fp32
+// numbers, the maps in LDS, the order of tiles, the gather and the scatter).
+#pragma once
+
+#include <algorithm>
+#include <cfloat>
+#include <cmath>
+#include <type_traits>
+
+#include "kernels.hpp"
+
+namespace hpacml {
+
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFoutMax = 8;
+// scheduling-barrier mask: only VALU, SALU and transcendental instructions
+// may be moved across
+constexpr int kSchedAluOnly = 0x2 | 0x4 | 0x400;
+constexpr int kFragBytes = 1024;        // one A operand: 64 lanes x 8 bf16
+constexpr int kLdsMax = 160 * 1024;     // LDS of a CU
+constexpr float kBig = 0x1p127f;        // this and more has no three-way split
+constexpr float kTiny = 0x1p-100f;      // below it the lo part loses bits
+
+// What a block keeps of the two maps in LDS, ahead of the split image: the
+// feature tables, read with a lane's own feature number, and the 32-bit
+// views, whose fields would otherwise occupy (and spill) scalar registers
+// over the whole kernel.
+struct MapsLds {
+    Map32 in, out;
+    const float *fptr[kTableMaxF];
+    float *optr[kFoutMax];
+    uint32_t raw8[kTableMaxF], oraw8[kFoutMax];
+};
+static_assert(sizeof(MapsLds) % 16 == 0 && sizeof(Map32) % 16 == 0, "read 16 bytes at a time");
+
+// locate32 on a view in LDS: unused dimensions (count 1, stride 0) add
+// nothing, those past the second are skipped for the usual ranks.
+__device__ __forceinline__ Pt32 locate_lds(const Map32 &m, int rank, int32_t b) {
+    Pt32 r;
+    uint32_t rem = (uint32_t)b;
+    r.pe = 0;
+    auto dim = [&](int d) __attribute__((always_inline)) {
+        uint32_t k = rem;
+        if (d > 0) {
+            rem = (uint32_t)(((uint64_t)rem * m.magic[d]) >> m.shift[d]);
+            k -= rem * (uint32_t)m.count[d];
+        }
+        r.p[d] = m.start[d] + (int32_t)k * m.step[d];
+        r.pe += r.p[d] * m.stride[d];
+    };
+    r.p[1] = r.p[2] = r.p[3] = 0;
+    if (rank > 1) {
+        if (rank > 2) {
+            dim(3);
+            dim(2);
+        }
+        dim(1);
+    }
+    dim(0);
+    return r;
+}
+
+// The dimensions along which some lane of the wave reads outside the arrays.
+__device__ __forceinline__ uint32_t edge_lds(const Map32 &m, int rank, const Pt32 &r) {
+    uint32_t edge = 0;
+#pragma unroll
+    for (int d = 0; d < HPACML_MAX_RANK; ++d)
+        if (d < rank && __any(r.p[d] + m.omin[d] < 0 || r.p[d] + m.omax[d] >= m.extent[d]))
+            edge |= 1u << d;
+    return edge;
+}
+
+// Boundary corrections of N accesses with raw offsets raw[] at point r, added
+// to idx[]; `edge`: the dimensions along which some lane of the wave leaves
+// the arrays.  Per dimension dl = clamp(at, 0, n - 1) - at (zero inside):
+// clamp adds dl strides, periodic one wrap in dl's direction (|offset| <=
+// extent).
+template <int N>
+__device__ __forceinline__ void fix_lds(const Map32 &m, const Pt32 &r, uint32_t edge, const uint32_t (&raw)[N],
+                                        int32_t (&idx)[N]) {
+#pragma unroll
+    for (int d = 0; d < HPACML_MAX_RANK; ++d) {
+        if (edge & (1u << d)) {
+            const int32_t n = m.extent[d], st = m.stride[d];
+            const bool per = m.bnd[d] == HPACML_BND_PERIODIC;
+            const int32_t lim = per ? 1 : INT32_MAX, mul = per ? (int32_t)((uint32_t)n * (uint32_t)st) : st;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const int32_t at = r.p[d] + (int32_t)(int8_t)(raw[j] >> (8 * d));
+                const int32_t dl = min(max(at, 0), n - 1) - at;
+                idx[j] += min(max(dl, -lim), lim) * mul;
+            }
+        }
+    }
+}
+
+// feature held by lane half g in register r of m-block mb
+__host__ __device__ inline int crow(int mb, int r, int g) { return 32 * mb + 8 * (r / 4) + 4 * g + (r % 4); }
+
+// N m-blocks from m-block mb0 on
+template <int NMB, int N = NMB>
+__device__ __forceinline__ void load_bias(const float *bias, int g, floatx16 *acc, int mb0 = 0) {
+#pragma unroll
+    for (int mb = 0; mb < N; ++mb) {
+        const float4 *p = reinterpret_cast<const float4 *>(bias + (g * NMB + mb0 + mb) * 16);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float4 v = p[q];
+            acc[mb][4 * q + 0] = v.x;
+            acc[mb][4 * q + 1] = v.y;
+            acc[mb][4 * q + 2] = v.z;
+            acc[mb][4 * q + 3] = v.w;
+        }
+    }
+}
+
+// compile-time loop: fn(std::integral_constant<int, i>) for i in [B, E)
+template <int B, int E, typename Fn>
+__device__ __forceinline__ void static_for(Fn &&fn) {
+    if constexpr (B < E) {
+        fn(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(fn);
+    }
+}
+
+// Eight floats as three B fragments, v = hi + mid + lo exactly (see above).
+struct Split {
+    u32x4 hi, mid, lo;
+};
+__device__ __forceinline__ Split split8(floatx8 v) {
+    Split f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
+        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+        f.hi[i] = h;
+        f.mid[i] = m;
+        f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
+    }
+    return f;
+}
+
+__device__ __forceinline__ floatx16 mfma(u32x4 a, u32x4 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The larger of m and two magnitudes (a NaN is passed over); for values that
+// the vector ALU made (not MFMA results: the compiler does not see the read).
+__device__ __forceinline__ float max_abs(float a, float b, float m) {
+    float r;
+    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(m));
+    return r;
+}
+
+// Lower bound of a layer's activation: 0 (ReLU) or none.
+__device__ __forceinline__ float act_floor(bool relu) { return relu ? 0.f : -FLT_MAX; }
+
+// Activation as one v_med3_f32(x, floor, FLT_MAX), without a branch, so that it
+// can be scheduled beside matrix instructions; the largest magnitude joins
+// `top`.  A NaN becomes the floor (v_med3_f32 returns the least of the other
+// two): 0 under ReLU, and the -FLT_MAX of an identity layer, like any
+// magnitude of 2^127 and more, sends the tile to the fp32 instruction.
+template <int N>
+__device__ __forceinline__ void activate(floatx16 *acc, float floor, float &top) {
+#pragma unroll
+    for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            acc[mb][r] = __builtin_amdgcn_fmed3f(acc[mb][r], floor, FLT_MAX);
+            acc[mb][r + 1] = __builtin_amdgcn_fmed3f(acc[mb][r + 1], floor, FLT_MAX);
+            top = max_abs(acc[mb][r], acc[mb][r + 1], top);
+        }
+}
+
+// Activation of the fp32 path: ReLU (a NaN gives 0) or nothing.
+template <int N>
+__device__ __forceinline__ void activate_plain(floatx16 *acc, bool relu) {
+    if (relu) {
+#pragma unroll
+        for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[mb][r] = relu_mfma(acc[mb][r]);
+    }
+}
+
+// Which tiles of 32 points a wave takes: first, first + step, ... below end.
+// XCD-aware (blocks of one XCD, hardware id % 8, share an L2).  Pointwise
+// maps: each round of the grid takes adjacent tiles per XCD.  Windowed maps
+// (xcd_ranges, grid a multiple of 8): each XCD walks one contiguous eighth of
+// the tiles, so the rows a window shares with the tiles before it are still in
+// that XCD's L2.
+struct TileOrder {
+    int first, step, end;
+    __device__ TileOrder(int32_t n_tiles, int32_t xcd_ranges) {
+        const int nb = gridDim.x, waves = blockDim.x >> 6, w = threadIdx.x >> 6;
+        if (xcd_ranges) {
+            const int per = (n_tiles + 7) / 8;
+            const int x = blockIdx.x % 8;
+            first = x * per + (blockIdx.x / 8) * waves + w;
+            step = (nb / 8) * waves;
+            end = (x + 1) * per < n_tiles ? (x + 1) * per : n_tiles;
+        } else {
+            const int lb = (nb % 8 == 0) ? (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8 : blockIdx.x;
+            first = lb * waves + w;
+            step = nb * waves;
+            end = n_tiles;
+        }
+    }
+};
+
+// The block's copy of the maps (blocks of at least 256 threads; a barrier follows).
+__device__ __forceinline__ void stage_maps(MapsLds &tab, const Map32 &in, const Map32 &out, const FeatTable32 &tin,
+                                           const FeatTable32 &tout) {
+    const int t = threadIdx.x;
+    constexpr int kWords = (int)(sizeof(Map32) / 4);
+    static_assert(kWords <= 64, "one word per thread");
+    if (t < kTableMaxF) {
+        tab.fptr[t] = tin.fptr[t];
+        tab.raw8[t] = tin.raw8[t];
+    } else if (t < 64 + kFoutMax) {
+        tab.optr[t - 64] = const_cast<float *>(tout.fptr[t - 64]);
+        tab.oraw8[t - 64] = tout.raw8[t - 64];
+    } else if (t >= 128 && t < 128 + kWords) {
+        ((int32_t *)&tab.in)[t - 128] = ((const int32_t *)&in)[t - 128];
+    } else if (t >= 192 && t < 192 + kWords) {
+        ((int32_t *)&tab.out)[t - 192] = ((const int32_t *)&out)[t - 192];
+    }
+}
+
+// Inputs of point b: lane half g loads features 2t + g into the slots t,
+// through the table's entry of that feature (entries past the last feature
+// repeat it).  Four slots at a time: table entries, boundary fix-ups along the
+// dimensions where the wave touches an edge, then the loads; the last four
+// slots are left out where no feature reaches them (pairs: ceil(F / 2)).
+template <int KS1>
+__device__ __forceinline__ void gather_inputs(const MapsLds &tab, int rank, int32_t n_points, bool windowed, int pairs,
+                                              int32_t b, int g, float (&x)[8 * KS1]) {
+    const Pt32 pt = locate_lds(tab.in, rank, b < n_points ? b : n_points - 1);
+    const uint32_t edge = windowed ? edge_lds(tab.in, rank, pt) : 0u;
+    static_for<0, 2 * KS1>([&](auto q) __attribute__((always_inline)) {
+        constexpr int s0 = 4 * q;
+        if (q < 2 * KS1 - 1 || s0 < pairs) {
+            int32_t idx[4] = {pt.pe, pt.pe, pt.pe, pt.pe};
+            if (edge) {
+                const uint32_t raw[4] = {tab.raw8[2 * s0 + g], tab.raw8[2 * s0 + 2 + g], tab.raw8[2 * s0 + 4 + g],
+                                         tab.raw8[2 * s0 + 6 + g]};
+                fix_lds<4>(tab.in, pt, edge, raw, idx);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[s0 + j] = ldg(tab.fptr[2 * (s0 + j) + g] + idx[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[s0 + j] = 0.f;
+        }
+    });
+}
+
+// Whether some point of the wave has only inputs that are tiny, and not all zero (top:
+// the largest magnitude of the lane's inputs; the other half has the rest).
+__device__ __forceinline__ bool tiny_inputs(float top) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(top), __float_as_uint(top), false, false);
+    const float m = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    return m > 0.f && m < kTiny;
+}
+
+// A point of the `from` map, and the store of four outputs: each lane half
+// holds its own features' sums of outputs go .. go + 3; swapping halves leaves
+// output go + 2i in lanes 0..31 and go + 2i + 1 in lanes 32..63.
+struct OutPoint {
+    Pt32 p;
+    uint32_t edge;
+    __device__ __forceinline__ OutPoint(const MapsLds &tab, int rank, bool offsets, int32_t b) {
+        p = locate_lds(tab.out, rank, b);
+        edge = offsets ? edge_lds(tab.out, rank, p) : 0u;
+    }
+    __device__ __forceinline__ void store(const MapsLds &tab, floatx4 sum, int go, int f_out, int g, const float *bias,
+                                          bool relu, bool valid) const {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int o = go + 2 * i + g;
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[2 * i]), __float_as_uint(sum[2 * i + 1]),
+                                                             false, false);
+            float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            if (o < f_out) {
+                v += bias[o];
+                if (relu)
+                    v = fmaxf(v, 0.f);
+                int32_t idx[1] = {p.pe};
+                if (edge) {
+                    const uint32_t raw[1] = {tab.oraw8[o]};
+                    fix_lds<1>(tab.out, p, edge, raw, idx);
+                }
+                if (valid)
+                    stg(tab.optr[o] + idx[0], v);
+            }
+        }
+    }
+};
+
+// Host side of the split: rounded to nearest even, as the device's conversion
+// (finite values).
+inline uint16_t rne(float x) {
+    uint32_t u = __builtin_bit_cast(uint32_t, x);
+    return (uint16_t)((u + 0x7FFFu + (u >> 16 & 1u)) >> 16);
+}
+inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
+
+// One layer's A fragments: K-step s, m-block mb, lane l, element j is weight
+// [32 mb + l % 32][feature(s, l / 32, j)] (zero past N rows and K columns), its
+// parts at img + hm(s, mb) (hi, then mid) and img + lo(s, mb).  False when a
+// weight has no split, or the largest is so small that splits lose bits.
+template <typename Hm, typename Lo, typename Feature>
+inline bool put_layer(char *img, const float *W, int N, int K, int steps, int blocks, Hm &&hm, Lo &&lo,
+                      Feature &&feature) {
+    bool fine = true;
+    float top = 0.f;
+    for (int s = 0; s < steps; ++s)
+        for (int mb = 0; mb < blocks; ++mb) {
+            uint16_t *qh = reinterpret_cast<uint16_t *>(img + hm(s, mb)), *qm = qh + kFragBytes / 2;
+            uint16_t *ql = reinterpret_cast<uint16_t *>(img + lo(s, mb));
+            for (int l = 0; l < 64; ++l)
+                for (int j = 0; j < 8; ++j) {
+                    const int k = feature(s, l / 32, j), row = 32 * mb + l % 32;
+                    const float w = k < K && row < N ? W[(size_t)row * K + k] : 0.f;
+                    if (!(std::fabs(w) < 0x1p127f)) {
+                        fine = false;
+                        continue;
+                    }
+                    top = std::max(top, std::fabs(w));
+                    const uint16_t h = rne(w);
+                    const float r = w - bf16_float(h);
+                    const uint16_t m = rne(r);
+                    qh[l * 8 + j] = h;
+                    qm[l * 8 + j] = m;
+                    ql[l * 8 + j] = rne(r - bf16_float(m));
+                }
+        }
+    return fine && (top == 0.f || top >= 0x1p-100f);
+}
+
+}  // namespace
+
+}  // namespace hpacml

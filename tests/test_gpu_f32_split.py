@@ -1,4 +1,4 @@
-"""The fp32 fused kernel multiplies on the bf16 matrix cores, each float split
+"""The fp32 fused kernels multiply on the bf16 matrix cores, each float split
 in three: its shapes (K-steps of the first layer, layers whose smallest parts
 stay in global memory, groups of four outputs), values that have no split, and
 its error against 64 bits."""
@@ -24,9 +24,9 @@ def _workload(dims, n, inputs, seed=3):
     return w
 
 
-def _run(w):
+def _run(w, path="mlp_f32_h"):
     got, var = run_infer(w)
-    assert var.startswith("mlp_f32_h"), var
+    assert var.startswith(path), var
     return np.stack(got, 1), oracle.infer_rows(w.in_spec, w.inputs, w.model)
 
 
@@ -51,7 +51,42 @@ def test_shapes_against_64_bits(dims, n):
         assert norm <= _bound(dims), (dims, norm, _bound(dims))
 
 
-@pytest.mark.parametrize("dims", [[5, 64, 64, 1], [9, 128, 128, 128, 1], [20, 128, 128, 5]])
+@pytest.mark.parametrize("dims", [
+    [5, 129, 1], [16, 1000, 5], [48, 300, 8],                 # one hidden layer: one and three K-steps, two output groups
+    [9, 200, 50, 1], [16, 257, 32, 4], [17, 160, 64, 5],      # two: one and two blocks of the second a pass
+    [9, 5, 300, 2], [1, 33, 225, 1],                          # several passes, the last with an empty block
+    [9, 400, 64, 1], [20, 129, 65, 3]])                       # lo parts in global memory
+@pytest.mark.parametrize("n", [1, 33, 3001, 70001])
+def test_any_widths_against_64_bits(dims, n):
+    g = np.random.default_rng(sum(dims) + n)
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    got, want = _run(w, "mlp_layers_f32")
+    worst, norm, nan = parity_stats(got, want)
+    assert nan == 0 and worst <= 4 * 4 * _bound(dims), (dims, worst, _bound(dims))
+    if n > 1000:
+        assert norm <= _bound(dims), (dims, norm, _bound(dims))
+
+
+@pytest.mark.parametrize("acts", [[0, 0, 0], [0, 1, 1], [1, 0, 0]])
+def test_any_widths_activations_and_window(acts):
+    """Identity hidden layers, a ReLU output layer, a clamped 3 x 3 window on a
+    grid narrower than a tile, outputs shifted along a periodic dimension."""
+    g = np.random.default_rng(5)
+    ny, nx = 37, 19
+    fields = [g.standard_normal((ny, nx)).astype(np.float32) for _ in range(3)]
+    spec = {"rank": 2, "slices": [((-1, -1), (3, 3))], "sweep": ((0, 0), (ny, nx), (1, 1)), "bnd": [wl.CLAMP, wl.PERIODIC]}
+    ospec = {"rank": 2, "slices": [((0, 2), (1, 1))], "sweep": ((0, 0), (ny, nx), (1, 1)), "bnd": [wl.NONE, wl.PERIODIC]}
+    w = wl.Workload("split", 0, "f32", [27, 170, 40, 2], spec, ospec, fields, [wl.sentinel_like((ny, nx)) for _ in range(2)])
+    w.model = wl.make_model(91, w.dims, "f32")
+    w.model["act"] = acts
+    got, var = run_infer(w)
+    exp = [o.copy() for o in w.outputs]
+    oracle.scatter(ospec, exp, oracle.infer_rows(spec, fields, w.model))
+    worst, _, nan = parity_stats(np.stack([a.reshape(-1) for a in got], 1), np.stack([a.reshape(-1) for a in exp], 1))
+    assert nan == 0 and worst <= 1e-5, (var, worst)
+
+
+@pytest.mark.parametrize("dims", [[5, 64, 64, 1], [9, 128, 128, 128, 1], [20, 128, 128, 5], [9, 200, 50, 1], [5, 300, 6]])
 def test_infinities_and_their_neighbours(dims):
     """Infinite and NaN inputs in some points: the same classes of results as
     64-bit arithmetic gives them, and every other point (some in the same wave)
@@ -61,7 +96,7 @@ def test_infinities_and_their_neighbours(dims):
     w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
     for k, v in ((3, np.inf), (40, -np.inf), (41, np.nan), (130, np.inf), (200, -np.inf)):
         w.inputs[k % dims[0]][k] = v
-    got, want = _run(w)
+    got, want = _run(w, "mlp_")
     assert np.array_equal(np.isnan(got), np.isnan(want))
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     fine = np.isfinite(want).all(1)
@@ -70,7 +105,7 @@ def test_infinities_and_their_neighbours(dims):
 
 
 @pytest.mark.parametrize("exponent", [127, 126, -90, -99, -101, -120])
-@pytest.mark.parametrize("dims", [[7, 64, 64, 2], [12, 128, 128, 1]])
+@pytest.mark.parametrize("dims", [[7, 64, 64, 2], [12, 128, 128, 1], [12, 200, 40, 1]])
 def test_ends_of_the_range(dims, exponent):
     """Inputs of 2^exponent with first-layer weights that bring them back, and
     no biases: the points keep 24 bits whether or not their inputs split."""
@@ -84,19 +119,20 @@ def test_ends_of_the_range(dims, exponent):
         w.model["W"][0] = (w.model["W"][0] * np.float32(2.0 ** (100 - exponent))).astype(np.float32)
     else:
         w.model["W"][-1] = (w.model["W"][-1] * np.float32(2.0 ** -exponent)).astype(np.float32)
-    got, want = _run(w)
+    got, want = _run(w, "mlp_")
     assert np.isfinite(want).all()
     worst, _, nan = parity_stats(got, want)
     assert nan == 0 and worst <= 1e-5, worst
 
 
 @pytest.mark.parametrize("value", [2.0 ** 127, 3e38])
-def test_weight_without_a_split(value):
+@pytest.mark.parametrize("dims", [[6, 128, 128, 1], [6, 200, 70, 1]])
+def test_weight_without_a_split(value, dims):
     """One first-layer weight of 2^127 and more, met by inputs of 2^-127."""
-    dims, n = [6, 128, 128, 1], 100
+    n = 100
     g = np.random.default_rng(11)
     w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(6)])
     w.inputs[2] = (w.inputs[2] * np.float32(2.0 ** -120) * np.float32(2.0 ** -6)).astype(np.float32)
     w.model["W"][0][17, 2] = value
-    got, want = _run(w)
+    got, want = _run(w, "mlp_")
     assert parity_stats(got, want)[0] <= 1e-5
