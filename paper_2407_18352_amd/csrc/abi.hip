@@ -64,6 +64,7 @@ struct hpacml_model_s {
     std::vector<CnnLayerDev> cnn_layers;
     bool cnn_fused = false;          // the fused kernel takes this stack
     float *fused_buf = nullptr;      // its packed weights
+    uint8_t *fused_image = nullptr;  // its matrix-core form's split weights
     CnnFused fused{};
     std::mutex ws_mu;                // layer-by-layer workspace, grown on demand
     float *ws = nullptr;
@@ -517,6 +518,7 @@ void hpacml_model_destroy(hpacml_model *m) {
     (void)hipFree(m->bf16r_buf);
     (void)hipFree(m->cnn_buf);
     (void)hipFree(m->fused_buf);
+    (void)hipFree(m->fused_image);
     (void)hipFree(m->ws);
     layers_destroy(m->layers);
     delete m;
@@ -781,6 +783,11 @@ hpacml_status hpacml_cnn_create(int32_t in_channels, int32_t height, int32_t wid
             s = upload(&m->fused_buf, packed.data(), packed.size());
             m->fused.wts = m->fused_buf;
             m->cnn_fused = true;
+            std::vector<uint8_t> image;
+            if (s == HPACML_OK && cnn_mfma_pack(p, W, b, m->fused, image)) {
+                s = upload(&m->fused_image, image.data(), image.size());
+                m->fused.image = m->fused_image;
+            }
         }
         if (s != HPACML_OK) {
             hpacml_model_destroy(m);

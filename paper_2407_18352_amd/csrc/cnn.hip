@@ -3,22 +3,21 @@
 // max-pool and fully connected layers for ParticleFilter).
 //
 // Fused path (convolution-only stacks, SAME padding, stride 1, <= 16
-// channels): plain fp32 FMA work with small channel counts, so VALU-bound,
-// not a contraction worth MFMA tiles (8 output channels would fill a quarter
-// of a 32-wide MFMA).  One block owns a tile of TY x 64 output pixels of one
-// image.  It gathers the tile plus the stack's total halo through the `to`
-// map into LDS ([row][column][channel], channels padded to 4), then runs every
-// layer over the shrinking region — each layer's output region is the next
-// layer's input region — and finally writes the last layer's tile through the
-// `from` map (a phase of its own, so the layer loops carry none of the output
-// map's state in registers).  One thread computes one pixel's output
-// channels per pass: 16-byte LDS reads of its window, weights as wave-uniform
-// scalar loads (one FMA per weight per lane), no bank conflicts for 4-channel
-// rows.  Outside the image, a layer's input follows its padding mode:
-// circular stacks wrap at the gather and then compute the halo as is (on a
-// torus the halo's values equal the wrapped ones); zeros writes 0; replicate
-// computes the pixel at the clamped position (inside the region, since the
-// region always contains the image edge it crosses).
+// channels): one block owns a tile of TY x 64 output pixels of one image.  It
+// gathers the tile plus the stack's total halo through the `to` map into LDS
+// ([row][column][channel], channels padded to 4), then runs every layer over
+// the shrinking region — each layer's output region is the next layer's
+// input region — and writes the last layer's tile through the `from` map.
+// Outside the image, a layer's input follows its padding mode: circular
+// stacks wrap at the gather and then compute the halo as is (on a torus the
+// halo's values equal the wrapped ones); zeros writes 0; replicate takes the
+// pixel at the clamped position (inside the region, since the region always
+// contains the image edge it crosses).  Two forms: on the matrix cores (exact
+// splits of the floats, several pixels a column; the usual one), and on the
+// vector ALU, with one thread per pixel, 16-byte LDS reads of its window and
+// weights as wave-uniform scalar loads (one FMA per weight per lane), for
+// stacks whose weights don't fit the LDS, large images with few
+// multiplications, and tiles with values that have no split.
 //
 // Layer-by-layer path (everything else, and in-place regions): kernels over
 // [S][h][w][c] tensors in a workspace -- convolutions (a max-pool with
@@ -27,18 +26,17 @@
 // fully connected layers closing a stack together with the scatter; else a
 // scatter of the last tensor.
 #include "cnn.hpp"
+#include "mlp_f32.hpp"
 
 namespace hpacml {
 
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int kThreads = 256;
 constexpr int kTX = 64;   // tile columns
 constexpr int kPix = 1;   // pixels per thread per pass
 
-// ------------------------------------------------------------------ fused
+// ------------------------------------------------------------------ fused, vector ALU
 struct FusedArgs {
     Map32 in, out;
     const FeatTable32 *tin, *tout;   // device; the used entries are staged in LDS
@@ -78,7 +76,7 @@ __device__ __forceinline__ void gather_region(const FusedArgs &a, const TabLds &
     const int rh = a.rh[0], rw = a.rw[0], n = rh * rw;
     const int mode = a.L[0].mode;
     const int vy0 = y0 - a.rt[0], vx0 = x0 - a.rl[0];
-    for (int i = threadIdx.x; i < n; i += kThreads) {
+    for (int i = threadIdx.x; i < n; i += (int)blockDim.x) {
         const int ry = div_region(i, a.rw_magic[0]), rx = i - ry * rw;
         int y = vy0 + ry, x = vx0 + rx;
         bool zero = false;
@@ -156,12 +154,13 @@ __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab,
     const float *bl = wts + Ly.boff;
     const int kh = Ly.kh, kw = Ly.kw;
     const int n = oh * ow;
-    for (int base = 0; base < n; base += kThreads * kPix) {
+    const int nt = (int)blockDim.x;
+    for (int base = 0; base < n; base += nt * kPix) {
         int off[kPix];          // LDS float offset of each pixel's window origin
         bool valid[kPix], zero[kPix];
 #pragma unroll
         for (int j = 0; j < kPix; ++j) {
-            const int i = base + j * kThreads + (int)threadIdx.x;
+            const int i = base + j * nt + (int)threadIdx.x;
             valid[j] = i < n;
             const int ic = valid[j] ? i : n - 1;
             int ry = div_region(ic, r.ow_magic), rx = ic - ry * ow;
@@ -225,7 +224,7 @@ __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab,
                 }
                 if (!valid[j])
                     continue;
-                const int i = base + j * kThreads + (int)threadIdx.x;
+                const int i = base + j * nt + (int)threadIdx.x;
                 reinterpret_cast<float4 *>(dst + (size_t)i * CO)[og] =
                     zero[j] ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
             }
@@ -239,7 +238,7 @@ __device__ __forceinline__ void scatter_tile(const FusedArgs &a, const TabLds &t
                                              int x0) {
     const int CO = a.co_last_pad;
     const int n = a.ty * kTX;
-    for (int i = threadIdx.x; i < n; i += kThreads) {
+    for (int i = threadIdx.x; i < n; i += (int)blockDim.x) {
         const int ry = i / kTX, rx = i % kTX;
         const int y = y0 + ry, x = x0 + rx;
         if (y >= a.H || x >= a.W)
@@ -266,11 +265,7 @@ __device__ __forceinline__ void conv_dispatch_out(const FusedArgs &a, const TabL
     }
 }
 
-__global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const float *__restrict__ wts) {
-    extern __shared__ float4 lds4[];
-    float *const buf0 = reinterpret_cast<float *>(lds4);
-    float *const buf1 = buf0 + a.buf1;
-    __shared__ TabLds tab;
+__device__ __forceinline__ void stage_tab(const FusedArgs &a, TabLds &tab) {
     if (threadIdx.x < kCnnFusedMaxC) {
         const int f = threadIdx.x;
         tab.in[f] = a.tin->fptr[f];
@@ -278,19 +273,12 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
         tab.out[f] = const_cast<float *>(a.tout->fptr[f]);
         tab.out_raw8[f] = a.tout->raw8[f];
     }
-    __syncthreads();
+}
 
-    // blocks of one XCD (blockIdx % 8) take a contiguous range of tiles, so
-    // neighbouring tiles share their halo rows in that XCD's L2
-    const int32_t k0 = blockIdx.x;
-    const int32_t xq = a.n_tiles / 8, xr = a.n_tiles % 8, xx = k0 % 8;
-    const int32_t tile = xx * xq + (xx < xr ? xx : xr) + k0 / 8;
-    const int32_t per_img = a.tiles_y * a.tiles_x;
-    const int s = tile / per_img;
-    const int rem = tile - s * per_img;
-    const int ty_i = rem / a.tiles_x;
-    const int y0 = ty_i * a.ty, x0 = (rem - ty_i * a.tiles_x) * kTX;
-
+// One tile by the vector ALU: gather, every layer, scatter.
+__device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, const float *__restrict__ wts,
+                                         float *buf0, int s, int y0, int x0) {
+    float *const buf1 = buf0 + a.buf1;
     switch (a.L[0].cin4) {
     case 1: gather_region<4>(a, tab, s, y0, x0, buf0); break;
     case 2: gather_region<8>(a, tab, s, y0, x0, buf0); break;
@@ -317,6 +305,589 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
         __syncthreads();
     }
     scatter_tile(a, tab, (a.n_layers & 1) ? buf1 : buf0, s, y0, x0);
+}
+
+__global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const float *__restrict__ wts) {
+    extern __shared__ float4 lds4[];
+    float *const buf0 = reinterpret_cast<float *>(lds4);
+    __shared__ TabLds tab;
+    stage_tab(a, tab);
+    __syncthreads();
+
+    // blocks of one XCD (blockIdx % 8) take a contiguous range of tiles, so
+    // neighbouring tiles share their halo rows in that XCD's L2
+    const int32_t k0 = blockIdx.x;
+    const int32_t xq = a.n_tiles / 8, xr = a.n_tiles % 8, xx = k0 % 8;
+    const int32_t tile = xx * xq + (xx < xr ? xx : xr) + k0 / 8;
+    const int32_t per_img = a.tiles_y * a.tiles_x;
+    const int s = tile / per_img;
+    const int rem = tile - s * per_img;
+    const int ty_i = rem / a.tiles_x;
+    const int y0 = ty_i * a.ty, x0 = (rem - ty_i * a.tiles_x) * kTX;
+
+    run_tile(a, tab, wts, buf0, s, y0, x0);
+}
+
+// ------------------------------------------------------------------ fused, matrix cores
+// The same tiles with the convolutions on the bf16 matrix cores, every float
+// as the exact sum of three bf16 parts (see mlp_f32.hip: six products, hi hi
+// accumulated apart; values without a split send their tile to the vector
+// ALU path above).
+//
+// A few channels would fill a quarter of a matrix instruction's rows, so P
+// neighbouring output pixels of a row share one column of it: rows = (pixel of
+// the group, output channel), columns = 32 (16) groups, K = (window row, the
+// kw + P - 1 input pixels the group's windows span, channel).  A weight that a
+// pixel's window doesn't reach is zero (a Toeplitz band: kw of kw + P - 1).
+// With channels last the K of one window row is contiguous in LDS, so a lane's
+// 8 values of K are one 16-byte read per part.  Four output channels take
+// 16 x 16 x 32 instructions with P = 4, more of them 32 x 32 x 16 with P = 32 /
+// channels.
+//
+// One block of 8 waves per CU loops over tiles: weights of all layers stay in
+// LDS (staged once), the layers' inputs as three bf16 planes [row][column]
+// [channel]; the next tile's pixels are requested while the current tile's
+// layers run (one-group inputs).  The last layer goes straight from the
+// accumulators through the `from` map.
+//
+// Measured, matrix cores / vector ALU: 4 -> 8 -> 4 channels, 5 x 5 and 3 x 3 on 2048 x
+// 2048: 174-181 / 299 us, on 512 x 512 16.4 / 33.3, on 64 x 64 11.4 / 33.2; 6 x 6 and 5 x 5
+// on 1426 x 1867: 178 / 465 us.  Error against 64 bits 1.2e-7 / 3.2e-7.  What bounds
+// it: of 26 thousand cycles a tile of 16 rows the first layer's column tiles take 8
+// (matrix instructions 3.8 of them, LDS reads as much), the second's 6, and the
+// gather's address arithmetic, splits and barriers most of the rest.
+constexpr int kMThreads = 512, kMWaves = 8;
+constexpr size_t kMStatic = 2048;        // LDS beside the image and the planes (tables, arguments, flags)
+constexpr int kPre = 4;                  // pixels per thread requested ahead
+struct ConvM {
+    int32_t cout, m16, P, ci, co;        // output channels; 16-row form; pixels per group; padded channels in, out
+    int32_t steps, rch, chunks;          // K-steps; 8-value chunks per window row, and in all
+    // A row of a plane in 16-byte chunks: a group starts S chunks after its
+    // neighbour, so chunk k is kept at place (k % S) sub + k / S: the same chunk
+    // of neighbouring groups is then contiguous (no bank conflicts)
+    int32_t S, inv, sub;                 // k / S == (k * inv) >> 16
+    int32_t row_b;                       // bytes of a plane's row of the input buffer
+    int32_t in_off, in_plane;            // the input's planes: byte offset in LDS, bytes per plane
+    int32_t out_off, out_plane, out_row_b, out_S, out_inv, out_sub;
+    int32_t a_off, bias_off;             // weights and bias in LDS
+    int32_t ng, oh, groups;              // groups per row, rows, groups of the output region
+    uint32_t ng_magic;                   // i / ng == (i * ng_magic) >> 24
+    int32_t relu, next_mode, rt, rl;     // what the next layer's padding reads outside; region origin
+    int32_t tab_off;                     // this layer's chunk offsets in LDS (steps x chunks a step)
+};
+struct MfmaArgs {
+    FusedArgs f;
+    ConvM c[kCnnFusedMaxLayers];
+    const void *image;                   // device: biases and fragments of every layer
+    int32_t image_bytes, planes_off, planes_bytes;   // LDS: image, then planes
+    int32_t pre;                         // the next tile is requested ahead
+    int32_t in_rank, out_rank, in_offsets, out_offsets;
+    int32_t imaged;                      // the sweep's last two dimensions are the image's (a snapshot record's are not)
+    int32_t ys, yd, yst, xs, xd, xst;    // sweep rows and columns: start, step, element stride
+    int32_t o_imaged;                    // the same of the `from` map, with one image
+    int32_t oys, oyd, oyst, oxs, oxd, oxst;
+    int32_t grid_x;                      // blocks per XCD
+};
+
+// A wave-uniform word of the block's LDS copy of the kernel arguments.  The
+// arguments are far more than the scalar registers hold over the kernel's
+// phases, and reading them again from memory costs microseconds (they lie in
+// host memory: 7 thousand cycles a phase as measured).
+__device__ __forceinline__ int32_t uni(const int32_t &v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The arguments where they lie (scalar loads), for the start and for rare paths.
+__device__ __forceinline__ const MfmaArgs &mfma_args() {
+    const __attribute__((address_space(4))) void *p =
+        (const __attribute__((address_space(4))) void *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const MfmaArgs *)(const __attribute__((address_space(4))) MfmaArgs *)p;
+}
+
+static_assert(sizeof(MfmaArgs) + sizeof(TabLds) + 2 * kMWaves * 4 <= kMStatic, "static LDS");
+
+// v0..v3 split into the three planes at byte `at` (four bf16 each).
+__device__ __forceinline__ void put4(char *base, int plane, int at, float v0, float v1, float v2, float v3) {
+    uint32_t q[3][2];
+    const float v[4] = {v0, v1, v2, v3};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
+        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+        q[0][i] = h;
+        q[1][i] = m;
+        q[2][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2 *>(base + at + p * plane) = make_uint2(q[p][0], q[p][1]);
+}
+
+// Byte e of a plane's row (see ConvM).
+__device__ __forceinline__ int row_spot(int e, int S, int inv, int sub) {
+    const int k = e >> 4, q = (k * inv) >> 16;
+    return ((k - q * S) * sub + q) * 16 + (e & 15);
+}
+
+// Region pixel i of layer 0's input at tile (s, y0, x0): element index of its
+// sweep point and where its boundary handling leaves it.
+struct GPix {
+    Pt32 pt;
+    bool zero;
+};
+__device__ __forceinline__ GPix region_pixel(const MfmaArgs &m, int i, int s, int y0, int x0, int32_t lead_pe,
+                                             const int32_t (&lead)[2], bool inside) {
+    const FusedArgs &a = m.f;
+    const int ry = div_region(i, a.rw_magic[0]), rx = i - ry * a.rw[0];
+    int y = y0 - a.rt[0] + ry, x = x0 - a.rl[0] + rx;
+    GPix g;
+    g.zero = false;
+    if (!inside && (y < 0 || y >= a.H || x < 0 || x >= a.W)) {
+        if (a.L[0].mode == HPACML_PADMODE_CIRCULAR) {
+            y = wrap(y, a.H);
+            x = wrap(x, a.W);
+        } else {
+            g.zero = a.L[0].mode == HPACML_PADMODE_ZEROS;
+            y = min(max(y, 0), a.H - 1);
+            x = min(max(x, 0), a.W - 1);
+        }
+    }
+    if (!m.imaged) {
+        g.pt = locate32(a.in, (s * a.H + y) * a.W + x);
+        return g;
+    }
+    // the sweep's last two dimensions are the image rows and columns
+    const int r = m.in_rank;
+    const int yy = m.ys + y * m.yd, xx = m.xs + x * m.xd;
+    g.pt.pe = lead_pe + yy * m.yst + xx * m.xst;
+    g.pt.p[0] = r == 2 ? yy : lead[0];
+    g.pt.p[1] = r == 2 ? xx : r == 3 ? yy : lead[1];
+    g.pt.p[2] = r == 2 ? 0 : r == 3 ? xx : yy;
+    g.pt.p[3] = r == 4 ? xx : 0;
+    return g;
+}
+
+// row m0 < 32 of a 32-row tile: pixel of the group (channels padded to co >= 8)
+__device__ __forceinline__ int pixel_of(int m0, int co) { return (m0 >= co) + (m0 >= 2 * co) + (m0 >= 3 * co); }
+
+template <bool M16>
+struct AccOf {
+    typedef floatx16 type;
+};
+template <>
+struct AccOf<true> {
+    typedef floatx4 type;
+};
+__device__ __forceinline__ floatx16 mma(u32x4 a, u32x4 b, floatx16 c) { return mfma(a, b, c); }
+__device__ __forceinline__ floatx4 mma(u32x4 a, u32x4 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// One layer of the tile: this wave's share of the groups.
+template <bool M16, bool LAST>
+__device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, const TabLds &tab, int wave, int lane, int s, int y0, int x0,
+                                          float &top) {
+    typedef typename AccOf<M16>::type Acc;
+    // columns; chunks per K-step; register quads; column tiles at a time (they
+    // share the weights' fragments, and the short 16-row tiles need company)
+    constexpr int N = M16 ? 16 : 32, KC = M16 ? 4 : 2, Q = M16 ? 1 : 4, T = M16 ? 2 : 1;
+    const ConvM &c = m.c[l];   // (m in LDS)
+    const int n = lane % N, kc = lane / N;
+    const int groups = uni(c.groups), ng = uni(c.ng), row_b = uni(c.row_b), plane = uni(c.in_plane), steps = uni(c.steps);
+    const int co = uni(c.co), P = uni(c.P), group_b = 16;
+    const uint32_t ng_magic = (uint32_t)uni((const int32_t &)c.ng_magic);
+    const char *in = lds + uni(c.in_off);
+    const char *wl = lds + uni(c.a_off) + lane * 16;
+    const int32_t *offs = reinterpret_cast<const int32_t *>(lds + uni(c.tab_off)) + kc;
+    const float *bias = reinterpret_cast<const float *>(lds + uni(c.bias_off));
+    const float floor = act_floor(uni(c.relu));
+    const int H = uni(m.f.H), W = uni(m.f.W), rt = uni(c.rt), rl = uni(c.rl);
+    const int out_S = uni(c.out_S), out_inv = uni(c.out_inv), out_sub = uni(c.out_sub);
+    const int out_off = uni(c.out_off), out_plane = uni(c.out_plane), out_row_b = uni(c.out_row_b), cout = uni(c.cout);
+    const bool circular = uni(m.f.circular), imaged = uni(m.o_imaged), offsets = uni(m.out_offsets);
+    const int oys = uni(m.oys), oyd = uni(m.oyd), oyst = uni(m.oyst), oxs = uni(m.oxs), oxd = uni(m.oxd), oxst = uni(m.oxst);
+    const int out_rank = uni(m.out_rank);
+    for (int t = wave; t * N * T < groups; t += kMWaves) {
+        int ry[T], gx[T];
+        const char *base[T];
+        Acc main[T], s0[T], s1[T];
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            const int gi = min((t * T + u) * N + n, groups - 1);
+            ry[u] = (int)(((uint32_t)gi * ng_magic) >> 24);
+            gx[u] = gi - ry[u] * ng;
+            base[u] = in + ry[u] * row_b + gx[u] * group_b;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int m0 = M16 ? 4 * kc : 8 * q + 4 * kc;
+                const int c0 = M16 ? 0 : m0 - pixel_of(m0, co) * co;
+                const float4 b4 = *reinterpret_cast<const float4 *>(bias + c0);
+                main[u][4 * q] = b4.x;
+                main[u][4 * q + 1] = b4.y;
+                main[u][4 * q + 2] = b4.z;
+                main[u][4 * q + 3] = b4.w;
+            }
+#pragma unroll
+            for (int r = 0; r < 4 * Q; ++r)
+                s0[u][r] = s1[u][r] = 0.f;
+        }
+        // K-steps two at a time: the fragments of one are read during the other
+        u32x4 b[2][T][3], w[2][3];
+        int off = offs[0];
+        auto fetch = [&](int st, u32x4 (&bb)[T][3], u32x4 (&ww)[3]) __attribute__((always_inline)) {
+            const char *q = wl + st * (3 * kFragBytes);
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                const char *p = base[u] + off;
+                bb[u][0] = *reinterpret_cast<const u32x4 *>(p);
+                bb[u][1] = *reinterpret_cast<const u32x4 *>(p + plane);
+                bb[u][2] = *reinterpret_cast<const u32x4 *>(p + 2 * plane);
+            }
+            ww[0] = *reinterpret_cast<const u32x4 *>(q);
+            ww[1] = *reinterpret_cast<const u32x4 *>(q + kFragBytes);
+            ww[2] = *reinterpret_cast<const u32x4 *>(q + 2 * kFragBytes);
+            off = offs[(st + 1) * KC];   // (the table ends with a spare step)
+        };
+        // (the two sums of small products in turn, also from one K-step to the
+        // next: no instruction waits for the one before it)
+        auto step = [&](const u32x4 (&bb)[T][3], const u32x4 (&ww)[3], Acc (&p0)[T], Acc (&p1)[T])
+                        __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+            auto product = [&](Acc (&d)[T], int x, int y) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < T; ++u)
+                    d[u] = mma(ww[x], bb[u][y], d[u]);
+                __builtin_amdgcn_sched_barrier(kSchedAluOnly);
+            };
+            product(p0, 0, 1);
+            product(p1, 0, 2);
+            product(main, 0, 0);
+            product(p0, 1, 0);
+            product(p1, 1, 1);
+            product(p0, 2, 0);
+        };
+        fetch(0, b[0], w[0]);
+        int st = 1;
+        for (; st + 1 < steps; st += 2) {
+            fetch(st, b[1], w[1]);
+            step(b[0], w[0], s0, s1);
+            fetch(st + 1, b[0], w[0]);
+            step(b[1], w[1], s1, s0);
+        }
+        if (st < steps) {
+            fetch(st, b[1], w[1]);
+            step(b[0], w[0], s0, s1);
+            step(b[1], w[1], s1, s0);
+        } else {
+            step(b[0], w[0], s0, s1);
+        }
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            const bool live = (t * T + u) * N + n < groups;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int m0 = M16 ? 4 * kc : 8 * q + 4 * kc;
+                const int px = M16 ? kc : pixel_of(m0, co), c0 = M16 ? 0 : m0 - px * co;
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[e] = __builtin_amdgcn_fmed3f(main[u][4 * q + e] + (s0[u][4 * q + e] + s1[u][4 * q + e]), floor, FLT_MAX);
+                top = max_abs(v[0], v[1], max_abs(v[2], v[3], top));
+                const int col = gx[u] * P + px;
+                const int y = y0 - rt + ry[u], x = x0 - rl + col;
+                if (LAST) {
+                    if (live && px < P && y < H && x < W) {
+                        Pt32 pt;
+                        if (imaged) {
+                            pt.p[0] = oys + y * oyd;
+                            pt.p[1] = oxs + x * oxd;
+                            pt.p[2] = pt.p[3] = 0;
+                            pt.pe = pt.p[0] * oyst + pt.p[1] * oxst;
+                        } else {
+                            pt = locate_lds(m.f.out, out_rank, (s * H + y) * W + x);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (c0 + e < cout) {
+                                int32_t idx[1] = {pt.pe};
+                                if (offsets) {
+                                    const uint32_t raw[1] = {tab.out_raw8[c0 + e]};
+                                    fix_lds<1>(m.f.out, pt, 15u, raw, idx);
+                                }
+                                stg(tab.out[c0 + e] + idx[0], v[e]);
+                            }
+                        }
+                    }
+                } else {
+                    const bool outside = !circular && (y < 0 || y >= H || x < 0 || x >= W);
+                    if (live && px < P) {
+                        if (outside)
+                            v[0] = v[1] = v[2] = v[3] = 0.f;   // (replicate: copied over afterwards)
+                        put4(lds + out_off, out_plane, ry[u] * out_row_b + row_spot((col * co + c0) * 2, out_S, out_inv, out_sub), v[0],
+                             v[1], v[2], v[3]);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Replicate padding of the next layer: pixels of this layer's output region
+// outside the image take the value at the nearest pixel inside (which the
+// region always contains).
+__device__ __forceinline__ void replicate_edges(const MfmaArgs &m, const ConvM &c, char *lds, int y0, int x0) {
+    const FusedArgs &a = m.f;
+    const int cols = c.ng * c.P, n = c.oh * cols;
+    for (int i = threadIdx.x; i < n; i += kMThreads) {
+        const int ry = i / cols, rx = i - ry * cols;
+        const int y = y0 - c.rt + ry, x = x0 - c.rl + rx;
+        const int qy = min(max(y, 0), a.H - 1) - y, qx = min(max(x, 0), a.W - 1) - x;
+        if (qy == 0 && qx == 0)
+            continue;
+        for (int e = 0; e < c.co / 4; ++e) {
+            const int d = c.out_off + ry * c.out_row_b + row_spot(rx * c.co * 2 + 8 * e, c.out_S, c.out_inv, c.out_sub);
+            const int from = c.out_off + (ry + qy) * c.out_row_b +
+                             row_spot((rx + qx) * c.co * 2 + 8 * e, c.out_S, c.out_inv, c.out_sub);
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<uint2 *>(lds + d + p * c.out_plane) =
+                    *reinterpret_cast<const uint2 *>(lds + from + p * c.out_plane);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, const float *__restrict__ wts) {
+    extern __shared__ float4 lds4[];
+    char *lds = reinterpret_cast<char *>(lds4);
+    __shared__ TabLds tab;
+    __shared__ MfmaArgs args_lds;
+    auto local = [&]() __attribute__((always_inline)) -> const MfmaArgs & {
+        int z = 0;
+        asm volatile("" : "+v"(z));   // read where it is used, not held in registers
+        return *reinterpret_cast<const MfmaArgs *>(reinterpret_cast<const char *>(&args_lds) + z);
+    };
+    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave: a value without a split, a normal input, an input that is not 0
+    int tile_no = 0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto clear = [&](int off, int bytes) {
+        for (int i = tid; i < bytes / 16; i += kMThreads)
+            reinterpret_cast<u32x4 *>(lds + off)[i] = u32x4{0u, 0u, 0u, 0u};
+    };
+    int n_tiles, n_layers, n_pix, grid_x, pre_on;
+    {
+        const MfmaArgs &m = mfma_args();
+        for (int i = tid; i < (int)(sizeof(MfmaArgs) / 4); i += kMThreads)
+            reinterpret_cast<int32_t *>(&args_lds)[i] = reinterpret_cast<const int32_t *>(&m)[i];
+        stage_tab(m.f, tab);
+        for (int i = tid; i < m.image_bytes / 16; i += kMThreads)
+            reinterpret_cast<u32x4 *>(lds)[i] = reinterpret_cast<const u32x4 *>(m.image)[i];
+        // byte offset of each chunk of K in a group's window (window row, place
+        // in it); past the last chunk the weights are zero and any place will do
+        for (int l = 0; l < m.f.n_layers; ++l) {
+            const int kcs = m.c[l].m16 ? 4 : 2, rch = m.c[l].rch, chunks = m.c[l].chunks;
+            int32_t *t = reinterpret_cast<int32_t *>(lds + m.c[l].tab_off);
+            for (int i = tid; i < (m.c[l].steps + 1) * kcs; i += kMThreads)
+                t[i] = i < chunks ? i / rch * m.c[l].row_b + row_spot(i % rch * 16, m.c[l].S, m.c[l].inv, m.c[l].sub) : 0;
+        }
+        n_tiles = m.f.n_tiles;
+        n_layers = m.f.n_layers;
+        n_pix = m.f.rh[0] * m.f.rw[0];
+        grid_x = m.grid_x;
+        pre_on = m.pre;
+    }
+    clear(mfma_args().planes_off, mfma_args().planes_bytes);   // columns past the gathered ones are read (with zero weights): they must be finite
+    __syncthreads();
+
+    // each XCD takes a contiguous range of tiles, its blocks adjacent ones
+    const int per = (n_tiles + 7) / 8, xcd = blockIdx.x % 8;
+    const int t_end = min(n_tiles, (xcd + 1) * per);
+    auto locate_tile = [&](const FusedArgs &a, int tile, int &s, int &y0, int &x0) {
+        const int tx = uni(a.tiles_x), per_img = uni(a.tiles_y) * tx;
+        s = tile / per_img;
+        const int rem = tile - s * per_img, ty_i = rem / tx;
+        y0 = ty_i * uni(a.ty);
+        x0 = (rem - ty_i * tx) * kTX;
+    };
+    // element index and coordinates of the leading sweep dimensions of image s
+    auto lead_of = [&](const MfmaArgs &m, int s, int32_t (&lead)[2]) -> int32_t {
+        const Map32 &in = m.f.in;
+        int32_t pe = 0;
+        const int rank = uni(m.imaged) ? uni(m.in_rank) : 0;
+        lead[0] = lead[1] = 0;
+        if (rank == 3) {
+            lead[0] = uni(in.start[0]) + s * uni(in.step[0]);
+            pe = lead[0] * uni(in.stride[0]);
+        } else if (rank == 4) {
+            const int n1 = uni(in.count[1]), q = s / n1;
+            lead[0] = uni(in.start[0]) + q * uni(in.step[0]);
+            lead[1] = uni(in.start[1]) + (s - q * n1) * uni(in.step[1]);
+            pe = lead[0] * uni(in.stride[0]) + lead[1] * uni(in.stride[1]);
+        }
+        return pe;
+    };
+    auto inside_of = [&](const FusedArgs &a, int y0, int x0) {
+        const int y = y0 - uni(a.rt[0]), x = x0 - uni(a.rl[0]);
+        return y >= 0 && x >= 0 && y + uni(a.rh[0]) <= uni(a.H) && x + uni(a.rw[0]) <= uni(a.W);
+    };
+    auto load4 = [&](const MfmaArgs &m, const GPix &g, int c4, float (&v)[4]) __attribute__((always_inline)) {
+        const FusedArgs &a = m.f;
+        const int ch = uni(a.c0);
+        const uint32_t edge = uni(m.in_offsets) ? edge_lds(a.in, uni(m.in_rank), g.pt) : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int f = 4 * c4 + e;
+            v[e] = 0.f;
+            if (f < ch) {
+                int32_t idx[1] = {g.pt.pe};
+                if (edge) {
+                    const uint32_t raw[1] = {tab.in_raw8[f]};
+                    fix_lds<1>(a.in, g.pt, edge, raw, idx);
+                }
+                v[e] = ldg(tab.in[f] + idx[0]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = g.zero ? 0.f : v[e];
+    };
+    // the pixels that this thread requests ahead: element offset from the
+    // region's first pixel, place in the planes (the same for every tile)
+    float pre[kPre][4];
+    int32_t rel[kPre], place[kPre];
+    if (pre_on) {
+        const MfmaArgs &m = mfma_args();
+#pragma unroll
+        for (int u = 0; u < kPre; ++u) {
+            const int i = min(tid + u * kMThreads, n_pix - 1);
+            const int ry = div_region(i, m.f.rw_magic[0]), rx = i - ry * m.f.rw[0];
+            rel[u] = ry * m.yd * m.yst + rx * m.xd * m.xst;
+            place[u] = m.c[0].in_off + ry * m.c[0].row_b + row_spot(rx * m.c[0].ci * 2, m.c[0].S, m.c[0].inv, m.c[0].sub);
+        }
+    }
+    uint32_t zeros = 0;   // bit u: pixel u is zero padding
+    auto request = [&](int tile) __attribute__((always_inline)) {
+        const MfmaArgs &m = local();
+        int s, y0, x0;
+        locate_tile(m.f, tile, s, y0, x0);
+        int32_t lead[2], at[kPre];
+        const int32_t pe = lead_of(m, s, lead);
+        zeros = 0;
+        if (inside_of(m.f, y0, x0) && uni(m.imaged)) {
+            const int32_t b = pe + (uni(m.ys) + (y0 - uni(m.f.rt[0])) * uni(m.yd)) * uni(m.yst) +
+                              (uni(m.xs) + (x0 - uni(m.f.rl[0])) * uni(m.xd)) * uni(m.xst);
+#pragma unroll
+            for (int u = 0; u < kPre; ++u)
+                at[u] = b + rel[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPre; ++u) {
+                const GPix g = region_pixel(m, min(tid + u * kMThreads, n_pix - 1), s, y0, x0, pe, lead, false);
+                at[u] = g.pt.pe;
+                zeros |= g.zero ? 1u << u : 0u;
+            }
+        }
+        // (nothing here waits for a load: padding and missing channels are
+        // zeroed when the values are used)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *p = tab.in[e];   // (entries past the last channel repeat it)
+#pragma unroll
+            for (int u = 0; u < kPre; ++u)
+                if (u * kMThreads < n_pix)
+                    pre[u][e] = ldg(p + at[u]);
+        }
+    };
+    const int first = xcd * per + blockIdx.x / 8;
+    if (pre_on && first < t_end)
+        request(first);
+    for (int tile = first; tile < t_end; tile += grid_x) {
+        int s, y0, x0;
+        float top = 0.f;        // the largest magnitude a layer gave
+        uint32_t in2 = 0;       // of the inputs, bits shifted past the sign (infinities and NaN above all)
+        {
+            const MfmaArgs &m = local();
+            locate_tile(m.f, tile, s, y0, x0);
+            const int in_off = uni(m.c[0].in_off), plane = uni(m.c[0].in_plane), row_b = uni(m.c[0].row_b), ci = uni(m.c[0].ci);
+            const uint32_t rw_magic = (uint32_t)uni((const int32_t &)m.f.rw_magic[0]);
+            const int rw = uni(m.f.rw[0]), ch = uni(m.f.c0);
+            const int S0 = uni(m.c[0].S), inv0 = uni(m.c[0].inv), sub0 = uni(m.c[0].sub);
+            auto put = [&](int at, const float (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    in2 = max(in2, __float_as_uint(v[e]) << 1);
+                put4(lds, plane, at, v[0], v[1], v[2], v[3]);
+            };
+            if (pre_on) {
+#pragma unroll
+                for (int u = 0; u < kPre; ++u) {
+                    if (tid + u * kMThreads < n_pix) {
+                        float v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            v[e] = (zeros >> u & 1u) || e >= ch ? 0.f : pre[u][e];
+                        put(place[u], v);
+                    }
+                }
+            } else {
+                int32_t lead[2];
+                const int32_t pe = lead_of(m, s, lead);
+                const bool inside = inside_of(m.f, y0, x0);
+                for (int i = tid; i < n_pix; i += kMThreads) {
+                    const GPix g = region_pixel(m, i, s, y0, x0, pe, lead, inside);
+                    const int ry = div_region(i, rw_magic), rx = i - ry * rw;
+                    for (int c4 = 0; c4 < ci / 4; ++c4) {
+                        float v[4];
+                        load4(m, g, c4, v);
+                        put(in_off + ry * row_b + row_spot((rx * ci + 4 * c4) * 2, S0, inv0, sub0), v);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (pre_on && tile + grid_x < t_end)
+            request(tile + grid_x);
+        for (int l = 0; l + 1 < n_layers; ++l) {
+            const MfmaArgs &m = local();
+            if (uni(m.c[l].m16))
+                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, top);
+            else
+                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, top);
+            __syncthreads();
+            if (uni(m.c[l].next_mode) == HPACML_PADMODE_REPLICATE) {
+                replicate_edges(m, m.c[l], lds, y0, x0);
+                __syncthreads();
+            }
+        }
+        {
+            const MfmaArgs &m = local();
+            if (uni(m.c[n_layers - 1].m16))
+                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, top);
+            else
+                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, top);
+        }
+        // (also the barrier after the last reads of this tile's planes)
+        const uint32_t kBig2 = __float_as_uint(kBig) << 1, kTiny2 = __float_as_uint(kTiny) << 1;
+        const uint32_t mine = (__any(top >= kBig || in2 >= kBig2) ? 1u : 0u) | (__any(in2 >= kTiny2) ? 2u : 0u) |
+                              (__any(in2 != 0) ? 4u : 0u);
+        if (lane == 0)
+            flags[tile_no & 1][wave] = mine;
+        __syncthreads();
+        uint32_t all = 0;
+#pragma unroll
+        for (int w = 0; w < kMWaves; ++w)
+            all |= flags[tile_no & 1][w];
+        ++tile_no;
+        all = __builtin_amdgcn_readfirstlane(all);
+        if ((all & 1u) || (all & 6u) == 4u) {
+            // a value without a split, or a tile of tiny ones
+            const MfmaArgs &m = mfma_args();
+            run_tile(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
+            __syncthreads();
+            clear(m.planes_off, m.planes_bytes);
+            __syncthreads();
+        }
+    }
 }
 
 // LDS floats of the two buffers for tiles of `ty` rows.
@@ -910,8 +1481,233 @@ int cnn_fused_tile_rows(const CnnFused &f, int32_t H) {
     return one;
 }
 
+// ---- matrix-core form: geometry, packing, choice of the tile
+static void mfma_shape(const CnnFusedLayer &y, ConvM *c) {
+    c->ci = 4 * y.cin4;
+    c->co = 4 * y.cout4;
+    c->m16 = y.cout4 == 1;
+    c->P = c->m16 ? 4 : 32 / c->co;
+    c->rch = ((y.kw + c->P - 1) * c->ci + 7) / 8;
+    c->chunks = y.kh * c->rch;
+    const int kc = c->m16 ? 4 : 2;
+    c->steps = (c->chunks + kc - 1) / kc;
+}
+
+bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, const CnnFused &f,
+                   std::vector<uint8_t> &buf) {
+    buf.clear();
+    for (int l = 0; l < f.n_layers; ++l) {
+        ConvM c{};
+        mfma_shape(f.L[l], &c);
+        const int cin = p.shape[l].c, cout = p.shape[l + 1].c, kh = f.L[l].kh, kw = f.L[l].kw;
+        const int N = c.m16 ? 16 : 32, kc = c.m16 ? 4 : 2;
+        const size_t at = buf.size();
+        buf.resize(at + 64 + (size_t)c.steps * 3 * kFragBytes, 0);
+        for (int o = 0; o < cout; ++o)
+            reinterpret_cast<float *>(&buf[at])[o] = b[l][o];
+        float top = 0.f;
+        for (int st = 0; st < c.steps; ++st)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int row = lane % N, ch = st * kc + lane / N;
+                const int px = row / c.co, o = row % c.co;
+                if (ch >= c.chunks || px >= c.P || o >= cout)
+                    continue;
+                const int ky = ch / c.rch;
+                for (int j = 0; j < 8; ++j) {
+                    const int e = ch % c.rch * 8 + j, kx = e / c.ci - px, i = e % c.ci;
+                    if (kx < 0 || kx >= kw || i >= cin)
+                        continue;
+                    const float w = W[l][(((size_t)o * cin + i) * kh + ky) * kw + kx];
+                    if (!(std::fabs(w) < kBig))
+                        return false;
+                    top = std::max(top, std::fabs(w));
+                    uint16_t *d = reinterpret_cast<uint16_t *>(&buf[at + 64 + (size_t)st * 3 * kFragBytes]) + lane * 8 + j;
+                    d[0] = rne(w);
+                    const float r = w - bf16_float(d[0]);
+                    d[kFragBytes / 2] = rne(r);
+                    d[kFragBytes] = rne(r - bf16_float(d[kFragBytes / 2]));
+                }
+            }
+        if (top != 0.f && top < kTiny)
+            return false;
+    }
+    return true;
+}
+
+// The launch's layer constants for tiles of `ty` rows; returns the LDS bytes.
+static size_t mfma_layout(const CnnFused &f, int ty, MfmaArgs *m) {
+    size_t f0, f1;
+    fused_regions(f, ty, &m->f, &f0, &f1);
+    const FusedArgs &a = m->f;
+    int off = 0;
+    for (int l = 0; l < f.n_layers; ++l) {
+        ConvM &c = m->c[l];
+        const CnnFusedLayer &y = f.L[l];
+        mfma_shape(y, &c);
+        c.cout = l + 1 < f.n_layers ? 4 * y.cout4 : f.cout_last;
+        c.bias_off = off;
+        c.a_off = off + 64;
+        off += 64 + c.steps * 3 * kFragBytes;
+        c.oh = a.rh[l + 1];
+        c.ng = (a.rw[l + 1] + c.P - 1) / c.P;
+        c.groups = c.oh * c.ng;
+        c.ng_magic = (uint32_t)(((1u << 24) + c.ng - 1) / c.ng);
+        c.relu = y.act == HPACML_ACT_RELU;
+        c.next_mode = l + 1 < f.n_layers ? f.L[l + 1].mode : HPACML_PADMODE_ZEROS;
+        c.rt = a.rt[l + 1];
+        c.rl = a.rl[l + 1];
+        // columns of the input buffer: the region, and what the layer before
+        // writes; chunks: those, and what the last group reads
+        int cols = a.rw[l];
+        if (l > 0)
+            cols = std::max(cols, m->c[l - 1].ng * m->c[l - 1].P);
+        c.S = c.P * c.ci / 8;
+        c.inv = (65536 + c.S - 1) / c.S;
+        c.sub = (std::max((cols * c.ci + 7) / 8, (c.ng - 1) * c.S + c.rch) + c.S - 1) / c.S;
+        c.row_b = c.S * c.sub * 16;
+        c.in_plane = a.rh[l] * c.row_b;
+    }
+    m->image_bytes = off;
+    for (int l = 0; l < f.n_layers; ++l) {
+        m->c[l].tab_off = off;
+        off += ((m->c[l].steps + 1) * (m->c[l].m16 ? 4 : 2) * 4 + 15) / 16 * 16;
+    }
+    m->planes_off = off;
+    int size[2] = {0, 0};
+    for (int l = 0; l < f.n_layers; ++l)
+        size[l & 1] = std::max(size[l & 1], 3 * m->c[l].in_plane);
+    for (int l = 0; l < f.n_layers; ++l) {
+        m->c[l].in_off = off + (l & 1 ? size[0] : 0);
+        if (l > 0) {
+            m->c[l - 1].out_off = m->c[l].in_off;
+            m->c[l - 1].out_plane = m->c[l].in_plane;
+            m->c[l - 1].out_row_b = m->c[l].row_b;
+            m->c[l - 1].out_S = m->c[l].S;
+            m->c[l - 1].out_inv = m->c[l].inv;
+            m->c[l - 1].out_sub = m->c[l].sub;
+        }
+    }
+    // (the vector ALU path of a tile uses the same space)
+    m->planes_bytes = std::max(size[0] + size[1], (int)((f0 + f1) * sizeof(float)) + 15 & ~15);
+    m->f.buf1 = (int32_t)f0;
+    return (size_t)off + m->planes_bytes;
+}
+
+// Tile rows of the matrix-core form for S images, or 0 where the vector ALU
+// kernel serves: no tile fits the LDS, or a large image and a stack with so few
+// multiplications that both wait for memory (2048 x 2048, 2 x 2 + 2 x 2 on 4
+// channels: 98 us against 109, 3 x 3 + 2 x 2: 110 / 115, 4 x 4: 102 / 93; at 1448 x
+// 1448 60 / 49).  The rows: the least time over the launch's rounds of 256 blocks.  A tile's cycles
+// as measured on the 5 x 5 + 3 x 3 stack with 6 to 18 rows (within 4%): 9500,
+// 8.2 per gathered pixel, and the matrix time of a wave's column tiles.
+int cnn_mfma_tile_rows(const CnnFused &f, int32_t S, int32_t H, int32_t W) {
+    int64_t taps = 0;   // multiplications per pixel
+    for (int l = 0; l < f.n_layers; ++l)
+        taps += 16 * f.L[l].kh * f.L[l].kw * f.L[l].cin4 * f.L[l].cout4;
+    if (taps <= 208 && (int64_t)S * H * W >= 3 << 20)
+        return 0;
+    int best = 0;
+    double least = 0;
+    for (int ty = 1; ty <= 32; ++ty) {
+        if (ty > 1 && ty > H)
+            break;
+        MfmaArgs m{};
+        if (mfma_layout(f, ty, &m) + kMStatic > kLdsOneBlock)
+            continue;
+        bool fits = true;   // the divisions' ranges (see launch_cnn_fused)
+        for (int l = 0; l <= f.n_layers; ++l)
+            fits = fits && m.f.rh[l] < 256 && m.f.rw[l] <= 256;
+        if (!fits)
+            continue;
+        double cycles = 9500 + 8.2 * m.f.rh[0] * m.f.rw[0];
+        for (int l = 0; l < f.n_layers; ++l) {
+            const ConvM &c = m.c[l];
+            const int n = c.m16 ? 16 : 32, each = c.m16 ? 2 : 1;   // columns of a tile, tiles at a time
+            const int rounds = ((c.groups + n * each - 1) / (n * each) + kMWaves - 1) / kMWaves;
+            cycles += (double)rounds * each * c.steps * 6 * n;
+        }
+        const double tiles = (double)S * ((H + ty - 1) / ty) * ((W + kTX - 1) / kTX);
+        const double t = std::ceil(tiles / 256) * cycles;
+        if (!best || t < least) {
+            best = ty;
+            least = t;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 *tin, const FeatTable32 *tout,
+                           const CnnFused &f, int32_t S, int32_t H, int32_t W, hipStream_t stream) {
+    const int ty = cnn_mfma_tile_rows(f, S, H, W);
+    if (ty == 0)
+        return hipErrorInvalidValue;
+    MfmaArgs m{};
+    const size_t lds = mfma_layout(f, ty, &m);
+    FusedArgs &a = m.f;
+    a.in = in;
+    a.out = out;
+    a.tin = tin;
+    a.tout = tout;
+    a.S = S;
+    a.H = H;
+    a.W = W;
+    a.n_layers = f.n_layers;
+    a.ty = ty;
+    a.tiles_y = (H + ty - 1) / ty;
+    a.tiles_x = (W + kTX - 1) / kTX;
+    const int64_t n_tiles = (int64_t)S * a.tiles_y * a.tiles_x;
+    if (n_tiles == 0)
+        return hipSuccess;
+    if (n_tiles > INT32_MAX - 16)
+        return hipErrorInvalidValue;
+    a.n_tiles = (int32_t)n_tiles;
+    a.c0 = f.c0;
+    a.cout_last = f.cout_last;
+    a.co_last_pad = 4 * f.L[f.n_layers - 1].cout4;
+    a.circular = f.circular;
+    for (int l = 0; l < f.n_layers; ++l)
+        a.L[l] = f.L[l];
+    for (int l = 0; l <= f.n_layers; ++l)
+        a.rw_magic[l] = (uint32_t)(((1u << 24) + a.rw[l] - 1) / a.rw[l]);
+    m.image = f.image;
+    m.in_rank = in.rank;
+    m.out_rank = out.rank;
+    for (int d = 0; d < out.rank; ++d)
+        m.out_offsets |= out.omin[d] != 0 || out.omax[d] != 0;
+    for (int d = 0; d < in.rank; ++d)
+        m.in_offsets |= in.omin[d] != 0 || in.omax[d] != 0;
+    m.pre = m.c[0].ci == 4 && a.rh[0] * a.rw[0] <= kPre * kMThreads && !m.in_offsets;
+    m.o_imaged = out.rank == 2 && out.count[0] == H && out.count[1] == W;   // (so S is 1)
+    if (m.o_imaged) {
+        m.oys = out.start[0];
+        m.oyd = out.step[0];
+        m.oyst = out.stride[0];
+        m.oxs = out.start[1];
+        m.oxd = out.step[1];
+        m.oxst = out.stride[1];
+    }
+    m.imaged = in.rank >= 2 && in.count[in.rank - 2] == H && in.count[in.rank - 1] == W;
+    if (m.imaged) {
+        m.ys = in.start[in.rank - 2];
+        m.yd = in.step[in.rank - 2];
+        m.yst = in.stride[in.rank - 2];
+        m.xs = in.start[in.rank - 1];
+        m.xd = in.step[in.rank - 1];
+        m.xst = in.stride[in.rank - 1];
+    }
+    m.grid_x = (int32_t)std::min<int64_t>(32, (n_tiles + 7) / 8);
+    hipError_t e = hipFuncSetAttribute((const void *)cnn_fused_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(cnn_fused_mfma_kernel, dim3((unsigned)(8 * m.grid_x)), dim3(kMThreads), lds, stream, m, f.wts);
+    return hipGetLastError();
+}
+
 hipError_t launch_cnn_fused(const Map32 &in, const Map32 &out, const FeatTable32 *tin, const FeatTable32 *tout,
                             const CnnFused &f, int32_t S, int32_t H, int32_t W, hipStream_t stream) {
+    if (f.image && cnn_mfma_tile_rows(f, S, H, W) > 0)
+        return launch_cnn_mfma(in, out, tin, tout, f, S, H, W, stream);
     const int ty = cnn_fused_tile_rows(f, H);
     if (ty == 0)
         return hipErrorInvalidValue;

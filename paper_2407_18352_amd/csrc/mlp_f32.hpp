@@ -6,6 +6,7 @@
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
+#include <vector>
 
 #include "kernels.hpp"
 
@@ -327,30 +328,45 @@ inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t
 template <typename Hm, typename Lo, typename Feature>
 inline bool put_layer(char *img, const float *W, int N, int K, int steps, int blocks, Hm &&hm, Lo &&lo,
                       Feature &&feature) {
-    bool fine = true;
-    float top = 0.f;
-    for (int s = 0; s < steps; ++s)
+    // split the layer in its own order (a loop the compiler vectorises), then
+    // place the parts
+    const size_t n = (size_t)N * K;
+    std::vector<uint16_t> q(3 * n);
+    uint16_t *qh = q.data(), *qm = qh + n, *ql = qm + n;
+    uint32_t top = 0;   // magnitudes as bits: infinities and NaN above all
+    for (size_t i = 0; i < n; ++i) {
+        const float w = W[i];
+        top = std::max(top, __builtin_bit_cast(uint32_t, w) & 0x7FFFFFFFu);
+        qh[i] = rne(w);
+        const float r = w - bf16_float(qh[i]);
+        qm[i] = rne(r);
+        ql[i] = rne(r - bf16_float(qm[i]));
+    }
+    for (int s = 0; s < steps; ++s) {
+        int at[2][8];
+        for (int g = 0; g < 2; ++g)
+            for (int j = 0; j < 8; ++j)
+                at[g][j] = feature(s, g, j);
         for (int mb = 0; mb < blocks; ++mb) {
-            uint16_t *qh = reinterpret_cast<uint16_t *>(img + hm(s, mb)), *qm = qh + kFragBytes / 2;
-            uint16_t *ql = reinterpret_cast<uint16_t *>(img + lo(s, mb));
-            for (int l = 0; l < 64; ++l)
+            uint16_t *h = reinterpret_cast<uint16_t *>(img + hm(s, mb)), *m = h + kFragBytes / 2;
+            uint16_t *l = reinterpret_cast<uint16_t *>(img + lo(s, mb));
+            for (int lane = 0; lane < 64; ++lane) {
+                if (32 * mb + lane % 32 >= N)
+                    continue;
+                const size_t row = (size_t)(32 * mb + lane % 32) * K;
                 for (int j = 0; j < 8; ++j) {
-                    const int k = feature(s, l / 32, j), row = 32 * mb + l % 32;
-                    const float w = k < K && row < N ? W[(size_t)row * K + k] : 0.f;
-                    if (!(std::fabs(w) < 0x1p127f)) {
-                        fine = false;
-                        continue;
+                    const int k = at[lane / 32][j];
+                    if (k < K) {
+                        h[lane * 8 + j] = qh[row + k];
+                        m[lane * 8 + j] = qm[row + k];
+                        l[lane * 8 + j] = ql[row + k];
                     }
-                    top = std::max(top, std::fabs(w));
-                    const uint16_t h = rne(w);
-                    const float r = w - bf16_float(h);
-                    const uint16_t m = rne(r);
-                    qh[l * 8 + j] = h;
-                    qm[l * 8 + j] = m;
-                    ql[l * 8 + j] = rne(r - bf16_float(m));
                 }
+            }
         }
-    return fine && (top == 0.f || top >= 0x1p-100f);
+    }
+    const float largest = __builtin_bit_cast(float, top);
+    return top == 0 || (largest >= 0x1p-100f && largest < kBig);
 }
 
 }  // namespace

@@ -1,0 +1,104 @@
+"""The fused convolution kernel multiplies on the bf16 matrix cores, each float
+split in three, several pixels of a row to a column of the product: its shapes
+(pixels a group, channel groups, windows that end inside a 16-byte chunk, odd
+K-steps, images smaller than a tile) against 64 bits, and pixels whose value
+has no split."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2407_18352_amd import workloads as wl
+from gpu_util import parity_stats, require_gpu
+from test_gpu_cnn import _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _workload(cin, layers, mode, S, H, W, seed=0, acts=None):
+    g = np.random.default_rng(seed + 17 * cin + H * W)
+    ls, c = [], cin
+    for i, (cout, kh, kw) in enumerate(layers):
+        m = mode[i] if isinstance(mode, list) else mode
+        act = acts[i] if acts else (wl.RELU if i + 1 < len(layers) else wl.IDENTITY)
+        ls.append(wl.conv_layer(900 + seed, 3 * i, c, cout, (kh, kw), mode=m, act=act))
+        c = cout
+    spec = {"rank": 3, "slices": [((0, 0, 0), (1, 1, 1))], "sweep": ((0, 0, 0), (S, H, W), (1, 1, 1)), "bnd": [0, 0, 0]}
+    model = {"kind": "cnn", "in_channels": cin, "image": (H, W), "layers": ls}
+    return wl.Workload("split", 0, "f32", [cin, c], spec, spec,
+                       [g.standard_normal((S, H, W)).astype(np.float32) for _ in range(cin)],
+                       [wl.sentinel_like((S, H, W)) for _ in range(c)], model)
+
+
+def _both(w):
+    got, var = _run(w)
+    assert var == "cnn_fused_f32", var
+    exp = [a.copy() for a in w.outputs]
+    oracle.infer(w.in_spec, w.inputs, w.out_spec, exp, w.model)
+    return np.stack([a.reshape(-1) for a in got], 1), np.stack([a.reshape(-1) for a in exp], 1)
+
+
+@pytest.mark.parametrize("cin, layers, mode", [
+    (4, [(8, 5, 5), (4, 3, 3)], "circular"),               # four pixels a group in both forms
+    (1, [(4, 2, 2)], "zeros"),                             # one layer, 16 rows, one channel
+    (3, [(12, 3, 4), (16, 2, 3), (9, 1, 5)], "replicate"), # two pixels a group; 12 and 16 channels, two groups of 4 unused
+    (5, [(6, 4, 2), (13, 3, 3), (7, 2, 2), (2, 3, 1)], "zeros"),
+    (8, [(8, 3, 3)], "replicate"),                         # inputs not requested ahead
+    (4, [(5, 8, 8), (4, 2, 6)], "circular"),
+    (4, [(4, 1, 1), (4, 7, 3), (4, 1, 2)], ["zeros", "replicate", "zeros"]),
+])
+@pytest.mark.parametrize("S, H, W", [(1, 37, 150), (2, 3, 5), (3, 19, 64), (1, 1, 200)])
+def test_shapes_against_64_bits(cin, layers, mode, S, H, W):
+    w = _workload(cin, layers, mode, S, H, W)
+    got, want = _both(w)
+    worst, norm, nan = parity_stats(got, want)
+    # a rounding of one part in 2^24 per 8 values of K and 6 more a layer, independent; four times that for the worst
+    bound = 2.0 ** -24 * np.sqrt(sum(kh * kw * c / 8 + 6 for (_, kh, kw), c in zip(layers, [cin] + [l[0] for l in layers])))
+    assert nan == 0 and worst <= 16 * bound, (worst, bound)
+    if H * W > 1000:
+        assert norm <= bound, (norm, bound)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("acts", [[1, 0], [0, 0]])
+def test_values_without_a_split(value, acts):
+    """One such pixel: the same classes of results as 64-bit arithmetic gives,
+    everywhere else the usual accuracy (a matrix column holds neighbouring
+    pixels, whose windows do not reach it)."""
+    w = _workload(4, [(8, 5, 5), (4, 3, 3)], "zeros", 1, 50, 140, acts=acts)
+    w.inputs[2][0, 21, 67] = value
+    if value == 3e38:   # finite sums in 64 bits and in 32: weights that bring it back
+        w.model["layers"][0]["W"][:, 2] *= np.float32(2.0 ** -127)
+    got, want = _both(w)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fine = np.isfinite(want).all(1)
+    far = np.ones((50, 140), bool)
+    far[18:25, 64:71] = False                      # beyond both windows' reach of the pixel
+    assert fine[far.reshape(-1)].all()
+    assert parity_stats(got[fine], want[fine])[0] <= 1e-5
+
+
+@pytest.mark.parametrize("exponent", [-90, -101, -120])
+def test_tiny_images(exponent):
+    w = _workload(4, [(8, 3, 3), (4, 3, 3)], "circular", 1, 40, 70, seed=2)
+    for a in w.inputs:
+        a[:] = (np.abs(a) + 0.5).astype(np.float32) * np.float32(2.0 ** exponent)
+    for ly in w.model["layers"]:
+        ly["b"][:] = 0
+    w.model["layers"][1]["W"] *= np.float32(2.0 ** -exponent)
+    got, want = _both(w)
+    worst, _, nan = parity_stats(got, want)
+    assert nan == 0 and worst <= 1e-5, worst
+
+
+def test_weight_without_a_split():
+    w = _workload(4, [(8, 3, 3), (4, 3, 3)], "circular", 1, 40, 70, seed=3)
+    w.model["layers"][0]["W"][3, 1, 1, 2] = 2.0 ** 127
+    w.inputs[1] *= np.float32(2.0 ** -126)
+    got, want = _both(w)
+    assert parity_stats(got, want)[0] <= 1e-5
