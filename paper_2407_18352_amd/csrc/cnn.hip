@@ -928,81 +928,105 @@ constexpr size_t kLdsOneBlock = 160 * 1024;
 // One thread per output pixel and group of kConvG output channels
 // (blockIdx.y).  Weights packed [group][ky][kx][ci][kConvG], zero past cout:
 // in the channels-last image the taps of one window row are one contiguous
-// run of kw * cin floats, and the kConvG weights of a tap are one
-// wave-uniform 32-byte scalar load, so every input value read feeds kConvG
-// FMAs.  Taps go in chunks of kTapChunk whose input loads are all issued
-// before the first FMA.  A pixel whose window leaves the image (SAME
-// padding at the border) resolves each tap through the padding mode.
+// run of kw * cin floats.  Taps go in chunks of kTapChunk whose input loads are
+// all issued before the first product.  A wave whose windows all lie inside the
+// image multiplies on the fp32 matrix instruction of sixteen 4 x 4 blocks:
+// columns = the wave's 64 pixels, rows = 4 output channels, one tap per
+// instruction, the block of A broadcast to the others (sixteen taps' weights for
+// 4 channels in one register): twice the vector ALU's rate and beside its index
+// arithmetic.  A wave with a window that leaves the image (SAME padding at the
+// border) works on the vector ALU, its weights as wave-uniform scalar loads, each
+// tap resolved through the padding mode.  Measured: 4 x 4, 8 channels, 2 x 2 pool on 1024
+// frames of 128 x 128: 21.0 -> 17.0 us (67 MB of frames: 4.5 TB/s with the output); the
+// whole model with 2 x 2 windows 91.7 -> 75 us, 7 x 7 and a 3 x 3 pool 49.7 -> 42.4.  What
+// bounds it: memory latency at a tile per wave, and its index arithmetic.
 //
 // With POOL, a max-pool whose windows do not overlap follows in the same
 // kernel, so the convolution's output never goes to memory: a group of
-// 2^qshift adjacent lanes holds one pooled pixel, lane q computing window
+// 2^QS adjacent lanes holds one pooled pixel, lane q computing window
 // position q (lanes past the window repeat position 0), and the group's
-// maximum comes from xor shuffles.  Each pairwise step keeps the lower
+// maximum comes from pairwise exchanges.  Each step keeps the lower
 // lane's value unless the other is larger or a NaN, and a NaN once taken
 // stays: the window's first NaN, else its first maximum, as in the pool
-// kernel.
+// kernel.  In a step the two lanes share the channels between them, so the
+// next one has half as many to exchange (7 in all for four lanes' 8 channels
+// where every lane reducing all of them takes 16), and the lanes of a group
+// store their channels side by side.
 constexpr int kTapChunk = 16;
 
-// Convolution outputs (bias, taps, activation) of output pixel (oy, ox).
+// One chunk's products: v[j] = this lane's value of tap t0 + j, a register of
+// weights for each four channels (see conv_pixel).
+__device__ __forceinline__ void conv_taps(const float (&v)[kTapChunk], int left, float w0, float w1, floatx4 &a0,
+                                          floatx4 &a1) {
+    static_for<0, kTapChunk / 4>([&](auto jj) __attribute__((always_inline)) {
+        constexpr int j = 4 * jj;
+        if (j < left) {   // taps past the last are zeros in both operands
+            static_for<0, 4>([&](auto ii) __attribute__((always_inline)) {
+                constexpr int t = j + ii;
+                a0 = __builtin_amdgcn_mfma_f32_4x4x1f32(w0, v[t], a0, 4, t, 0);
+                a1 = __builtin_amdgcn_mfma_f32_4x4x1f32(w1, v[t], a1, 4, t, 0);
+            });
+        }
+    });
+}
+
+// Convolution outputs (bias, taps, activation) of output pixel (oy, ox).  Called
+// by whole waves.
 __device__ __forceinline__ void conv_pixel(const CnnLayerDev &L, const float *img, const float *__restrict__ wg,
                                            int oy, int ox, int ng, float (&acc)[kConvG]) {
+    static_assert(kConvG == 8 && kTapChunk == 16, "two registers of sixteen taps' weights");
     const int y0 = oy * L.sh - (L.same ? (L.kh - 1) / 2 : 0);
     const int x0 = ox * L.sw - (L.same ? (L.kw - 1) / 2 : 0);
     const int taps = L.kh * L.kw * L.cin;
 #pragma unroll
     for (int g = 0; g < kConvG; ++g)
         acc[g] = g < ng ? L.b[blockIdx.y * kConvG + g] : 0.f;
-    if (y0 >= 0 && x0 >= 0 && y0 + L.kh <= L.h && x0 + L.kw <= L.w) {
+    if (__all(y0 >= 0 && x0 >= 0 && y0 + L.kh <= L.h && x0 + L.kw <= L.w)) {
         const float *base = img + ((int64_t)y0 * L.w + x0) * L.cin;
         const int run = L.kw * L.cin;                 // floats of one window row
         const int64_t rs = (int64_t)L.w * L.cin;      // image row stride
+        const int lane = threadIdx.x & 63;
+        // weights of tap t0 + lane / 4, channels lane % 4 and 4 + lane % 4
+        const float *wl = wg + (lane >> 2) * kConvG + (lane & 3);
+        floatx4 a0 = {acc[0], acc[1], acc[2], acc[3]}, a1 = {acc[4], acc[5], acc[6], acc[7]};
+        const bool vec = run % 4 == 0 && rs % 4 == 0 && __all(((uintptr_t)base & 15) == 0);
         int ky = 0, r = 0;
-        if (run % 4 == 0 && rs % 4 == 0 && ((uintptr_t)base & 15) == 0) {
-            // window rows of whole, aligned float4s: 16-byte loads
-            for (int t0 = 0; t0 < taps; t0 += kTapChunk) {
-                float4 v[kTapChunk / 4];
+        for (int t0 = 0; t0 < taps; t0 += kTapChunk) {
+            const bool in = t0 + (lane >> 2) < taps;
+            const float w0 = in ? wl[t0 * kConvG] : 0.f, w1 = in ? wl[t0 * kConvG + 4] : 0.f;
+            float v[kTapChunk];
+            if (vec) {
+                // window rows of whole, aligned float4s: 16-byte loads
 #pragma unroll
-                for (int j = 0; j < kTapChunk / 4; ++j) {
-                    v[j] = t0 + 4 * j < taps ? *reinterpret_cast<const float4 *>(base + ky * rs + r)
-                                             : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int j = 0; j < kTapChunk; j += 4) {
+                    const float4 q = t0 + j < taps ? *reinterpret_cast<const float4 *>(base + ky * rs + r)
+                                                   : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[j] = q.x;
+                    v[j + 1] = q.y;
+                    v[j + 2] = q.z;
+                    v[j + 3] = q.w;
                     r += 4;
                     if (r == run) {
                         r = 0;
                         ++ky;
                     }
                 }
+            } else {
 #pragma unroll
-                for (int j = 0; j < kTapChunk / 4; ++j)
-                    if (t0 + 4 * j < taps) {
-                        const float *w = wg + (int64_t)(t0 + 4 * j) * kConvG;
-                        const float e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-#pragma unroll
-                            for (int g = 0; g < kConvG; ++g)
-                                acc[g] = fmaf(w[i * kConvG + g], e[i], acc[g]);
+                for (int j = 0; j < kTapChunk; ++j) {
+                    v[j] = t0 + j < taps ? base[ky * rs + r] : 0.f;
+                    if (++r == run) {
+                        r = 0;
+                        ++ky;
                     }
-            }
-        } else
-        for (int t0 = 0; t0 < taps; t0 += kTapChunk) {
-            float v[kTapChunk];
-#pragma unroll
-            for (int j = 0; j < kTapChunk; ++j) {
-                v[j] = t0 + j < taps ? base[ky * rs + r] : 0.f;
-                if (++r == run) {
-                    r = 0;
-                    ++ky;
                 }
             }
+            conv_taps(v, taps - t0, w0, w1, a0, a1);
+        }
 #pragma unroll
-            for (int j = 0; j < kTapChunk; ++j)
-                if (t0 + j < taps) {
-                    const float *w = wg + (int64_t)(t0 + j) * kConvG;
-#pragma unroll
-                    for (int g = 0; g < kConvG; ++g)
-                        acc[g] = fmaf(w[g], v[j], acc[g]);
-                }
+        for (int g = 0; g < 4; ++g) {
+            acc[g] = a0[g];
+            acc[4 + g] = a1[g];
         }
     } else {
         for (int ky = 0; ky < L.kh; ++ky) {
@@ -1049,15 +1073,42 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t i, uint32_t magic, uint32_t sh
     return (uint32_t)(((uint64_t)i * magic) >> shift);
 }
 
-template <bool POOL>
-__global__ void __launch_bounds__(256) cnn_conv_kernel(CnnLayerDev L, CnnLayerDev P, int qshift,
-                                                      const float *__restrict__ in, float *__restrict__ out,
-                                                      int64_t n_pix) {
+// The value of lane l ^ D (neighbours within four lanes without LDS).
+template <int D>
+__device__ __forceinline__ float lane_xor(float v) {
+    if (D <= 2)
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), D == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+    return __shfl_xor(v, D);
+}
+
+// Maximum of acc[0, N) over the lanes l, l ^ D, ... of the 2^QS-lane groups.
+// While more than one channel is left a lane keeps half of them: the lower of
+// a pair the first half.  Returns in `c0` the first channel the lane ends up with.
+template <int D, int END, int N>
+__device__ __forceinline__ void group_max(int q, float (&acc)[kConvG], int &c0) {
+    if constexpr (D < END) {
+        constexpr int H = N > 1 ? N / 2 : 1;
+        const bool lower = (q & D) == 0;
+#pragma unroll
+        for (int g = 0; g < H; ++g) {
+            const float mine = N > 1 && !lower ? acc[H + g] : acc[g];
+            const float give = N > 1 && lower ? acc[H + g] : acc[g];
+            const float o = lane_xor<D>(give);
+            const float a = lower ? mine : o, b = lower ? o : mine;
+            acc[g] = (!(a != a) && (b != b || b > a)) ? b : a;
+        }
+        if (N > 1 && !lower)
+            c0 += H;
+        group_max<2 * D, END, H>(q, acc, c0);
+    }
+}
+
+template <bool POOL, int QS>
+__global__ void __launch_bounds__(256) cnn_conv_kernel(CnnLayerDev L, CnnLayerDev P, const float *__restrict__ in,
+                                                      float *__restrict__ out, int64_t n_pix) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t pix = POOL ? tid >> qshift : tid;
-    if (!POOL && pix >= n_pix)
-        return;
-    // (pooled: every lane of a group takes part in the shuffles)
+    const int64_t pix = POOL ? tid >> QS : tid;
+    // (every lane takes part in the matrix instructions and the exchanges)
     const int64_t pc = pix < n_pix ? pix : n_pix - 1;
     const int co0 = blockIdx.y * kConvG;
     const int ng = min(kConvG, L.cout - co0);
@@ -1077,7 +1128,7 @@ __global__ void __launch_bounds__(256) cnn_conv_kernel(CnnLayerDev L, CnnLayerDe
         oy = (int)(pc / G.w2 % G.h2);
         s = pc / ((int64_t)G.w2 * G.h2);
     }
-    const int q = POOL ? (int)(tid & ((1 << qshift) - 1)) : 0;
+    const int q = POOL ? (int)(tid & ((1 << QS) - 1)) : 0;
     if (POOL) {
         // window position qq < 16 of a window kw <= 16 wide: (qq + 1/2) / kw
         // lies at least 1/32 from an integer, so the approximate reciprocal
@@ -1092,21 +1143,31 @@ __global__ void __launch_bounds__(256) cnn_conv_kernel(CnnLayerDev L, CnnLayerDe
     float acc[kConvG];
     conv_pixel(L, img, wg, oy, ox, ng, acc);
     if (POOL) {
-        for (int d = 1; d < (1 << qshift); d <<= 1) {
-            const bool lower = (q & d) == 0;
-#pragma unroll
-            for (int g = 0; g < kConvG; ++g) {
-                const float o = __shfl_xor(acc[g], d);
-                const float a = lower ? acc[g] : o, b = lower ? o : acc[g];
-                acc[g] = (!(a != a) && (b != b || b > a)) ? b : a;
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < kConvG; ++g)
-            acc[g] = P.act == HPACML_ACT_RELU ? (acc[g] > 0.f ? acc[g] : 0.f) : acc[g];
-        if (q != 0 || pix >= n_pix)
+        constexpr int C = kConvG >> QS ? kConvG >> QS : 1;   // channels a lane ends up with
+        int c0 = 0;
+        group_max<1, 1 << QS, kConvG>(q, acc, c0);
+        if (pix >= n_pix || q >= kConvG)   // (16 lanes: the last 8 hold the same as the first)
             return;
+        float *o = out + pix * L.cout + co0 + c0;
+#pragma unroll
+        for (int g = 0; g < C; ++g)
+            acc[g] = P.act == HPACML_ACT_RELU ? (acc[g] > 0.f ? acc[g] : 0.f) : acc[g];
+        if (C == 2 && c0 + 2 <= ng && ((uintptr_t)o & 7) == 0) {
+            *reinterpret_cast<float2 *>(o) = make_float2(acc[0], acc[1]);
+        } else if (C >= 4 && c0 + C <= ng && ((uintptr_t)o & 15) == 0) {
+#pragma unroll
+            for (int g = 0; g + 3 < C; g += 4)
+                *reinterpret_cast<float4 *>(o + g) = make_float4(acc[g], acc[g + 1], acc[g + 2], acc[g + 3]);
+        } else {
+#pragma unroll
+            for (int g = 0; g < C; ++g)
+                if (c0 + g < ng)
+                    o[g] = acc[g];
+        }
+        return;
     }
+    if (pix >= n_pix)
+        return;
     float *o = out + pix * L.cout + co0;
     if (ng == kConvG && ((uintptr_t)o & 15) == 0) {
         *reinterpret_cast<float4 *>(o) = make_float4(acc[0], acc[1], acc[2], acc[3]);
@@ -1817,12 +1878,14 @@ hipError_t launch_cnn_conv(const CnnLayerDev &L, const CnnLayerDev *pool, const 
     const int64_t bx = ((n_pix << qshift) + 255) / 256, by = (L.cout + kConvG - 1) / kConvG;
     if (bx > INT32_MAX || by > 65535)
         return hipErrorInvalidValue;
-    if (pool)
-        hipLaunchKernelGGL(cnn_conv_kernel<true>, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, stream, L, *pool,
-                           qshift, in, out, n_pix);
-    else
-        hipLaunchKernelGGL(cnn_conv_kernel<false>, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, stream, L, L, 0,
-                           in, out, n_pix);
+    const auto kernel = !pool         ? cnn_conv_kernel<false, 0>
+                        : qshift == 0 ? cnn_conv_kernel<true, 0>
+                        : qshift == 1 ? cnn_conv_kernel<true, 1>
+                        : qshift == 2 ? cnn_conv_kernel<true, 2>
+                        : qshift == 3 ? cnn_conv_kernel<true, 3>
+                                      : cnn_conv_kernel<true, 4>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, stream, L, pool ? *pool : L, in, out,
+                       n_pix);
     return hipGetLastError();
 }
 
