@@ -881,11 +881,8 @@ hpacml_status cnn_infer(const hpacml_model *model, const hpacml_map *in, const h
     const int64_t per = (S * c.max_elems + 63) / 64 * 64;   // 256-byte aligned buffers
     // split-K partial sums of the fully connected layers
     int64_t part_floats = 0;
-    for (const CnnLayerDev &L : model->cnn_layers) {
-        const int z = linear_splits(L, S);
-        if (z > 1)
-            part_floats = std::max<int64_t>(part_floats, (int64_t)z * S * L.cout);
-    }
+    for (const CnnLayerDev &L : model->cnn_layers)
+        part_floats = std::max<int64_t>(part_floats, linear_part_rows(L, S) * L.cout);
     float *a = nullptr, *b = nullptr, *part = nullptr;
     {
         std::lock_guard<std::mutex> lock(mm->ws_mu);

@@ -1377,6 +1377,133 @@ __global__ void __launch_bounds__(256) cnn_linear_mfma_kernel(CnnLayerDev L, con
         }
 }
 
+// The same products where the images are few (see split_few): a block owns 32
+// images x 64 outputs and one K range, its four waves a quarter of the range
+// each, in steps of 32 k: loads one step ahead (eight lanes to 128 bytes of a
+// row) go through the wave's own part of the LDS, without a barrier, to
+// fragments (lane l: k of half l / 32 of the step; the two halves' k pair up in
+// an instruction).  The waves' sums meet in LDS in wave
+// order, so a K range is four times as long as a 128-image block's for as many
+// blocks, and a quarter as many partial sums go through memory.  What bounds
+// it is the latency of one round of blocks, not the matrix cores.  VEC: rows of
+// whole, aligned float4s.
+constexpr int kFewS = 32, kFewRows = kFewS + kMfO;
+constexpr int kFewPad = kMfK + 4;   // floats a staged row: 16 rows read at once lie in 64 different banks
+template <bool VEC>
+__global__ void __launch_bounds__(256) cnn_linear_few_kernel(CnnLayerDev L, const float *__restrict__ in, int64_t S,
+                                                            int64_t Kc, float *__restrict__ part) {
+    __shared__ __align__(16) float lds[4 * kFewRows * kFewPad];
+    auto red = reinterpret_cast<float(*)[kFewS][kMfO + 4]>(lds);   // after the products
+    static_assert(4 * kFewS * (kMfO + 4) <= 4 * kFewRows * kFewPad, "the sums fit where the rows were");
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int col = lane & 31, kh = lane >> 5;
+    const int O = L.cout;
+    const int64_t s0 = (int64_t)blockIdx.x * kFewS;
+    const int o0 = blockIdx.y * kMfO;
+    const int64_t K = (int64_t)L.h * L.w * L.cin;
+    // Kc is a multiple of 128: whole steps for every wave, cut at K
+    const int64_t kb = (int64_t)blockIdx.z * Kc + w * (Kc / 4);
+    const int64_t ke = kb + Kc / 4 < K ? kb + Kc / 4 : K;
+    // row 8m + lane / 8 of the step's 96 (32 images, 64 outputs), floats 4 (lane % 8) .. + 3;
+    // rows past the last image or output read the last one, their results unused
+    const int lr = lane >> 3, lk = 4 * (lane & 7);
+    float *mine = lds + w * kFewRows * kFewPad;
+    float4 pre[kFewRows / 8];
+    auto fetch = [&](int64_t k0) {
+        const int64_t k = k0 + lk;
+#pragma unroll
+        for (int m = 0; m < kFewRows / 8; ++m) {
+            const float *p;
+            if (8 * m < kFewS) {
+                const int64_t r = s0 + 8 * m + lr;
+                p = in + (r < S ? r : S - 1) * K + k;
+            } else {
+                const int r = o0 + 8 * m - kFewS + lr;
+                p = L.W + (int64_t)(r < O ? r : O - 1) * K + k;
+            }
+            if (VEC)
+                pre[m] = k < ke ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
+            else
+                pre[m] = make_float4(k < ke ? p[0] : 0.f, k + 1 < ke ? p[1] : 0.f, k + 2 < ke ? p[2] : 0.f,
+                                     k + 3 < ke ? p[3] : 0.f);
+        }
+    };
+    floatx16 acc[2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            acc[mb][r] = 0.f;
+    if (kb < ke)
+        fetch(kb);
+    for (int64_t k0 = kb; k0 < ke; k0 += 32) {
+#pragma unroll
+        for (int m = 0; m < kFewRows / 8; ++m)
+            *reinterpret_cast<float4 *>(mine + (8 * m + lr) * kFewPad + lk) = pre[m];
+        // the wave's own writes before its reads, and these before the next step's writes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (k0 + 32 < ke)
+            fetch(k0 + 32);
+        float4 x[4], y[2][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float *f = mine + col * kFewPad + 16 * kh + 4 * i;
+            x[i] = *reinterpret_cast<const float4 *>(f);
+            y[0][i] = *reinterpret_cast<const float4 *>(f + kFewS * kFewPad);
+            y[1][i] = *reinterpret_cast<const float4 *>(f + (kFewS + 32) * kFewPad);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float b[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+            const float a0[4] = {y[0][i].x, y[0][i].y, y[0][i].z, y[0][i].w};
+            const float a1[4] = {y[1][i].x, y[1][i].y, y[1][i].z, y[1][i].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[j], b[j], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[j], b[j], acc[1], 0, 0, 0);
+            }
+        }
+    }
+    __syncthreads();   // every wave is done with its rows
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4 *>(&red[w][col][32 * mb + 8 * q + 4 * kh]) =
+                make_float4(acc[mb][4 * q], acc[mb][4 * q + 1], acc[mb][4 * q + 2], acc[mb][4 * q + 3]);
+    __syncthreads();
+    // thread t: outputs 4 (t % 16) .. + 3 of images t / 16 and t / 16 + 16
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int si = t / 16 + 16 * h, oi = t % 16 * 4;
+        const int64_t s = s0 + si;
+        float4 v = *reinterpret_cast<const float4 *>(&red[0][si][oi]);
+#pragma unroll
+        for (int u = 1; u < 4; ++u) {
+            const float4 p = *reinterpret_cast<const float4 *>(&red[u][si][oi]);
+            v.x += p.x;
+            v.y += p.y;
+            v.z += p.z;
+            v.w += p.w;
+        }
+        if (s >= S)
+            continue;
+        float *dst = part + ((int64_t)blockIdx.z * S + s) * O + o0 + oi;
+        if (o0 + oi + 3 < O && ((uintptr_t)dst & 15) == 0) {
+            *reinterpret_cast<float4 *>(dst) = v;
+        } else {
+            const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (o0 + oi + i < O)
+                    dst[i] = e[i];
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) cnn_linear_reduce_kernel(CnnLayerDev L, const float *__restrict__ part,
                                                                float *__restrict__ out, int64_t S, int splits) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1846,11 +1973,30 @@ void cnn_conv_pack(const float *W, int cout, int cin, int kh, int kw, std::vecto
 // outputs, where most of such a tile would be padding.
 int linear_tile(const CnnLayerDev &L) { return L.cout > 16 ? 64 : 16; }
 
+// Few images: where the 32-image kernel's blocks take at least two K ranges to
+// fill the chip's 256 CUs (128-image / 32-image kernel, whole model of a 2048 -> 64
+// layer: 16 images 18.1 / 15.0 us, 1024: 30.0 / 27.8, 4096: 82.2 / 75.9; above that
+// the larger tiles fill the chip too and read the weights a quarter as often), and
+// a step for each wave of two ranges at least.
+static int64_t few_tiles(const CnnLayerDev &L, int64_t S) {
+    return ((S + kFewS - 1) / kFewS) * ((L.cout + kMfO - 1) / kMfO);
+}
+static bool split_few(const CnnLayerDev &L, int64_t S) {
+    const int64_t K = (int64_t)L.h * L.w * L.cin;
+    return L.cout > 16 && L.cout <= 256 && K >= 256 && few_tiles(L, S) <= 128;
+}
+
 int linear_splits(const CnnLayerDev &L, int64_t S) {
     if (L.kind != HPACML_LAYER_LINEAR || S <= 0)
         return 1;
     const int64_t K = (int64_t)L.h * L.w * L.cin;
     const int64_t T = linear_tile(L);
+    if (split_few(L, S)) {
+        // about 256 blocks, each at least one 32-k step per wave (more ranges for a
+        // long K, 1024 each: 32768 -> 33 on 1024 images 104 us against 99)
+        const int64_t tiles = few_tiles(L, S);
+        return (int)std::min<int64_t>(std::min<int64_t>((256 + tiles - 1) / tiles, K / 128), kLinSplit);
+    }
     // split products of layers with more than 16 outputs run on the MFMA
     // kernel's 128 x 64 tiles
     const int64_t blocks = T == 64 ? ((S + kMfS - 1) / kMfS) * ((L.cout + kMfO - 1) / kMfO)
@@ -1858,6 +2004,18 @@ int linear_splits(const CnnLayerDev &L, int64_t S) {
     int64_t z = (1024 + blocks - 1) / blocks;                 // about 1024 blocks in all
     z = std::min<int64_t>(z, std::max<int64_t>(1, K / 64));  // at least 64 k per block
     return (int)std::max<int64_t>(1, std::min<int64_t>(z, kLinSplit));
+}
+
+int64_t linear_part_rows(const CnnLayerDev &L, int64_t S) {
+    const int64_t z = linear_splits(L, S);
+    if (z <= 1)
+        return 0;
+    if (!split_few(L, S))
+        return z * S;
+    // z S < 256 S / tiles + S and S / tiles <= 32 / (output tiles): growing with S,
+    // so a workspace made for more images serves fewer
+    const int64_t K = (int64_t)L.h * L.w * L.cin, to = (L.cout + kMfO - 1) / kMfO;
+    return std::min<int64_t>(std::min<int64_t>(K / 128, kLinSplit) * S, 256 * kFewS / to + 1 + S);
 }
 
 // pooled pixels take groups of 2^qshift lanes: windows of at most 16
@@ -1895,7 +2053,13 @@ hipError_t launch_linear_split(const CnnLayerDev &L, const float *in, float *out
                                hipStream_t stream) {
     const int64_t K = (int64_t)L.h * L.w * L.cin;
     const int64_t Kc = (K + splits - 1) / splits;
-    if (linear_tile(L) == 64) {
+    if (split_few(L, S)) {
+        const int64_t Kf = (Kc + 127) / 128 * 128;   // a range past K leaves zeros
+        const unsigned bx = (unsigned)((S + kFewS - 1) / kFewS), by = (unsigned)((L.cout + kMfO - 1) / kMfO);
+        const bool vec = K % 4 == 0 && ((uintptr_t)in & 15) == 0 && ((uintptr_t)L.W & 15) == 0;
+        hipLaunchKernelGGL(vec ? cnn_linear_few_kernel<true> : cnn_linear_few_kernel<false>, dim3(bx, by, splits),
+                           dim3(256), 0, stream, L, in, S, Kf, part);
+    } else if (linear_tile(L) == 64) {
         const int64_t bx = (S + kMfS - 1) / kMfS, by = (L.cout + kMfO - 1) / kMfO;
         if (bx > INT32_MAX || by > 65535)
             return hipErrorInvalidValue;

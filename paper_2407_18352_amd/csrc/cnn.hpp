@@ -25,10 +25,11 @@ void cnn_layer_divisors(CnnLayerDev &L);
 // Convolution weights [cout][cin][kh][kw] -> [ceil(cout / kConvG)][kh][kw][cin]
 // [kConvG], zero past cout (appended to `dst`).
 void cnn_conv_pack(const float *W, int cout, int cin, int kh, int kw, std::vector<float> &dst);
-// `part`: scratch of linear_splits(L, S) * S * cout floats for a fully
+// `part`: scratch of linear_part_rows(L, S) * cout floats for a fully
 // connected layer whose K is split over several blocks (unused otherwise)
 constexpr int kLinSplit = 32;
 int linear_splits(const CnnLayerDev &L, int64_t S);
+int64_t linear_part_rows(const CnnLayerDev &L, int64_t S);
 hipError_t launch_cnn_layer(const CnnLayerDev &L, const float *in, float *out, int64_t S, float *part,
                             hipStream_t stream);
 // A convolution and the max-pool after it in one kernel: pools whose

@@ -1,5 +1,7 @@
-"""Max-pools that share their channels between the lanes of a window, against the
-oracle: window sizes of every group of lanes, channel counts that leave lanes idle."""
+"""Fully connected layers on few images (32 images and 64 outputs a block, a K
+range over four waves) and max-pools that share their channels between the
+lanes of a window, against the oracle: edges of tiles, K not a multiple of a
+step or of four floats, padded ranges, channel counts that leave lanes idle."""
 import numpy as np
 import pytest
 
@@ -27,6 +29,18 @@ def _both(S, H, W, layers, n_out, seed):
     exp = [a.copy() for a in w.outputs]
     oracle.infer(w.in_spec, w.inputs, w.out_spec, exp, w.model)
     return np.stack([a.reshape(-1) for a in got], 1), np.stack([a.reshape(-1) for a in exp], 1)
+
+
+@pytest.mark.parametrize("S, H, W, out", [
+    (1, 16, 16, 17), (31, 16, 16, 64), (33, 16, 17, 65), (100, 17, 19, 33), (1, 29, 40, 256), (1024, 17, 19, 33),
+    (100, 29, 40, 256), (4096, 16, 16, 17), (4097, 16, 16, 17)])   # the last by the 128-image kernel
+def test_linear(S, H, W, out):
+    layers = [wl.linear_layer(61, 0, H * W, out), wl.linear_layer(62, 0, out, 3, act=0)]
+    got, want = _both(S, H, W, layers, 3, seed=S + out)
+    worst, norm, nan = parity_stats(got, want)
+    # sums of H W + out products, each rounded to 2^-24 of a partial sum: at most a random walk of that many roundings
+    bound = 2.0 ** -24 * np.sqrt(H * W + out)
+    assert nan == 0 and worst <= 8 * bound and norm <= bound, (worst, norm, bound)
 
 
 @pytest.mark.parametrize("pool", [(1, 1), (1, 2), (2, 2), (1, 3), (2, 3), (4, 2), (3, 3), (4, 4)])
