@@ -611,7 +611,7 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
 
         if (f32_fast_supported(n_layers, fd, compute)) {
             std::vector<float> img(f32_image_floats(n_layers, fd));
-            m->f32.plain = !f32_pack(n_layers, fd, fW, fb, img.data());
+            f32_pack(n_layers, fd, fW, fb, img.data(), &m->f32);
             s = upload(&m->f32_img, img.data(), img.size());
             if (s != HPACML_OK) {
                 hpacml_model_destroy(m);
@@ -663,7 +663,7 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
         }
         if (m->variant == Variant::Generic && f32w_supported(n_layers, dims, compute)) {
             std::vector<float> img(f32w_image_floats(n_layers, dims));
-            m->f32w.plain = !f32w_pack(n_layers, dims, W, b, img.data(), &m->f32w);
+            f32w_pack(n_layers, dims, W, b, img.data(), &m->f32w);
             s = upload(&m->f32_img, img.data(), img.size());
             if (s != HPACML_OK) {
                 hpacml_model_destroy(m);

@@ -331,8 +331,8 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
 // ------------------------------------------------------------------ fused, matrix cores
 // The same tiles with the convolutions on the bf16 matrix cores, every float
 // as the exact sum of three bf16 parts (see mlp_f32.hip: six products, hi hi
-// accumulated apart; values without a split send their tile to the vector
-// ALU path above).
+// accumulated apart; values outside the range of that arithmetic send their
+// tile to the vector ALU path above).
 //
 // A few channels would fill a quarter of a matrix instruction's rows, so P
 // neighbouring output pixels of a row share one column of it: rows = (pixel of
@@ -379,6 +379,7 @@ struct MfmaArgs {
     FusedArgs f;
     ConvM c[kCnnFusedMaxLayers];
     const void *image;                   // device: biases and fragments of every layer
+    float limit;                         // of the layers' inputs (see input_limit)
     int32_t image_bytes, planes_off, planes_bytes;   // LDS: image, then planes
     int32_t pre;                         // the next tile is requested ahead
     int32_t in_rank, out_rank, in_offsets, out_offsets;
@@ -488,7 +489,7 @@ __device__ __forceinline__ floatx4 mma(u32x4 a, u32x4 b, floatx4 c) {
 // One layer of the tile: this wave's share of the groups.
 template <bool M16, bool LAST>
 __device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, const TabLds &tab, int wave, int lane, int s, int y0, int x0,
-                                          float &top) {
+                                          Range &range) {
     typedef typename AccOf<M16>::type Acc;
     // columns; chunks per K-step; register quads; column tiles at a time (they
     // share the weights' fragments, and the short 16-row tiles need company)
@@ -594,7 +595,10 @@ __device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, c
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     v[e] = __builtin_amdgcn_fmed3f(main[u][4 * q + e] + (s0[u][4 * q + e] + s1[u][4 * q + e]), floor, FLT_MAX);
-                top = max_abs(v[0], v[1], max_abs(v[2], v[3], top));
+                if (!LAST) {
+                    range.add(v[0], v[1]);
+                    range.add(v[2], v[3]);
+                }
                 const int col = gx[u] * P + px;
                 const int y = y0 - rt + ry[u], x = x0 - rl + col;
                 if (LAST) {
@@ -667,7 +671,7 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         asm volatile("" : "+v"(z));   // read where it is used, not held in registers
         return *reinterpret_cast<const MfmaArgs *>(reinterpret_cast<const char *>(&args_lds) + z);
     };
-    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave: a value without a split, a normal input, an input that is not 0
+    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave: a value outside the range, a normal input, an input that is not 0
     int tile_no = 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto clear = [&](int off, int bytes) {
@@ -803,8 +807,8 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         request(first);
     for (int tile = first; tile < t_end; tile += grid_x) {
         int s, y0, x0;
-        float top = 0.f;        // the largest magnitude a layer gave
-        uint32_t in2 = 0;       // of the inputs, bits shifted past the sign (infinities and NaN above all)
+        Range range;            // of the layers' inputs but the first's
+        uint32_t in2 = 0;       // the first's: largest magnitude, bits shifted past the sign (infinities and NaN above all)
         {
             const MfmaArgs &m = local();
             locate_tile(m.f, tile, s, y0, x0);
@@ -850,9 +854,9 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         for (int l = 0; l + 1 < n_layers; ++l) {
             const MfmaArgs &m = local();
             if (uni(m.c[l].m16))
-                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, top);
+                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, range);
             else
-                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, top);
+                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, range);
             __syncthreads();
             if (uni(m.c[l].next_mode) == HPACML_PADMODE_REPLICATE) {
                 replicate_edges(m, m.c[l], lds, y0, x0);
@@ -862,13 +866,13 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         {
             const MfmaArgs &m = local();
             if (uni(m.c[n_layers - 1].m16))
-                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, top);
+                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, range);
             else
-                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, top);
+                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, range);
         }
         // (also the barrier after the last reads of this tile's planes)
-        const uint32_t kBig2 = __float_as_uint(kBig) << 1, kTiny2 = __float_as_uint(kTiny) << 1;
-        const uint32_t mine = (__any(top >= kBig || in2 >= kBig2) ? 1u : 0u) | (__any(in2 >= kTiny2) ? 2u : 0u) |
+        const uint32_t kLimit2 = __float_as_uint(local().limit) << 1, kTiny2 = __float_as_uint(kTiny) << 1;
+        const uint32_t mine = (__any(range.outside(local().limit) || in2 >= kLimit2) ? 1u : 0u) | (__any(in2 >= kTiny2) ? 2u : 0u) |
                               (__any(in2 != 0) ? 4u : 0u);
         if (lane == 0)
             flags[tile_no & 1][wave] = mine;
@@ -880,7 +884,7 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         ++tile_no;
         all = __builtin_amdgcn_readfirstlane(all);
         if ((all & 1u) || (all & 6u) == 4u) {
-            // a value without a split, or a tile of tiny ones
+            // a value outside the range, or a tile of tiny ones
             const MfmaArgs &m = mfma_args();
             run_tile(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
             __syncthreads();
@@ -1681,9 +1685,10 @@ static void mfma_shape(const CnnFusedLayer &y, ConvM *c) {
     c->steps = (c->chunks + kc - 1) / kc;
 }
 
-bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, const CnnFused &f,
+bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, CnnFused &f,
                    std::vector<uint8_t> &buf) {
     buf.clear();
+    f.limit = kBig;   // the least of the layers'
     for (int l = 0; l < f.n_layers; ++l) {
         ConvM c{};
         mfma_shape(f.L[l], &c);
@@ -1716,7 +1721,8 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                     d[kFragBytes] = rne(r - bf16_float(d[kFragBytes / 2]));
                 }
             }
-        if (top != 0.f && top < kTiny)
+        f.limit = std::min(f.limit, input_limit(W[l], b[l], cout, cin * kh * kw));
+        if ((top != 0.f && top < kTiny) || f.limit <= 0.f)
             return false;
     }
     return true;
@@ -1858,6 +1864,7 @@ hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 
     for (int l = 0; l <= f.n_layers; ++l)
         a.rw_magic[l] = (uint32_t)(((1u << 24) + a.rw[l] - 1) / a.rw[l]);
     m.image = f.image;
+    m.limit = f.limit;
     m.in_rank = in.rank;
     m.out_rank = out.rank;
     for (int d = 0; d < out.rank; ++d)

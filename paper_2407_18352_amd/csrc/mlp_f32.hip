@@ -36,11 +36,12 @@
 // slots t = 8s .. 8s + 7 of K-step s.  Output layer (<= 8 outputs): the fp32 matrix
 // instruction of 4 x 4 blocks.  Biases enter as the initial accumulator.
 //
-// Values of 2^127 and more (infinities among them) have no such split, and
-// inputs that are all below 2^-100 lose bits in it: a wave that meets a point
-// of that kind (or such an activation) computes its tile again on the fp32
-// matrix instruction, with the caller's weights read from global memory; so
-// does every wave of a model with such a weight or layer of weights.
+// Values of 2^127 and more (infinities among them) have no such split, values
+// large enough for a sum to overflow could turn an infinity into a NaN (see
+// input_limit), and inputs that are all below 2^-100 lose bits: a wave that
+// meets a point of that kind (or such an activation) computes its tile again on
+// the fp32 matrix instruction, with the caller's weights read from global
+// memory; so does every wave of a model with such a weight or layer of weights.
 #include "mlp_f32.hpp"
 
 namespace hpacml {
@@ -172,7 +173,9 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         const bool valid = b < n_points;
         int ln = lane;
         asm volatile("" : "+v"(ln));   // nothing read from LDS is held from one tile to the next
-        float top = pk.plain ? kBig : 0.f;   // the largest magnitude met
+        Range range;   // of the inputs of every layer
+        if (pk.plain)
+            range.top = kBig;
         Split b1[KS1];
         floatx16 acc[NMB];
         const u32x4 *fl = lds4 + ln;                                        // this lane's part of the LDS fragments
@@ -245,7 +248,7 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
 #pragma unroll
                         for (int r = 0; r < 16; ++r)
                             main[i][r] += sub[i][r];
-                    activate<2>(main, act_floor(relu), top);
+                    activate<2>(main, act_floor(relu), range);
                     acc[2 * p] = main[0];
                     acc[2 * p + 1] = main[1];
                     __builtin_amdgcn_sched_barrier(0);
@@ -260,12 +263,14 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
                 for (int j = 0; j < 8; ++j) {
                     // zero where there is no feature (only in the last K-step)
                     v[j] = s < KS1 - 1 || 2 * (8 * s + j) + g < F ? xn[8 * s + j] : 0.f;
-                    }
-                top = max_abs(v[0], v[1], max_abs(v[2], v[3], max_abs(v[4], v[5], max_abs(v[6], v[7], top))));
+                }
+#pragma unroll
+                for (int j = 0; j < 8; j += 2)
+                    range.add(v[j], v[j + 1]);
                 b1[s] = split8(v);
             });
-            if (tiny_inputs(top))
-                top = kBig;
+            if (tiny_inputs(range.top))
+                range.top = kBig;
         });
 
         // ---- hidden layers H -> H
@@ -284,8 +289,8 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         };
         for (int h = 0; h < pk.n_hidden; ++h)
             hidden(h);
-        if (__any(top >= kBig)) {
-            // a value without a split: this tile again on the fp32 instruction
+        if (__any(range.outside(pk.limit))) {
+            // this tile again on the fp32 instruction
             const MapsLds &tab = maps();
             const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
             layers_plain<NMB>(pk, lds, lay, [&](int s) __attribute__((always_inline)) {
@@ -410,8 +415,8 @@ size_t f32_image_floats(int n_layers, const int32_t *dims) {
 
 // Host packing of the split image (see SplitLayout): A fragments in the order
 // the lanes read them, biases and output weights in the C-fragment order.
-// Returns whether every weight has a three-way split.
-bool f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *img) {
+void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *img,
+              F32Packed *pk) {
     const int H = dims[1], NMB = H / 32, Fin = dims[0], Fout = dims[n_layers], NH = n_layers - 2;
     const SplitLayout sl{NMB, (Fin + 15) / 16, NH, Fout};
     std::fill(img, img + sl.total() / 4, 0.f);
@@ -446,7 +451,12 @@ bool f32_pack(int n_layers, const int32_t *dims, const float *const *W, const fl
                 }
     for (int go = 0; go < Fout; ++go)
         img[sl.out_b() / 4 + go] = b[n_layers - 1][go];
-    return fine;
+    // the least of the layers' limits, which takes one running maximum in the
+    // kernel (the output layer is on the fp32 instruction)
+    pk->limit = kBig;
+    for (int l = 0; l + 1 < n_layers; ++l)
+        pk->limit = std::min(pk->limit, input_limit(W[l], b[l], dims[l + 1], dims[l]));
+    pk->plain = !fine || pk->limit <= 0.f;
 }
 
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

@@ -168,20 +168,29 @@ __device__ __forceinline__ float max_abs(float a, float b, float m) {
 // Lower bound of a layer's activation: 0 (ReLU) or none.
 __device__ __forceinline__ float act_floor(bool relu) { return relu ? 0.f : -FLT_MAX; }
 
+// The magnitudes that a lane met among a layer's inputs.
+struct Range {
+    float top = 0.f;   // the largest (a NaN is passed over)
+    __device__ __forceinline__ void add(float a, float b) { top = max_abs(a, b, top); }
+    // Whether a layer could leave the range (limit: see input_limit).
+    __device__ __forceinline__ bool outside(float limit) const { return top >= limit; }
+};
+
 // Activation as one v_med3_f32(x, floor, FLT_MAX), without a branch, so that it
-// can be scheduled beside matrix instructions; the largest magnitude joins
-// `top`.  A NaN becomes the floor (v_med3_f32 returns the least of the other
+// can be scheduled beside matrix instructions; the magnitudes join `range`.
+// Only a NaN among the inputs makes a NaN here (no sum overflows, see
+// input_limit).  It becomes the floor (v_med3_f32 returns the least of the other
 // two): 0 under ReLU, and the -FLT_MAX of an identity layer, like any
 // magnitude of 2^127 and more, sends the tile to the fp32 instruction.
 template <int N>
-__device__ __forceinline__ void activate(floatx16 *acc, float floor, float &top) {
+__device__ __forceinline__ void activate(floatx16 *acc, float floor, Range &range) {
 #pragma unroll
     for (int mb = 0; mb < N; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
             acc[mb][r] = __builtin_amdgcn_fmed3f(acc[mb][r], floor, FLT_MAX);
             acc[mb][r + 1] = __builtin_amdgcn_fmed3f(acc[mb][r + 1], floor, FLT_MAX);
-            top = max_abs(acc[mb][r], acc[mb][r + 1], top);
+            range.add(acc[mb][r], acc[mb][r + 1]);
         }
 }
 
@@ -312,6 +321,25 @@ struct OutPoint {
         }
     }
 };
+
+// The magnitude from which on a layer's inputs go to the fp32 instruction; 0 when
+// all have to.  Below it no sum overflows: with the largest row sum of |w| and
+// inputs below the limit the products of a row, and the bias, come to 2^126
+// each, so that hi hi (at most 1 + 2^-6 times as large) and the sums of small
+// products stay finite.  Otherwise an infinite sum of hi hi could meet small
+// products that are infinite with the other sign, where the fp32 sum is infinite.
+inline float input_limit(const float *W, const float *b, int N, int K) {
+    double worst = 0;
+    for (int o = 0; o < N; ++o) {
+        double sum = 0;
+        for (int k = 0; k < K; ++k)
+            sum += std::fabs((double)W[(size_t)o * K + k]);
+        if (!(sum < HUGE_VAL) || !(std::fabs(b[o]) < 0.5f * kBig))
+            return 0.f;
+        worst = std::max(worst, sum);
+    }
+    return worst <= 0.5 ? kBig : (float)(0.5 * kBig / worst * (1 - 0x1p-20));
+}
 
 // Host side of the split: rounded to nearest even, as the device's conversion
 // (finite values).

@@ -98,7 +98,9 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
         asm volatile("" : "+v"(ln));
         const u32x4 *fl = lds4 + ln;
         const u32x4 *gl = reinterpret_cast<const u32x4 *>(pk.image) + ln;
-        float top = pk.plain ? kBig : 0.f;
+        Range range;   // of the inputs of every layer
+        if (pk.plain)
+            range.top = kBig;
         Split b1[KS1];
         static_for<0, KS1>([&](auto s) __attribute__((always_inline)) {
             floatx8 v;
@@ -107,11 +109,13 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                 // zero where there is no feature
                 v[j] = 2 * (8 * s + j) + g < F ? xn[8 * s + j] : 0.f;
             }
-            top = max_abs(v[0], v[1], max_abs(v[2], v[3], max_abs(v[4], v[5], max_abs(v[6], v[7], top))));
-                b1[s] = split8(v);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2)
+                range.add(v[j], v[j + 1]);
+            b1[s] = split8(v);
         });
-        if (tiny_inputs(top))
-            top = kBig;
+        if (tiny_inputs(range.top))
+            range.top = kBig;
         if (tile + order.step < order.end) {
             gather_inputs<KS1>(maps(), rank_in, n_points, windowed, pairs, (tile + order.step) * 32 + col, g, xn);
         } else {
@@ -154,7 +158,7 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 main[r] += sub[r];
-            activate<1>(&main, act_floor(pk.relu >> layer & 1), top);
+            activate<1>(&main, act_floor(pk.relu >> layer & 1), range);
             return main;
         };
         if constexpr (G == 0) {
@@ -262,9 +266,8 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                     out_add(finish(m2[i], s2[i], 1), p + i);
             }
         }
-        if (__any(top >= kBig)) {
-            // a value without a split: this tile again on the fp32 instruction,
-            // with the caller's weights in global memory (rows and columns past
+        if (__any(range.outside(pk.limit))) {
+            // this tile again on the fp32 instruction, with the caller's weights in global memory (rows and columns past
             // them are zero)
             const MapsLds &tab = maps();
             const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
@@ -367,7 +370,7 @@ bool f32w_supported(int n_layers, const int32_t *dims, int compute) {
 
 size_t f32w_image_floats(int n_layers, const int32_t *dims) { return (size_t)wide_layout(n_layers, dims).total() / 4; }
 
-bool f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
+void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
                F32WPacked *pk) {
     const WideLayout lay = wide_layout(n_layers, dims);
     pk->nb1 = lay.nb1;
@@ -407,7 +410,12 @@ bool f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
         }
     for (int o = 0; o < O; ++o)
         reinterpret_cast<float *>(img + lay.out_b())[o] = b[n_layers - 1][o];
-    return fine;
+    // the least of the layers' limits, which takes one running maximum in the
+    // kernel (the output layer is on the fp32 instruction)
+    pk->limit = kBig;
+    for (int l = 0; l + 1 < n_layers; ++l)
+        pk->limit = std::min(pk->limit, input_limit(W[l], b[l], dims[l + 1], dims[l]));
+    pk->plain = !fine || pk->limit <= 0.f;
 }
 
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

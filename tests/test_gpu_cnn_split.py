@@ -102,3 +102,26 @@ def test_weight_without_a_split():
     w.inputs[1] *= np.float32(2.0 ** -126)
     got, want = _both(w)
     assert parity_stats(got, want)[0] <= 1e-5
+
+
+@pytest.mark.parametrize("layers", [[(8, 3, 3), (4, 3, 3)], [(8, 3, 3)], [(4, 3, 3)], [(4, 1, 1), (8, 3, 3), (3, 2, 2)]])
+@pytest.mark.parametrize("factor, value", [(1.0e20, 1.1e25), (7.77e20, 9.3e25), (3.3e19, 5.9e24), (2.0e21, 6.1e20)])
+def test_overflow_inside_a_layer(layers, factor, value):
+    """One weight of 1e20 meets one pixel of 1e25 (of either sign, in a ReLU
+    layer): infinite, or 0, like every output that it reaches; the other pixels
+    are as accurate as ever."""
+    for sign in (1, -1):
+        w = _workload(4, layers, "zeros", 1, 40, 140, seed=5, acts=[1] * len(layers))
+        L = w.model["layers"]
+        L[0]["W"][:, 1] = 0
+        L[0]["W"][2, 1, 0, 0] = factor
+        for ly in L[1:]:
+            ly["W"][:] = np.abs(ly["W"]) + np.float32(0.01)
+        w.inputs[1][:] = 0
+        w.inputs[1][0, 21, 67] = sign * np.float32(value)
+        got, want = _both(w)
+        assert np.isinf(want).any() == (sign > 0)
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+        rows = np.isfinite(want).all(1)
+        assert np.isfinite(got[rows]).all()
+        assert parity_stats(got[rows], want[rows])[0] <= 1e-5

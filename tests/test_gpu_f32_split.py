@@ -136,3 +136,29 @@ def test_weight_without_a_split(value, dims):
     w.model["W"][0][17, 2] = value
     got, want = _run(w, "mlp_")
     assert parity_stats(got, want)[0] <= 1e-5
+
+
+@pytest.mark.parametrize("factor, value", [(1.0e20, 1.1e25), (7.77e20, 9.3e25), (3.3e19, 5.9e24), (2.0e21, 6.1e20)])
+@pytest.mark.parametrize("dims", [[7, 64, 1], [7, 64, 64, 2], [12, 128, 128, 128, 1], [12, 40, 1], [12, 200, 40, 1], [9, 300, 3]])
+def test_overflow_inside_a_layer(dims, factor, value):
+    """One weight of 1e20 meets one input of 1e25 in some points, everything else
+    is of order 1: the neuron is infinite (or, negative, 0 after its ReLU) and
+    so is every output that it reaches; the other points are as accurate as ever."""
+    n = 100
+    g = np.random.default_rng(dims[0])
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    W = w.model["W"]
+    W[0][:, 3] = 0
+    W[0][17, 3] = factor
+    for l in range(1, len(W)):
+        W[l][:] = np.abs(W[l]) + np.float32(0.01)   # the infinity reaches every output, and meets no other sign
+    w.inputs[3][:] = 0
+    for k, sign in ((5, 1), (37, -1), (64, 1), (90, -1), (99, 1)):
+        w.inputs[3][k] = sign * np.float32(value) * np.float32(1 + 0.01 * k)
+    got, want = _run(w, "mlp_")
+    assert np.array_equal(np.isinf(want).all(1), np.isin(np.arange(n), [5, 64, 99]))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fine = np.isfinite(want)
+    assert np.isfinite(got[fine]).all()
+    rows = fine.all(1)
+    assert parity_stats(got[rows], want[rows])[0] <= 1e-5
