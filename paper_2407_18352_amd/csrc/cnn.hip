@@ -379,7 +379,8 @@ struct MfmaArgs {
     FusedArgs f;
     ConvM c[kCnnFusedMaxLayers];
     const void *image;                   // device: biases and fragments of every layer
-    float limit;                         // of the layers' inputs (see input_limit)
+    float limit, least;                  // of the layers' inputs and the outputs (see split_range)
+    int32_t tiny;                        // a weight loses bits
     int32_t image_bytes, planes_off, planes_bytes;   // LDS: image, then planes
     int32_t pre;                         // the next tile is requested ahead
     int32_t in_rank, out_rank, in_offsets, out_offsets;
@@ -486,10 +487,25 @@ __device__ __forceinline__ floatx4 mma(u32x4 a, u32x4 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// What a lane met in a tile.
+struct Seen {
+    Range hidden;                  // the layers' inputs but the first's
+    uint32_t in2 = 0;              // the first's largest: bits shifted past the sign (infinities and NaN above all)
+    uint32_t low = 0xFFFFFFFFu;    // the least input of any layer but 0: the same bits, less 1 (0 comes last)
+    float out = FLT_MAX;           // the least output
+    __device__ __forceinline__ void add_low(float v) { low = min(low, (__float_as_uint(v) << 1) - 1u); }
+    // bit 0: the matrix form may not serve this tile; bit 1: nor if bit 2 (a
+    // value lost bits) is set as well, in any wave of the block
+    __device__ __forceinline__ uint32_t flags(float limit, float least) const {
+        return (__any(hidden.outside(limit) || in2 >= __float_as_uint(limit) << 1) ? 1u : 0u) | (__any(out < least) ? 2u : 0u) |
+               (__any(low < (__float_as_uint(kLeast) << 1) - 1u) ? 4u : 0u);
+    }
+};
+
 // One layer of the tile: this wave's share of the groups.
 template <bool M16, bool LAST>
 __device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, const TabLds &tab, int wave, int lane, int s, int y0, int x0,
-                                          Range &range) {
+                                          Seen &seen) {
     typedef typename AccOf<M16>::type Acc;
     // columns; chunks per K-step; register quads; column tiles at a time (they
     // share the weights' fragments, and the short 16-row tiles need company)
@@ -594,10 +610,15 @@ __device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, c
                 float v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    v[e] = __builtin_amdgcn_fmed3f(main[u][4 * q + e] + (s0[u][4 * q + e] + s1[u][4 * q + e]), floor, FLT_MAX);
+                    v[e] = main[u][4 * q + e] + (s0[u][4 * q + e] + s1[u][4 * q + e]);
                 if (!LAST) {
-                    range.add(v[0], v[1]);
-                    range.add(v[2], v[3]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = __builtin_amdgcn_fmed3f(v[e], floor, FLT_MAX);
+                        seen.add_low(v[e]);
+                    }
+                    seen.hidden.add(v[0], v[1]);
+                    seen.hidden.add(v[2], v[3]);
                 }
                 const int col = gx[u] * P + px;
                 const int y = y0 - rt + ry[u], x = x0 - rl + col;
@@ -620,7 +641,8 @@ __device__ __forceinline__ void conv_mfma(const MfmaArgs &m, int l, char *lds, c
                                     const uint32_t raw[1] = {tab.out_raw8[c0 + e]};
                                     fix_lds<1>(m.f.out, pt, 15u, raw, idx);
                                 }
-                                stg(tab.out[c0 + e] + idx[0], v[e]);
+                                seen.out = fminf(seen.out, fabsf(v[e]));
+                                stg(tab.out[c0 + e] + idx[0], __builtin_amdgcn_fmed3f(v[e], floor, FLT_MAX));
                             }
                         }
                     }
@@ -671,7 +693,7 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         asm volatile("" : "+v"(z));   // read where it is used, not held in registers
         return *reinterpret_cast<const MfmaArgs *>(reinterpret_cast<const char *>(&args_lds) + z);
     };
-    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave: a value outside the range, a normal input, an input that is not 0
+    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave (see Seen)
     int tile_no = 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto clear = [&](int off, int bytes) {
@@ -807,8 +829,7 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         request(first);
     for (int tile = first; tile < t_end; tile += grid_x) {
         int s, y0, x0;
-        Range range;            // of the layers' inputs but the first's
-        uint32_t in2 = 0;       // the first's: largest magnitude, bits shifted past the sign (infinities and NaN above all)
+        Seen seen;
         {
             const MfmaArgs &m = local();
             locate_tile(m.f, tile, s, y0, x0);
@@ -818,8 +839,10 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
             const int S0 = uni(m.c[0].S), inv0 = uni(m.c[0].inv), sub0 = uni(m.c[0].sub);
             auto put = [&](int at, const float (&v)[4]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    in2 = max(in2, __float_as_uint(v[e]) << 1);
+                for (int e = 0; e < 4; ++e) {
+                    seen.in2 = max(seen.in2, __float_as_uint(v[e]) << 1);
+                    seen.add_low(v[e]);
+                }
                 put4(lds, plane, at, v[0], v[1], v[2], v[3]);
             };
             if (pre_on) {
@@ -854,9 +877,9 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         for (int l = 0; l + 1 < n_layers; ++l) {
             const MfmaArgs &m = local();
             if (uni(m.c[l].m16))
-                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, range);
+                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
             else
-                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, range);
+                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
             __syncthreads();
             if (uni(m.c[l].next_mode) == HPACML_PADMODE_REPLICATE) {
                 replicate_edges(m, m.c[l], lds, y0, x0);
@@ -866,14 +889,12 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         {
             const MfmaArgs &m = local();
             if (uni(m.c[n_layers - 1].m16))
-                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, range);
+                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
             else
-                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, range);
+                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
         }
         // (also the barrier after the last reads of this tile's planes)
-        const uint32_t kLimit2 = __float_as_uint(local().limit) << 1, kTiny2 = __float_as_uint(kTiny) << 1;
-        const uint32_t mine = (__any(range.outside(local().limit) || in2 >= kLimit2) ? 1u : 0u) | (__any(in2 >= kTiny2) ? 2u : 0u) |
-                              (__any(in2 != 0) ? 4u : 0u);
+        const uint32_t mine = seen.flags(local().limit, local().least) | (local().tiny ? 4u : 0u);
         if (lane == 0)
             flags[tile_no & 1][wave] = mine;
         __syncthreads();
@@ -883,8 +904,8 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
             all |= flags[tile_no & 1][w];
         ++tile_no;
         all = __builtin_amdgcn_readfirstlane(all);
-        if ((all & 1u) || (all & 6u) == 4u) {
-            // a value outside the range, or a tile of tiny ones
+        if ((all & 1u) || (all & 6u) == 6u) {
+            // values that the split products can't take
             const MfmaArgs &m = mfma_args();
             run_tile(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
             __syncthreads();
@@ -1688,7 +1709,7 @@ static void mfma_shape(const CnnFusedLayer &y, ConvM *c) {
 bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, CnnFused &f,
                    std::vector<uint8_t> &buf) {
     buf.clear();
-    f.limit = kBig;   // the least of the layers'
+    LayerRows rows[kCnnFusedMaxLayers];
     for (int l = 0; l < f.n_layers; ++l) {
         ConvM c{};
         mfma_shape(f.L[l], &c);
@@ -1698,7 +1719,7 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
         buf.resize(at + 64 + (size_t)c.steps * 3 * kFragBytes, 0);
         for (int o = 0; o < cout; ++o)
             reinterpret_cast<float *>(&buf[at])[o] = b[l][o];
-        float top = 0.f;
+        rows[l] = LayerRows{W[l], b[l], cout, cin * kh * kw};
         for (int st = 0; st < c.steps; ++st)
             for (int lane = 0; lane < 64; ++lane) {
                 const int row = lane % N, ch = st * kc + lane / N;
@@ -1713,7 +1734,6 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                     const float w = W[l][(((size_t)o * cin + i) * kh + ky) * kw + kx];
                     if (!(std::fabs(w) < kBig))
                         return false;
-                    top = std::max(top, std::fabs(w));
                     uint16_t *d = reinterpret_cast<uint16_t *>(&buf[at + 64 + (size_t)st * 3 * kFragBytes]) + lane * 8 + j;
                     d[0] = rne(w);
                     const float r = w - bf16_float(d[0]);
@@ -1721,10 +1741,13 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                     d[kFragBytes] = rne(r - bf16_float(d[kFragBytes / 2]));
                 }
             }
-        f.limit = std::min(f.limit, input_limit(W[l], b[l], cout, cin * kh * kw));
-        if ((top != 0.f && top < kTiny) || f.limit <= 0.f)
-            return false;
     }
+    SplitRange range;
+    if (!split_range(rows, f.n_layers, 1, &range))
+        return false;
+    f.limit = range.limit;
+    f.least = range.least;
+    f.tiny = range.tiny;
     return true;
 }
 
@@ -1865,6 +1888,8 @@ hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 
         a.rw_magic[l] = (uint32_t)(((1u << 24) + a.rw[l] - 1) / a.rw[l]);
     m.image = f.image;
     m.limit = f.limit;
+    m.least = f.least;
+    m.tiny = f.tiny;
     m.in_rank = in.rank;
     m.out_rank = out.rank;
     for (int d = 0; d < out.rank; ++d)

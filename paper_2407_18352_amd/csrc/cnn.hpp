@@ -74,7 +74,9 @@ struct CnnFused {
     int32_t n_layers = 0, c0 = 0, cout_last = 0, circular = 0;
     CnnFusedLayer L[kCnnFusedMaxLayers]{};
     const void *image = nullptr;   // device: the matrix-core form's biases and split weights (null: a weight has no split)
-    float limit = 0;               // ... a layer's inputs from this magnitude on: the tile on the vector ALU
+    // ... a layer's inputs from `limit` on: the tile on the vector ALU; also outputs below `least` where a value (`tiny`: a weight) lost bits
+    float limit = 0, least = 0;
+    int32_t tiny = 0;
     const float *wts = nullptr;    // device: per layer [cout4][ky][kx][cin4*4][4], then bias [cout4*4]
 };
 bool cnn_fused_supported(const CnnPlan &p);
@@ -82,7 +84,7 @@ bool cnn_fused_supported(const CnnPlan &p);
 void cnn_fused_pack(const CnnPlan &p, const float *const *W, const float *const *b, std::vector<float> &buf,
                     CnnFused *out);
 // The same for the matrix-core form (biases, then fragments, layer by layer), and
-// f.limit; false when a weight has no split.
+// f.limit, f.least, f.tiny; false when a weight has no split.
 bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, CnnFused &f,
                    std::vector<uint8_t> &buf);
 // Rows per tile (64 columns) for this stack, or 0 when no tile fits in LDS.

@@ -71,7 +71,7 @@ struct F32Packed {
     int32_t f_out;        // outputs (1..8)
     uint32_t relu;        // bit l: layer l has a ReLU
     int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
-    float limit;          // a layer's inputs from this magnitude on: the tile on the fp32 MFMA
+    float limit, least;   // a layer's inputs from `limit` on, or outputs below `least`: the tile on the fp32 MFMA
     const float *image;   // device: the packed split image
     // the unpadded layers, read for values without a split
     int32_t dims[HPACML_MAX_LAYERS + 1];
@@ -79,7 +79,7 @@ struct F32Packed {
 };
 bool f32_fast_supported(int n_layers, const int32_t *dims, int compute);
 size_t f32_image_floats(int n_layers, const int32_t *dims);
-// Packs the image and sets limit and plain.
+// Packs the image and sets limit, least and plain.
 void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
               F32Packed *pk);
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
@@ -93,14 +93,14 @@ struct F32WPacked {
     int32_t f_out;
     uint32_t relu;        // bit l: layer l has a ReLU
     int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
-    float limit;          // a layer's inputs from this magnitude on: the tile on the fp32 MFMA
+    float limit, least;   // a layer's inputs from `limit` on, or outputs below `least`: the tile on the fp32 MFMA
     const float *image;   // device: the packed split image
     int32_t dims[4];
     const float *W[3];    // the caller's layers, read for values without a split
 };
 bool f32w_supported(int n_layers, const int32_t *dims, int compute);
 size_t f32w_image_floats(int n_layers, const int32_t *dims);
-// Packs the image and sets nb1, nb2, f_out, limit and plain.
+// Packs the image and sets nb1, nb2, f_out, limit, least and plain.
 void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
                F32WPacked *pk);
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

@@ -37,11 +37,11 @@
 // instruction of 4 x 4 blocks.  Biases enter as the initial accumulator.
 //
 // Values of 2^127 and more (infinities among them) have no such split, values
-// large enough for a sum to overflow could turn an infinity into a NaN (see
-// input_limit), and inputs that are all below 2^-100 lose bits: a wave that
-// meets a point of that kind (or such an activation) computes its tile again on
-// the fp32 matrix instruction, with the caller's weights read from global
-// memory; so does every wave of a model with such a weight or layer of weights.
+// large enough for a sum to overflow could turn an infinity into a NaN, and
+// values below 2^-110 lose bits in it, which shows in very small outputs: a wave
+// that meets a point of that kind (see split_range for the bounds) computes its
+// tile again on the fp32 matrix instruction, with the caller's weights read from
+// global memory; so does every wave of a model with a weight that has no split.
 #include "mlp_f32.hpp"
 
 namespace hpacml {
@@ -269,8 +269,6 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
                     range.add(v[j], v[j + 1]);
                 b1[s] = split8(v);
             });
-            if (tiny_inputs(range.top))
-                range.top = kBig;
         });
 
         // ---- hidden layers H -> H
@@ -289,20 +287,6 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         };
         for (int h = 0; h < pk.n_hidden; ++h)
             hidden(h);
-        if (__any(range.outside(pk.limit))) {
-            // this tile again on the fp32 instruction
-            const MapsLds &tab = maps();
-            const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
-            layers_plain<NMB>(pk, lds, lay, [&](int s) __attribute__((always_inline)) {
-                const int f = 2 * s + g;
-                const uint32_t raw[1] = {tab.raw8[f]};
-                int32_t idx[1] = {pt.pe};
-                fix_lds<1>(tab.in, pt, 15u, raw, idx);
-                const float v = ldg(tab.fptr[f] + idx[0]);
-                return f < F ? v : 0.f;
-            }, lane, acc);
-        }
-
         // the next tile's inputs are requested here, where the activations'
         // splits are free; they arrive during the output layer and the other
         // wave's work
@@ -321,10 +305,10 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         //      operand of block `abid` (cbsz 3).  Each half sums its own
         //      features; swapping halves leaves output 2i in lanes 0..31 and
         //      2i + 1 in lanes 32..63.
-        const MapsLds &tab = maps();
-        const OutPoint po(tab, rank_out, out_offsets, valid ? b : n_points - 1);
-        for (int go = 0; go < pk.f_out; go += 4) {
-            const float4 *wq = reinterpret_cast<const float4 *>(lds + lay.out_w(go / 4)) + ln;
+        const float *ob = reinterpret_cast<const float *>(lds + lay.out_b()) + (ln >> 5);
+        float v[2][2];   // outputs 2i + g and 4 + 2i + g
+        auto outputs = [&](int group) __attribute__((always_inline)) {
+            const float4 *wq = reinterpret_cast<const float4 *>(lds + lay.out_w(group)) + ln;
             float a[2 * NMB];
 #pragma unroll
             for (int i = 0; i < NMB / 2; ++i) {
@@ -345,9 +329,34 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
 #pragma unroll
             for (int mb = 1; mb < NMB; ++mb)
                 sum += y[mb];
-            po.store(tab, sum, go, pk.f_out, g, reinterpret_cast<const float *>(lds + lay.out_b()),
-                     pk.relu >> (pk.n_hidden + 1) & 1, valid);
+            join_halves(sum, ob + 4 * group, v[group]);
+        };
+        outputs(0);
+        if (pk.f_out > 4)
+            outputs(1);
+        const float all[4] = {v[0][0], v[0][1], v[1][0], v[1][1]};
+        if (__any(outside(range, pk.limit, pk.least, all, pk.f_out, g))) {
+            // this tile again on the fp32 instruction
+            const MapsLds &tab = maps();
+            const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
+            layers_plain<NMB>(pk, lds, lay, [&](int s) __attribute__((always_inline)) {
+                const int f = 2 * s + g;
+                const uint32_t raw[1] = {tab.raw8[f]};
+                int32_t idx[1] = {pt.pe};
+                fix_lds<1>(tab.in, pt, 15u, raw, idx);
+                const float v = ldg(tab.fptr[f] + idx[0]);
+                return f < F ? v : 0.f;
+            }, lane, acc);
+            outputs(0);
+            if (pk.f_out > 4)
+                outputs(1);
         }
+        const MapsLds &tab = maps();
+        const OutPoint po(tab, rank_out, out_offsets, valid ? b : n_points - 1);
+        const bool orelu = pk.relu >> (pk.n_hidden + 1) & 1;
+        po.store(tab, v[0][0], v[0][1], 0, pk.f_out, g, orelu, valid);
+        if (pk.f_out > 4)
+            po.store(tab, v[1][0], v[1][1], 4, pk.f_out, g, orelu, valid);
     }
 }
 
@@ -451,12 +460,14 @@ void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const fl
                 }
     for (int go = 0; go < Fout; ++go)
         img[sl.out_b() / 4 + go] = b[n_layers - 1][go];
-    // the least of the layers' limits, which takes one running maximum in the
-    // kernel (the output layer is on the fp32 instruction)
-    pk->limit = kBig;
+    // (the output layer is on the fp32 instruction)
+    LayerRows rows[HPACML_MAX_LAYERS];
     for (int l = 0; l + 1 < n_layers; ++l)
-        pk->limit = std::min(pk->limit, input_limit(W[l], b[l], dims[l + 1], dims[l]));
-    pk->plain = !fine || pk->limit <= 0.f;
+        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
+    SplitRange range;
+    pk->plain = !split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range) || !fine;
+    pk->limit = range.limit;
+    pk->least = range.least;
 }
 
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

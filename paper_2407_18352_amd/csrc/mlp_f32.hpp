@@ -29,7 +29,7 @@ constexpr int kSchedAluOnly = 0x2 | 0x4 | 0x400;
 constexpr int kFragBytes = 1024;        // one A operand: 64 lanes x 8 bf16
 constexpr int kLdsMax = 160 * 1024;     // LDS of a CU
 constexpr float kBig = 0x1p127f;        // this and more has no three-way split
-constexpr float kTiny = 0x1p-100f;      // below it the lo part loses bits
+constexpr float kLeast = 0x1p-110f;     // below it the lo part loses bits (bf16 numbers end at 2^-133)
 
 // What a block keeps of the two maps in LDS, ahead of the split image: the
 // feature tables, read with a lane's own feature number, and the 32-bit
@@ -172,14 +172,14 @@ __device__ __forceinline__ float act_floor(bool relu) { return relu ? 0.f : -FLT
 struct Range {
     float top = 0.f;   // the largest (a NaN is passed over)
     __device__ __forceinline__ void add(float a, float b) { top = max_abs(a, b, top); }
-    // Whether a layer could leave the range (limit: see input_limit).
+    // Whether a sum could overflow (limit: see split_range).
     __device__ __forceinline__ bool outside(float limit) const { return top >= limit; }
 };
 
 // Activation as one v_med3_f32(x, floor, FLT_MAX), without a branch, so that it
 // can be scheduled beside matrix instructions; the magnitudes join `range`.
 // Only a NaN among the inputs makes a NaN here (no sum overflows, see
-// input_limit).  It becomes the floor (v_med3_f32 returns the least of the other
+// split_range).  It becomes the floor (v_med3_f32 returns the least of the other
 // two): 0 under ReLU, and the -FLT_MAX of an identity layer, like any
 // magnitude of 2^127 and more, sends the tile to the fp32 instruction.
 template <int N>
@@ -280,17 +280,33 @@ __device__ __forceinline__ void gather_inputs(const MapsLds &tab, int rank, int3
     });
 }
 
-// Whether some point of the wave has only inputs that are tiny, and not all zero (top:
-// the largest magnitude of the lane's inputs; the other half has the rest).
-__device__ __forceinline__ bool tiny_inputs(float top) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(top), __float_as_uint(top), false, false);
-    const float m = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    return m > 0.f && m < kTiny;
+// Four outputs: each lane half holds its own features' sums of outputs go .. go +
+// 3; swapping halves leaves output go + 2i in lanes 0..31 and go + 2i + 1 in lanes
+// 32..63.  (bias: kFoutMax of them)
+__device__ __forceinline__ void join_halves(floatx4 sum, const float *bias, float (&v)[2]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[2 * i]), __float_as_uint(sum[2 * i + 1]),
+                                                         false, false);
+        v[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]) + bias[2 * i];
+    }
 }
 
-// A point of the `from` map, and the store of four outputs: each lane half
-// holds its own features' sums of outputs go .. go + 3; swapping halves leaves
-// output go + 2i in lanes 0..31 and go + 2i + 1 in lanes 32..63.
+// Whether the split products may not serve this lane's point: a value too large
+// for them, or an output so small that the bits which tiny values lose would
+// show in it (see split_range).  All the outputs of a point whose inputs and
+// activations are 0 are exact.
+__device__ __forceinline__ bool outside(const Range &range, float limit, float least, const float (&v)[4], int f_out, int g) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(range.top), __float_as_uint(range.top), false, false);
+    const float top = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    float low = FLT_MAX;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)   // output 2i + g
+        low = 2 * i + g < f_out ? fminf(low, fabsf(v[i])) : low;
+    return range.outside(limit) || (top > 0.f && low < least);
+}
+
+// A point of the `from` map, and the store of outputs go + g and go + 2 + g.
 struct OutPoint {
     Pt32 p;
     uint32_t edge;
@@ -298,16 +314,13 @@ struct OutPoint {
         p = locate_lds(tab.out, rank, b);
         edge = offsets ? edge_lds(tab.out, rank, p) : 0u;
     }
-    __device__ __forceinline__ void store(const MapsLds &tab, floatx4 sum, int go, int f_out, int g, const float *bias,
-                                          bool relu, bool valid) const {
+    __device__ __forceinline__ void store(const MapsLds &tab, float v0, float v1, int go, int f_out, int g, bool relu,
+                                          bool valid) const {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int o = go + 2 * i + g;
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[2 * i]), __float_as_uint(sum[2 * i + 1]),
-                                                             false, false);
-            float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
             if (o < f_out) {
-                v += bias[o];
+                float v = i ? v1 : v0;
                 if (relu)
                     v = fmaxf(v, 0.f);
                 int32_t idx[1] = {p.pe};
@@ -322,23 +335,72 @@ struct OutPoint {
     }
 };
 
-// The magnitude from which on a layer's inputs go to the fp32 instruction; 0 when
-// all have to.  Below it no sum overflows: with the largest row sum of |w| and
-// inputs below the limit the products of a row, and the bias, come to 2^126
-// each, so that hi hi (at most 1 + 2^-6 times as large) and the sums of small
-// products stay finite.  Otherwise an infinite sum of hi hi could meet small
-// products that are infinite with the other sign, where the fp32 sum is infinite.
-inline float input_limit(const float *W, const float *b, int N, int K) {
+// The values that a stack of layers can leave to the split products; false when
+// every tile has to take the fp32 path.  `after`: the largest row sum of |w| of
+// the layer behind them (1: none).
+//
+// limit: no sum overflows for inputs (of any layer) below it.  With the largest
+// row sum of |w| the products of a row, and the bias, come to 2^126 each, so
+// that hi hi (at most 1 + 2^-6 times as large) and the sums of small products
+// stay finite.  Otherwise an infinite sum of hi hi could meet small products that
+// are infinite with the other sign, where the fp32 sum is infinite.
+//
+// least: a value below 2^-110 loses what its split has below 2^-133, at most
+// 2^-134.  Through a layer that makes row sum x 2^-134, and 2^-134 K x the largest
+// input (kept below 2^40 then) where a weight is that small; the layers behind
+// multiply it by their row sums at most.  Outputs of 2^26 times the whole and
+// more keep their 24 bits.
+struct LayerRows {
+    const float *W, *b;   // [N][K], [N]
+    int N, K;
+};
+struct SplitRange {
+    float limit, least;
+    bool tiny;   // a weight loses bits
+};
+inline bool split_range(const LayerRows *layers, int n, double after, SplitRange *r) {
+    double limit = kBig, lost = 0;
+    *r = SplitRange{};
+    for (int l = n - 1; l >= 0; --l) {
+        const LayerRows &y = layers[l];
+        double worst = 0;
+        bool tiny = false;
+        for (int o = 0; o < y.N; ++o) {
+            double sum[4] = {};
+            float low = kBig;   // the least but 0
+            const float *w = y.W + (size_t)o * y.K;
+            for (int k = 0; k < y.K; ++k) {
+                const float a = std::fabs(w[k]);
+                sum[k % 4] += a;
+                low = std::min(low, a > 0.f ? a : kBig);
+            }
+            const double all = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            if (!(all < HUGE_VAL) || !(std::fabs(y.b[o]) < 0.5f * kBig))
+                return false;
+            worst = std::max(worst, all);
+            tiny = tiny || low < kLeast;
+        }
+        if (worst > 0.5)
+            limit = std::min(limit, 0.5 * kBig / worst * (1 - 0x1p-20));
+        lost += after * (worst + (tiny ? 0x1p40 * y.K : 0));
+        after *= worst;
+        r->tiny = r->tiny || tiny;
+    }
+    if (r->tiny)
+        limit = std::min(limit, 0x1p40);
+    r->limit = (float)limit;
+    r->least = (float)(0x1p-108 * lost);   // 2^26 x 2^-134
+    return lost < 0x1p200;
+}
+inline double largest_row_sum(const float *W, int N, int K) {
     double worst = 0;
     for (int o = 0; o < N; ++o) {
         double sum = 0;
         for (int k = 0; k < K; ++k)
             sum += std::fabs((double)W[(size_t)o * K + k]);
-        if (!(sum < HUGE_VAL) || !(std::fabs(b[o]) < 0.5f * kBig))
-            return 0.f;
         worst = std::max(worst, sum);
     }
-    return worst <= 0.5 ? kBig : (float)(0.5 * kBig / worst * (1 - 0x1p-20));
+    return worst;
 }
 
 // Host side of the split: rounded to nearest even, as the device's conversion
@@ -352,7 +414,7 @@ inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t
 // One layer's A fragments: K-step s, m-block mb, lane l, element j is weight
 // [32 mb + l % 32][feature(s, l / 32, j)] (zero past N rows and K columns), its
 // parts at img + hm(s, mb) (hi, then mid) and img + lo(s, mb).  False when a
-// weight has no split, or the largest is so small that splits lose bits.
+// weight has no split.
 template <typename Hm, typename Lo, typename Feature>
 inline bool put_layer(char *img, const float *W, int N, int K, int steps, int blocks, Hm &&hm, Lo &&lo,
                       Feature &&feature) {
@@ -393,8 +455,7 @@ inline bool put_layer(char *img, const float *W, int N, int K, int steps, int bl
             }
         }
     }
-    const float largest = __builtin_bit_cast(float, top);
-    return top == 0 || (largest >= 0x1p-100f && largest < kBig);
+    return top < __builtin_bit_cast(uint32_t, kBig);
 }
 
 }  // namespace

@@ -114,8 +114,6 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                 range.add(v[j], v[j + 1]);
             b1[s] = split8(v);
         });
-        if (tiny_inputs(range.top))
-            range.top = kBig;
         if (tile + order.step < order.end) {
             gather_inputs<KS1>(maps(), rank_in, n_points, windowed, pairs, (tile + order.step) * 32 + col, g, xn);
         } else {
@@ -266,7 +264,16 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                     out_add(finish(m2[i], s2[i], 1), p + i);
             }
         }
-        if (__any(range.outside(pk.limit))) {
+        const float *ob = reinterpret_cast<const float *>(lds + lay.out_b()) + (ln >> 5);
+        float v[2][2] = {};   // outputs 2i + g and 4 + 2i + g
+        auto outputs = [&]() __attribute__((always_inline)) {
+            join_halves(y[0], ob, v[0]);
+            if (pk.f_out > 4)
+                join_halves(y[1], ob + 4, v[1]);
+        };
+        outputs();
+        const float all[4] = {v[0][0], v[0][1], v[1][0], v[1][1]};
+        if (__any(outside(range, pk.limit, pk.least, all, pk.f_out, g))) {
             // this tile again on the fp32 instruction, with the caller's weights in global memory (rows and columns past
             // them are zero)
             const MapsLds &tab = maps();
@@ -313,14 +320,14 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                     out_add(acc, p);
                 }
             }
+            outputs();
         }
         const MapsLds &tab = maps();
         const OutPoint po(tab, rank_out, out_offsets, valid ? b : n_points - 1);
         const bool orelu = pk.relu >> (G ? 2 : 1) & 1;
-        const float *ob = reinterpret_cast<const float *>(lds + lay.out_b());
-        po.store(tab, y[0], 0, pk.f_out, g, ob, orelu, valid);
+        po.store(tab, v[0][0], v[0][1], 0, pk.f_out, g, orelu, valid);
         if (pk.f_out > 4)
-            po.store(tab, y[1], 4, pk.f_out, g, ob, orelu, valid);
+            po.store(tab, v[1][0], v[1][1], 4, pk.f_out, g, orelu, valid);
     }
 }
 
@@ -410,12 +417,14 @@ void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
         }
     for (int o = 0; o < O; ++o)
         reinterpret_cast<float *>(img + lay.out_b())[o] = b[n_layers - 1][o];
-    // the least of the layers' limits, which takes one running maximum in the
-    // kernel (the output layer is on the fp32 instruction)
-    pk->limit = kBig;
+    // (the output layer is on the fp32 instruction)
+    LayerRows rows[HPACML_MAX_LAYERS];
     for (int l = 0; l + 1 < n_layers; ++l)
-        pk->limit = std::min(pk->limit, input_limit(W[l], b[l], dims[l + 1], dims[l]));
-    pk->plain = !fine || pk->limit <= 0.f;
+        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
+    SplitRange range;
+    pk->plain = !split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range) || !fine;
+    pk->limit = range.limit;
+    pk->least = range.least;
 }
 
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

@@ -125,3 +125,54 @@ def test_overflow_inside_a_layer(layers, factor, value):
         rows = np.isfinite(want).all(1)
         assert np.isfinite(got[rows]).all()
         assert parity_stats(got[rows], want[rows])[0] <= 1e-5
+
+
+def _fp32_error(w, got, want):
+    """The worst error, in parts of the same sums without signs, over what the
+    vector ALU's sums give: a rounding of one part in 2^24 per product,
+    independent of each other."""
+    layers = [dict(ly, W=np.abs(ly["W"]), b=np.abs(ly["b"])) for ly in w.model["layers"]]
+    size = [np.zeros_like(a) for a in w.outputs]
+    oracle.infer(w.in_spec, [np.abs(a) for a in w.inputs], w.out_spec, size, dict(w.model, layers=layers))
+    size = np.stack([a.reshape(-1) for a in size], 1).astype(np.float64)
+    terms = sum(ly["W"][0].size for ly in layers)
+    return np.max(np.abs(got.astype(np.float64) - want) / size) / (2.0 ** -24 * np.sqrt(terms))
+
+
+@pytest.mark.parametrize("exponent", [-112, -118, -124])
+def test_tiny_hidden_values(exponent):
+    """Inputs and first-layer weights of half the exponent each, the second
+    layer's weights bring the sums back."""
+    layers = [(8, 3, 3), (4, 3, 3)]
+    w = _workload(4, layers, "circular", 1, 40, 70, seed=6)
+    half = exponent // 2
+    for a in w.inputs:
+        a[:] = (np.abs(a) + 0.5).astype(np.float32) * np.float32(2.0 ** half)
+    for ly in w.model["layers"]:
+        ly["b"][:] = 0
+    w.model["layers"][0]["W"] *= np.float32(2.0 ** (exponent - half))
+    w.model["layers"][1]["W"] *= np.float32(2.0 ** -exponent)
+    got, want = _both(w)
+    assert _fp32_error(w, got, want) <= 4
+
+
+@pytest.mark.parametrize("tiny", ["input", "weight", "most pixels"])
+def test_tiny_factors_beside_normal_ones(tiny):
+    """A channel of 2^-122 with weights that make it count, the other way round,
+    and an image of 2^-122 but for one pixel."""
+    layers = [(8, 3, 3), (4, 3, 3)]
+    w = _workload(4, layers, "circular", 1, 40, 70, seed=7)
+    L = w.model["layers"]
+    if tiny == "most pixels":
+        for ly in L:
+            ly["b"][:] = 0
+        L[1]["W"] *= np.float32(2.0 ** 122)
+        for a in w.inputs:
+            a[:] = (np.abs(a) + 0.5).astype(np.float32) * np.float32(2.0 ** -122)
+        w.inputs[0][0, 20, 30] = 1.0
+    else:
+        by = np.float32(2.0 ** (-122 if tiny == "input" else 122))
+        w.inputs[2] *= by
+        L[0]["W"][:, 2] /= by
+    got, want = _both(w)
+    assert _fp32_error(w, got, want) <= 4

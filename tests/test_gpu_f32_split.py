@@ -162,3 +162,43 @@ def test_overflow_inside_a_layer(dims, factor, value):
     assert np.isfinite(got[fine]).all()
     rows = fine.all(1)
     assert parity_stats(got[rows], want[rows])[0] <= 1e-5
+
+
+def _fp32_error(w, got, want):
+    """The worst error, in parts of the same sums without signs, over what the
+    fp32 instruction's sums give: a rounding of one part in 2^24 per product,
+    independent of each other."""
+    m = dict(w.model, W=[np.abs(x) for x in w.model["W"]], b=[np.abs(x) for x in w.model["b"]])
+    size = oracle.infer_rows(w.in_spec, [np.abs(x) for x in w.inputs], m).astype(np.float64)
+    return np.max(np.abs(got.astype(np.float64) - want) / size) / (2.0 ** -24 * np.sqrt(sum(w.dims[:-1])))
+
+
+@pytest.mark.parametrize("exponent", [-105, -112, -118, -124])
+@pytest.mark.parametrize("dims", [[7, 64, 64, 2], [7, 64, 64, 64, 1], [12, 128, 128, 1], [12, 200, 40, 1]])
+def test_tiny_hidden_values(dims, exponent):
+    """First-layer weights and inputs of half the exponent each make hidden
+    values of 2^exponent, the next layer's weights bring them back."""
+    n = 300
+    g = np.random.default_rng(-exponent)
+    half = exponent // 2
+    w = _workload(dims, n, [(g.uniform(0.5, 1, n) * 2.0 ** half).astype(np.float32) for _ in range(dims[0])])
+    w.model["b"] = [np.zeros_like(b) for b in w.model["b"]]
+    w.model["W"][0] = (w.model["W"][0] * np.float32(2.0 ** (exponent - half))).astype(np.float32)
+    w.model["W"][1] = (w.model["W"][1] * np.float32(2.0 ** -exponent)).astype(np.float32)
+    got, want = _run(w, "mlp_")
+    assert _fp32_error(w, got, want) <= 4
+
+
+@pytest.mark.parametrize("tiny", ["input", "weight"])
+@pytest.mark.parametrize("dims", [[7, 64, 64, 2], [12, 128, 128, 1], [12, 200, 40, 1], [12, 300, 1]])
+def test_one_tiny_factor_beside_normal_ones(dims, tiny):
+    """A feature of 2^-122 with first-layer weights that make it count as much as
+    the others, or the other way round."""
+    n = 300
+    g = np.random.default_rng(len(dims))
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    by = np.float32(2.0 ** (-122 if tiny == "input" else 122))
+    w.inputs[2] = (w.inputs[2] * by).astype(np.float32)
+    w.model["W"][0][:, 2] = (w.model["W"][0][:, 2] / by).astype(np.float32)
+    got, want = _run(w, "mlp_")
+    assert _fp32_error(w, got, want) <= 4
