@@ -98,7 +98,7 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
         for (int mb = 0; mb < NMB; ++mb)
             acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, mb, 2 * s + g), x, acc[mb], 0, 0, 0);
     }
-    activate_plain<NMB>(acc, pk.relu & 1);
+    activate_plain<NMB>(acc, pk.relu & 1, 0, g, pk.dims[1]);
     for (int h = 0; h < pk.n_hidden; ++h) {
         floatx16 hin[NMB];
 #pragma unroll
@@ -119,7 +119,7 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
             for (int i = 0; i + 1 < NMB; ++i)
                 hin[i] = hin[i + 1];
         }
-        activate_plain<NMB>(acc, pk.relu >> (h + 1) & 1);
+        activate_plain<NMB>(acc, pk.relu >> (h + 1) & 1, 0, g, pk.dims[h + 2]);
     }
 }
 

@@ -194,16 +194,19 @@ __device__ __forceinline__ void activate(floatx16 *acc, float floor, Range &rang
         }
 }
 
-// Activation of the fp32 path: ReLU (a NaN gives 0) or nothing.
+// Activation of the fp32 path: ReLU (a NaN gives 0) or nothing; m-blocks mb0 on of
+// a layer of `width` neurons.  Those past it are 0 whatever the inputs (an
+// infinite input times their weights of 0 is a NaN).
 template <int N>
-__device__ __forceinline__ void activate_plain(floatx16 *acc, bool relu) {
-    if (relu) {
+__device__ __forceinline__ void activate_plain(floatx16 *acc, bool relu, int mb0, int g, int width) {
+    asm volatile("" : "+v"(g));   // (compared here, not ahead of the tiles)
 #pragma unroll
-        for (int mb = 0; mb < N; ++mb)
+    for (int mb = 0; mb < N; ++mb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[mb][r] = relu_mfma(acc[mb][r]);
-    }
+        for (int r = 0; r < 16; ++r) {
+            const float v = relu ? relu_mfma(acc[mb][r]) : acc[mb][r];
+            acc[mb][r] = crow(mb0 + mb, r, g) < width ? v : 0.f;
+        }
 }
 
 // Which tiles of 32 points a wave takes: first, first + step, ... below end.

@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                     const float x = ldg(tab.fptr[f] + idx[0]);
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, 32 * j, f), f < F ? x : 0.f, acc, 0, 0, 0);
                 }
-                activate_plain<1>(&acc, pk.relu & 1);
+                activate_plain<1>(&acc, pk.relu & 1, j, g, pk.dims[1]);
                 return acc;
             };
             y[0] = y[1] = floatx4{};
@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                         for (int r = 0; r < 16; ++r)
                             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(1, 32 * p, crow(j, r, g)), x[r], acc, 0, 0, 0);
                     }
-                    activate_plain<1>(&acc, pk.relu >> 1 & 1);
+                    activate_plain<1>(&acc, pk.relu >> 1 & 1, p, g, pk.dims[2]);
                     out_add(acc, p);
                 }
             }

@@ -202,3 +202,22 @@ def test_one_tiny_factor_beside_normal_ones(dims, tiny):
     w.model["W"][0][:, 2] = (w.model["W"][0][:, 2] / by).astype(np.float32)
     got, want = _run(w, "mlp_")
     assert _fp32_error(w, got, want) <= 4
+
+
+@pytest.mark.parametrize("dims", [[9, 200, 50, 1], [5, 300, 6], [9, 5, 300, 2], [20, 129, 65, 3], [5, 50, 50, 1], [9, 100, 70, 90, 3]])
+def test_infinities_through_identity_layers(dims):
+    """An infinite feature whose weights are all positive makes every neuron of
+    an identity layer +inf or -inf: outputs infinite, and none of them NaN from
+    neurons that the kernel pads its blocks with."""
+    n = 201
+    g = np.random.default_rng(dims[0] + 1)
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    w.model["act"] = [wl.IDENTITY] * (len(dims) - 1)
+    w.model["W"] = [np.abs(x) + np.float32(1e-3) for x in w.model["W"]]
+    for k, v in ((3, np.inf), (40, -np.inf), (130, np.inf), (200, -np.inf)):
+        w.inputs[k % dims[0]][k] = v
+    got, want = _run(w, "mlp_")
+    assert np.isinf(want[[3, 40, 130, 200]]).all() and np.isfinite(want).all(1).sum() == n - 4
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fine = np.isfinite(want).all(1)
+    assert parity_stats(got[fine], want[fine])[0] <= 1e-5
