@@ -610,8 +610,8 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
         }
 
         if (f32_fast_supported(n_layers, fd, compute)) {
-            std::vector<float> img(f32_image_floats(n_layers, fd));
-            f32_pack(n_layers, fd, fW, fb, img.data(), &m->f32);
+            std::vector<float> img;
+            f32_pack(n_layers, fd, fW, fb, img, &m->f32);
             s = upload(&m->f32_img, img.data(), img.size());
             if (s != HPACML_OK) {
                 hpacml_model_destroy(m);
@@ -627,8 +627,6 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
             m->f32.image = m->f32_img;
             for (int l = 0; l <= n_layers; ++l)
                 m->f32.dims[l] = dims[l];
-            for (int l = 0; l < n_layers; ++l)
-                m->f32.W[l] = m->gen.W[l];
             m->variant = Variant::F32;
             m->fast_name = f32_variant_name(m->f32);
         } else if (bf16r_supported(n_layers, fd, act, compute)) {
@@ -662,18 +660,16 @@ hpacml_status hpacml_model_create(int32_t n_layers, const int32_t *dims, const f
             m->fast_name = bf16_variant_name(m->bf16);
         }
         if (m->variant == Variant::Generic && f32w_supported(n_layers, dims, compute)) {
-            std::vector<float> img(f32w_image_floats(n_layers, dims));
-            f32w_pack(n_layers, dims, W, b, img.data(), &m->f32w);
+            std::vector<float> img;
+            f32w_pack(n_layers, dims, W, b, img, &m->f32w);
             s = upload(&m->f32_img, img.data(), img.size());
             if (s != HPACML_OK) {
                 hpacml_model_destroy(m);
                 return s;
             }
             m->f32w.relu = 0;
-            for (int l = 0; l < n_layers; ++l) {
+            for (int l = 0; l < n_layers; ++l)
                 m->f32w.relu |= act[l] == HPACML_ACT_RELU ? 1u << l : 0u;
-                m->f32w.W[l] = m->gen.W[l];
-            }
             for (int l = 0; l <= n_layers; ++l)
                 m->f32w.dims[l] = dims[l];
             m->f32w.image = m->f32_img;

@@ -1710,6 +1710,14 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                    std::vector<uint8_t> &buf) {
     buf.clear();
     LayerRows rows[kCnnFusedMaxLayers];
+    for (int l = 0; l < f.n_layers; ++l)
+        rows[l] = LayerRows{W[l], b[l], p.shape[l + 1].c, p.shape[l].c * f.L[l].kh * f.L[l].kw};
+    SplitRange range;
+    if (!split_range(rows, f.n_layers, 1, &range))
+        return false;
+    f.limit = range.limit;
+    f.least = range.least;
+    f.tiny = range.tiny;
     for (int l = 0; l < f.n_layers; ++l) {
         ConvM c{};
         mfma_shape(f.L[l], &c);
@@ -1719,7 +1727,6 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
         buf.resize(at + 64 + (size_t)c.steps * 3 * kFragBytes, 0);
         for (int o = 0; o < cout; ++o)
             reinterpret_cast<float *>(&buf[at])[o] = b[l][o];
-        rows[l] = LayerRows{W[l], b[l], cout, cin * kh * kw};
         for (int st = 0; st < c.steps; ++st)
             for (int lane = 0; lane < 64; ++lane) {
                 const int row = lane % N, ch = st * kc + lane / N;
@@ -1732,8 +1739,6 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                     if (kx < 0 || kx >= kw || i >= cin)
                         continue;
                     const float w = W[l][(((size_t)o * cin + i) * kh + ky) * kw + kx];
-                    if (!(std::fabs(w) < kBig))
-                        return false;
                     uint16_t *d = reinterpret_cast<uint16_t *>(&buf[at + 64 + (size_t)st * 3 * kFragBytes]) + lane * 8 + j;
                     d[0] = rne(w);
                     const float r = w - bf16_float(d[0]);
@@ -1742,12 +1747,6 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                 }
             }
     }
-    SplitRange range;
-    if (!split_range(rows, f.n_layers, 1, &range))
-        return false;
-    f.limit = range.limit;
-    f.least = range.least;
-    f.tiny = range.tiny;
     return true;
 }
 

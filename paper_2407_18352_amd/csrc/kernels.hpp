@@ -70,17 +70,14 @@ struct F32Packed {
     int32_t ks1;          // pairs of input features (ceil(F_in / 2))
     int32_t f_out;        // outputs (1..8)
     uint32_t relu;        // bit l: layer l has a ReLU
-    int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
+    int32_t weights;      // WeightForm; kPlainWeights (a weight has no split): every tile on the fp32 MFMA
     float limit, least;   // a layer's inputs from `limit` on, or outputs below `least`: the tile on the fp32 MFMA
-    const float *image;   // device: the packed split image
-    // the unpadded layers, read for values without a split
-    int32_t dims[HPACML_MAX_LAYERS + 1];
-    const float *W[HPACML_MAX_LAYERS];
+    const float *image;   // device: the packed image
+    int32_t dims[HPACML_MAX_LAYERS + 1];   // the unpadded layers
 };
 bool f32_fast_supported(int n_layers, const int32_t *dims, int compute);
-size_t f32_image_floats(int n_layers, const int32_t *dims);
-// Packs the image and sets limit, least and plain.
-void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
+// Packs the image and sets limit, least and weights.
+void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, std::vector<float> &image,
               F32Packed *pk);
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                           const F32Packed &pk, hipStream_t stream);
@@ -92,16 +89,14 @@ struct F32WPacked {
     int32_t nb1, nb2;     // blocks of 32 neurons of the hidden layers (nb2 0: one hidden layer)
     int32_t f_out;
     uint32_t relu;        // bit l: layer l has a ReLU
-    int32_t plain;        // a weight has no split: every tile on the fp32 MFMA
+    int32_t weights;      // WeightForm; kPlainWeights (a weight has no split): every tile on the fp32 MFMA
     float limit, least;   // a layer's inputs from `limit` on, or outputs below `least`: the tile on the fp32 MFMA
-    const float *image;   // device: the packed split image
+    const float *image;   // device: the packed image
     int32_t dims[4];
-    const float *W[3];    // the caller's layers, read for values without a split
 };
 bool f32w_supported(int n_layers, const int32_t *dims, int compute);
-size_t f32w_image_floats(int n_layers, const int32_t *dims);
-// Packs the image and sets nb1, nb2, f_out, limit, least and plain.
-void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
+// Packs the image and sets nb1, nb2, f_out, limit, least and weights.
+void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, std::vector<float> &image,
                F32WPacked *pk);
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                            const F32WPacked &pk, hipStream_t stream);

@@ -40,8 +40,11 @@
 // large enough for a sum to overflow could turn an infinity into a NaN, and
 // values below 2^-110 lose bits in it, which shows in very small outputs: a wave
 // that meets a point of that kind (see split_range for the bounds) computes its
-// tile again on the fp32 matrix instruction, with the caller's weights read from
-// global memory; so does every wave of a model with a weight that has no split.
+// tile on the fp32 matrix instruction, with the weights put together from their
+// parts (see WeightForm).  So does every wave of a model with a weight that has no
+// split.  Measured, 9-128-128-128-1 on 1,048,576 points: 316 us; with an infinite
+// input in every tile 873, with such a weight 668 (weights from global memory: 2073
+// both); 5-64-64-1: 61, 160 and 132 (249 both).
 #include "mlp_f32.hpp"
 
 namespace hpacml {
@@ -71,33 +74,39 @@ struct SplitLayout {
     __host__ __device__ int l1_lo() const { return hidden(n_hidden); }
     __host__ __device__ int hidden_lo(int h) const { return l1_lo() + (ks + h * 2 * nmb) * nmb * kFragBytes; }
     __host__ __device__ int total() const { return hidden_lo(n_hidden); }
+    // kPlainBehind: fp32 weights for the fragment pair at byte f lie at f + behind()
+    __host__ __device__ int behind() const { return total() - l1(); }
     // what a block keeps in LDS
     __host__ __device__ int image_lds(bool lo_global) const { return lo_global ? l1_lo() : total(); }
     __host__ __device__ int lds(bool lo_global) const { return image_lds(lo_global) + (int)sizeof(MapsLds); }
 };
 
-// Every layer but the output on the fp32 matrix instruction, with the
-// caller's weights in global memory ([out][in], unpadded: rows and columns
-// past them are zero) and the biases in LDS; input(s) = feature 2s + g of the
-// lane's point.
-template <int NMB, typename In>
-__device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *lds, const SplitLayout &lay, In &&input,
-                                             int lane, floatx16 *acc) {
-    const int g = lane >> 5;
-    auto weight = [&](int l, int mb, int k) __attribute__((always_inline)) {
-        const int row = 32 * mb + (lane & 31), n_in = pk.dims[l];
-        const bool in = row < pk.dims[l + 1] && k < n_in;
-        const float w = ldg(pk.W[l] + (in ? row * n_in + k : 0));
-        return in ? w : 0.f;
+// Every layer but the output on the fp32 matrix instruction; x: the point's inputs
+// (0 past the last); fl, gl: this lane's part of the image in LDS and in global memory.
+template <int NMB, int KS1, bool LOG>
+__device__ __forceinline__ void layers_plain(const F32Packed &pk, const float (&x)[8 * KS1], const u32x4 *fl,
+                                             const u32x4 *gl, const char *lds, const SplitLayout &lay, int g, floatx16 *acc) {
+    const int form = pk.weights, behind = lay.behind() / 16;
+    auto step = [&](int hm, int lo, const float *xs) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) {
+            u32x4 f[3];
+            if (form == kPlainBehind) {
+                f[0] = gl[behind + hm / 16 + mb * 128];
+                f[1] = gl[behind + hm / 16 + mb * 128 + 64];
+            } else {
+                f[0] = fl[hm / 16 + mb * 128];
+                f[1] = fl[hm / 16 + mb * 128 + 64];
+            }
+            f[2] = (LOG ? gl : fl)[lo / 16 + mb * 64];
+            acc[mb] = mfma_plain(f[0], f[1], f[2], form, xs, acc[mb]);
+            __builtin_amdgcn_sched_barrier(0);   // (few registers are left)
+        }
     };
     load_bias<NMB>(reinterpret_cast<const float *>(lds + lay.l1_bias()), g, acc);
-#pragma unroll 1
-    for (int s = 0; s < pk.ks1; ++s) {
-        const float x = input(s);
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb)
-            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, mb, 2 * s + g), x, acc[mb], 0, 0, 0);
-    }
+    for (int s = 0; s < KS1; ++s)
+        step(lay.l1() + s * NMB * 2 * kFragBytes, lay.l1_lo() + s * NMB * kFragBytes, x + 8 * s);
     activate_plain<NMB>(acc, pk.relu & 1, 0, g, pk.dims[1]);
     for (int h = 0; h < pk.n_hidden; ++h) {
         floatx16 hin[NMB];
@@ -108,12 +117,12 @@ __device__ __forceinline__ void layers_plain(const F32Packed &pk, const char *ld
 #pragma unroll 1
         for (int q = 0; q < NMB; ++q) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                // register r of m-block q holds feature crow(q, r, g)
+            for (int t = 0; t < 2; ++t) {
+                float xs[8];
 #pragma unroll
-                for (int mb = 0; mb < NMB; ++mb)
-                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(h + 1, mb, crow(q, r, g)), hin[0][r], acc[mb],
-                                                                   0, 0, 0);
+                for (int j = 0; j < 8; ++j)
+                    xs[j] = hin[0][8 * t + j];
+                step(lay.hidden(h) + (2 * q + t) * NMB * 2 * kFragBytes, lay.hidden_lo(h) + (2 * q + t) * NMB * kFragBytes, xs);
             }
 #pragma unroll
             for (int i = 0; i + 1 < NMB; ++i)
@@ -174,8 +183,7 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         int ln = lane;
         asm volatile("" : "+v"(ln));   // nothing read from LDS is held from one tile to the next
         Range range;   // of the inputs of every layer
-        if (pk.plain)
-            range.top = kBig;
+        range.top = pk.weights == kPlainWeights ? kBig : 0.f;
         Split b1[KS1];
         floatx16 acc[NMB];
         const u32x4 *fl = lds4 + ln;                                        // this lane's part of the LDS fragments
@@ -256,7 +264,8 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
             });
         };
         // ---- first layer
-        layer(b1, std::integral_constant<int, KS1>{}, lay.l1(), lay.l1_lo(), lay.l1_bias(), pk.relu & 1, [&]() {
+        if (pk.weights != kPlainWeights)
+            layer(b1, std::integral_constant<int, KS1>{}, lay.l1(), lay.l1_lo(), lay.l1_bias(), pk.relu & 1, [&]() {
             static_for<0, KS1>([&](auto s) __attribute__((always_inline)) {
                 floatx8 v;
 #pragma unroll
@@ -285,7 +294,8 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
                       });
                   });
         };
-        for (int h = 0; h < pk.n_hidden; ++h)
+        const int n_split = __any(range.outside(pk.limit)) ? 0 : pk.n_hidden;   // (the fp32 path follows)
+        for (int h = 0; h < n_split; ++h)
             hidden(h);
         // the next tile's inputs are requested here, where the activations'
         // splits are free; they arrive during the output layer and the other
@@ -334,19 +344,14 @@ __global__ void __launch_bounds__(NMB == 4 ? 512 : 256, 2) mlp_f32_kernel(Map32 
         outputs(0);
         if (pk.f_out > 4)
             outputs(1);
-        const float all[4] = {v[0][0], v[0][1], v[1][0], v[1][1]};
-        if (__any(outside(range, pk.limit, pk.least, all, pk.f_out, g))) {
-            // this tile again on the fp32 instruction
-            const MapsLds &tab = maps();
-            const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
-            layers_plain<NMB>(pk, lds, lay, [&](int s) __attribute__((always_inline)) {
-                const int f = 2 * s + g;
-                const uint32_t raw[1] = {tab.raw8[f]};
-                int32_t idx[1] = {pt.pe};
-                fix_lds<1>(tab.in, pt, 15u, raw, idx);
-                const float v = ldg(tab.fptr[f] + idx[0]);
-                return f < F ? v : 0.f;
-            }, lane, acc);
+        if (outside(range, pk.limit, pk.least, v, pk.f_out)) {
+            // this tile (again) on the fp32 instruction
+            float x[XS];
+            gather(tile, x);
+#pragma unroll
+            for (int s = 0; s < XS; ++s)
+                x[s] = 2 * s + (ln >> 5) < F ? x[s] : 0.f;
+            layers_plain<NMB, KS1, LOG>(pk, x, fl, gl, lds, lay, ln >> 5, acc);
             outputs(0);
             if (pk.f_out > 4)
                 outputs(1);
@@ -418,35 +423,41 @@ bool f32_fast_supported(int n_layers, const int32_t *dims, int compute) {
     return SplitLayout{H / 32, (dims[0] + 15) / 16, n_layers - 2, dims[n_layers]}.lds(true) <= kLdsMax;
 }
 
-size_t f32_image_floats(int n_layers, const int32_t *dims) {
-    return (size_t)SplitLayout{dims[1] / 32, (dims[0] + 15) / 16, n_layers - 2, dims[n_layers]}.total() / 4;
-}
-
 // Host packing of the split image (see SplitLayout): A fragments in the order
 // the lanes read them, biases and output weights in the C-fragment order.
-void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *img,
+void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, std::vector<float> &image,
               F32Packed *pk) {
     const int H = dims[1], NMB = H / 32, Fin = dims[0], Fout = dims[n_layers], NH = n_layers - 2;
     const SplitLayout sl{NMB, (Fin + 15) / 16, NH, Fout};
-    std::fill(img, img + sl.total() / 4, 0.f);
     auto put_bias = [&](float *dst, const float *bias) {
         for (int g = 0; g < 2; ++g)
             for (int mb = 0; mb < NMB; ++mb)
                 for (int r = 0; r < 16; ++r)
                     dst[(g * NMB + mb) * 16 + r] = bias[crow(mb, r, g)];
     };
-    bool fine = put_layer(
-        reinterpret_cast<char *>(img), W[0], H, Fin, sl.ks, NMB,
-        [&](int s, int mb) { return sl.l1() + (s * NMB + mb) * 2 * kFragBytes; },
-        [&](int s, int mb) { return sl.l1_lo() + (s * NMB + mb) * kFragBytes; },
-        [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
+    // (the output layer is on the fp32 instruction)
+    LayerRows rows[HPACML_MAX_LAYERS];
+    for (int l = 0; l + 1 < n_layers; ++l)
+        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
+    SplitRange range;
+    const bool fine = split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range);
+    pk->weights = !fine ? kPlainWeights : range.tiny ? kPlainBehind : kSplitWeights;
+    pk->limit = range.limit;
+    pk->least = range.least;
+    image.assign((sl.total() + (range.tiny ? sl.l1_lo() - sl.l1() : 0)) / 4, 0.f);
+    float *img = image.data();
+    auto put = [&](const float *w, int K, int steps, int hm0, int lo0, auto &&feature) {
+        auto hm = [&](int s, int mb) { return hm0 + (s * NMB + mb) * 2 * kFragBytes; };
+        auto lo = [&](int s, int mb) { return lo0 + (s * NMB + mb) * kFragBytes; };
+        put_layer(reinterpret_cast<char *>(img), w, H, K, steps, NMB, !fine, hm, lo, feature);
+        if (fine && range.tiny)
+            put_layer(reinterpret_cast<char *>(img) + sl.behind(), w, H, K, steps, NMB, true, hm, lo, feature);
+    };
+    put(W[0], Fin, sl.ks, sl.l1(), sl.l1_lo(), [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
     put_bias(img + sl.l1_bias() / 4, b[0]);
     for (int h = 0; h < NH; ++h) {
         // element j of K-step s is register 8 (s % 2) + j of m-block s / 2
-        fine &= put_layer(
-            reinterpret_cast<char *>(img), W[h + 1], H, H, 2 * NMB, NMB,
-            [&](int s, int mb) { return sl.hidden(h) + (s * NMB + mb) * 2 * kFragBytes; },
-            [&](int s, int mb) { return sl.hidden_lo(h) + (s * NMB + mb) * kFragBytes; },
+        put(W[h + 1], H, 2 * NMB, sl.hidden(h), sl.hidden_lo(h),
             [](int s, int g, int j) { return crow(s / 2, 8 * (s % 2) + j, g); });
         put_bias(img + sl.hidden_bias(h) / 4, b[h + 1]);
     }
@@ -458,16 +469,8 @@ void f32_pack(int n_layers, const int32_t *dims, const float *const *W, const fl
                     const int r = 8 * i + bb, lane = 32 * g + 4 * bb + o % 4;
                     img[sl.out_w(o / 4) / 4 + (i / 4 * 64 + lane) * 4 + i % 4] = Wo[(size_t)o * H + crow(r / 16, r % 16, g)];
                 }
-    for (int go = 0; go < Fout; ++go)
-        img[sl.out_b() / 4 + go] = b[n_layers - 1][go];
-    // (the output layer is on the fp32 instruction)
-    LayerRows rows[HPACML_MAX_LAYERS];
-    for (int l = 0; l + 1 < n_layers; ++l)
-        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
-    SplitRange range;
-    pk->plain = !split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range) || !fine;
-    pk->limit = range.limit;
-    pk->least = range.least;
+    for (int go = 0; go < kFoutMax; ++go)
+        img[sl.out_b() / 4 + go] = go < Fout ? b[n_layers - 1][go] : FLT_MAX;   // (never below `least`)
 }
 
 hipError_t launch_mlp_f32(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

@@ -194,6 +194,35 @@ __device__ __forceinline__ void activate(floatx16 *acc, float floor, Range &rang
         }
 }
 
+// Where the fp32 path of a tile has its weights: the split image's fragments put
+// together (hi + mid + lo is the weight, exactly, from 2^-110 up), or fragments of
+// fp32 weights (see put_layer) in the image's place in LDS or, for a model with
+// smaller weights, behind the image in global memory.
+enum WeightForm : int32_t { kSplitWeights = 0, kPlainWeights = 1, kPlainBehind = 2 };
+
+// One K-step of an m-block on the fp32 matrix instruction: a fragment (h, m, l)
+// holds rows and columns as eight of its A operands do; x: features (s, g, 0 .. 7)
+// of the lane's point.
+__device__ __forceinline__ floatx16 mfma_plain(u32x4 h, u32x4 m, u32x4 l, int form, const float *x, floatx16 acc) {
+    float w[8];
+    if (form == kSplitWeights) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[2 * i] = (__uint_as_float(h[i] << 16) + __uint_as_float(m[i] << 16)) + __uint_as_float(l[i] << 16);
+            w[2 * i + 1] = (__uint_as_float(h[i] & 0xFFFF0000u) + __uint_as_float(m[i] & 0xFFFF0000u)) +
+                           __uint_as_float(l[i] & 0xFFFF0000u);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            w[j] = __uint_as_float(j < 4 ? h[j] : m[j - 4]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j], x[j], acc, 0, 0, 0);
+    return acc;
+}
+
 // Activation of the fp32 path: ReLU (a NaN gives 0) or nothing; m-blocks mb0 on of
 // a layer of `width` neurons.  Those past it are 0 whatever the inputs (an
 // infinite input times their weights of 0 is a NaN).
@@ -295,18 +324,19 @@ __device__ __forceinline__ void join_halves(floatx4 sum, const float *bias, floa
     }
 }
 
-// Whether the split products may not serve this lane's point: a value too large
-// for them, or an output so small that the bits which tiny values lose would
-// show in it (see split_range).  All the outputs of a point whose inputs and
-// activations are 0 are exact.
-__device__ __forceinline__ bool outside(const Range &range, float limit, float least, const float (&v)[4], int f_out, int g) {
+// Whether the split products may not serve a point of the wave: a value too large
+// for them, or an output (v: those of this lane; FLT_MAX past the last) so small
+// that the bits which tiny values lose would show in it (see split_range).  All
+// outputs of a point whose inputs and activations are 0 are exact.
+__device__ __forceinline__ bool outside(const Range &range, float limit, float least, const float (&v)[2][2], int f_out) {
+    float low = fminf(fabsf(v[0][0]), fabsf(v[0][1]));
+    if (f_out > 4)
+        low = fminf(low, fminf(fabsf(v[1][0]), fabsf(v[1][1])));
+    if (!__any(range.outside(limit) || low < least))
+        return false;
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(range.top), __float_as_uint(range.top), false, false);
     const float top = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    float low = FLT_MAX;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)   // output 2i + g
-        low = 2 * i + g < f_out ? fminf(low, fabsf(v[i])) : low;
-    return range.outside(limit) || (top > 0.f && low < least);
+    return __any(range.outside(limit) || (top > 0.f && low < least));
 }
 
 // A point of the `from` map, and the store of outputs go + g and go + 2 + g.
@@ -370,15 +400,17 @@ inline bool split_range(const LayerRows *layers, int n, double after, SplitRange
         bool tiny = false;
         for (int o = 0; o < y.N; ++o) {
             double sum[4] = {};
-            float low = kBig;   // the least but 0
+            float low = kBig, top = 0.f;   // the least but 0
             const float *w = y.W + (size_t)o * y.K;
             for (int k = 0; k < y.K; ++k) {
                 const float a = std::fabs(w[k]);
                 sum[k % 4] += a;
                 low = std::min(low, a > 0.f ? a : kBig);
+                top = std::max(top, a);
             }
             const double all = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-            if (!(all < HUGE_VAL) || !(std::fabs(y.b[o]) < 0.5f * kBig))
+            // (a weight without a split, or a bias without room)
+            if (!(all < HUGE_VAL) || top >= kBig || !(std::fabs(y.b[o]) < 0.5f * kBig))
                 return false;
             worst = std::max(worst, all);
             tiny = tiny || low < kLeast;
@@ -416,20 +448,18 @@ inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t
 
 // One layer's A fragments: K-step s, m-block mb, lane l, element j is weight
 // [32 mb + l % 32][feature(s, l / 32, j)] (zero past N rows and K columns), its
-// parts at img + hm(s, mb) (hi, then mid) and img + lo(s, mb).  False when a
-// weight has no split.
+// parts at img + hm(s, mb) (hi, then mid) and img + lo(s, mb); `plain`: the
+// weights themselves, elements 0 .. 3 in place of hi and 4 .. 7 in place of mid.
 template <typename Hm, typename Lo, typename Feature>
-inline bool put_layer(char *img, const float *W, int N, int K, int steps, int blocks, Hm &&hm, Lo &&lo,
+inline void put_layer(char *img, const float *W, int N, int K, int steps, int blocks, bool plain, Hm &&hm, Lo &&lo,
                       Feature &&feature) {
     // split the layer in its own order (a loop the compiler vectorises), then
     // place the parts
     const size_t n = (size_t)N * K;
-    std::vector<uint16_t> q(3 * n);
+    std::vector<uint16_t> q(plain ? 0 : 3 * n);
     uint16_t *qh = q.data(), *qm = qh + n, *ql = qm + n;
-    uint32_t top = 0;   // magnitudes as bits: infinities and NaN above all
-    for (size_t i = 0; i < n; ++i) {
+    for (size_t i = 0; !plain && i < n; ++i) {
         const float w = W[i];
-        top = std::max(top, __builtin_bit_cast(uint32_t, w) & 0x7FFFFFFFu);
         qh[i] = rne(w);
         const float r = w - bf16_float(qh[i]);
         qm[i] = rne(r);
@@ -443,13 +473,16 @@ inline bool put_layer(char *img, const float *W, int N, int K, int steps, int bl
         for (int mb = 0; mb < blocks; ++mb) {
             uint16_t *h = reinterpret_cast<uint16_t *>(img + hm(s, mb)), *m = h + kFragBytes / 2;
             uint16_t *l = reinterpret_cast<uint16_t *>(img + lo(s, mb));
+            float *f = reinterpret_cast<float *>(img + hm(s, mb));
             for (int lane = 0; lane < 64; ++lane) {
                 if (32 * mb + lane % 32 >= N)
                     continue;
                 const size_t row = (size_t)(32 * mb + lane % 32) * K;
                 for (int j = 0; j < 8; ++j) {
                     const int k = at[lane / 32][j];
-                    if (k < K) {
+                    if (k < K && plain) {
+                        f[(j / 4) * (kFragBytes / 4) + lane * 4 + j % 4] = W[row + k];
+                    } else if (k < K) {
                         h[lane * 8 + j] = qh[row + k];
                         m[lane * 8 + j] = qm[row + k];
                         l[lane * 8 + j] = ql[row + k];
@@ -458,7 +491,6 @@ inline bool put_layer(char *img, const float *W, int N, int K, int steps, int bl
             }
         }
     }
-    return top < __builtin_bit_cast(uint32_t, kBig);
 }
 
 }  // namespace

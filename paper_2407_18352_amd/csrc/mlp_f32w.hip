@@ -42,6 +42,8 @@ struct WideLayout {
     __host__ __device__ int l2(int j, int t, int blk) const { return l1(nb1, 0) + ((j * 2 + t) * nb2 + blk) * 2 * kFragBytes; }
     __host__ __device__ int l2_lo(int j, int t, int blk) const { return l2(nb1, 0, 0) + ((j * 2 + t) * nb2 + blk) * kFragBytes; }
     __host__ __device__ int total() const { return l2_lo(nb1, 0, 0); }
+    // kPlainBehind: fp32 weights for the fragment pair at byte f lie at f + behind()
+    __host__ __device__ int behind() const { return total() - l1(0, 0); }
     __host__ __device__ int image_lds(bool lo_global) const { return lo_global ? l2_lo(0, 0, 0) : total(); }
     __host__ __device__ int lds(bool lo_global) const { return image_lds(lo_global) + (int)sizeof(MapsLds); }
 };
@@ -99,8 +101,7 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
         const u32x4 *fl = lds4 + ln;
         const u32x4 *gl = reinterpret_cast<const u32x4 *>(pk.image) + ln;
         Range range;   // of the inputs of every layer
-        if (pk.plain)
-            range.top = kBig;
+        range.top = pk.weights == kPlainWeights ? kBig : 0.f;
         Split b1[KS1];
         static_for<0, KS1>([&](auto s) __attribute__((always_inline)) {
             floatx8 v;
@@ -159,7 +160,9 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
             activate<1>(&main, act_floor(pk.relu >> layer & 1), range);
             return main;
         };
-        if constexpr (G == 0) {
+        if (__any(range.outside(pk.limit))) {
+            // (see below)
+        } else if constexpr (G == 0) {
             floatx16 main, sub;
             Frags f;
             read1(0, f);
@@ -272,31 +275,32 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
                 join_halves(y[1], ob + 4, v[1]);
         };
         outputs();
-        const float all[4] = {v[0][0], v[0][1], v[1][0], v[1][1]};
-        if (__any(outside(range, pk.limit, pk.least, all, pk.f_out, g))) {
-            // this tile again on the fp32 instruction, with the caller's weights in global memory (rows and columns past
-            // them are zero)
-            const MapsLds &tab = maps();
-            const Pt32 pt = locate_lds(tab.in, rank_in, valid ? b : n_points - 1);
-            auto weight = [&](int l, int row0, int k) __attribute__((always_inline)) {
-                const int row = row0 + (lane & 31), n_in = pk.dims[l];
-                const bool is = row < pk.dims[l + 1] && k < n_in;
-                const float w = ldg(pk.W[l] + (is ? row * n_in + k : 0));
-                return is ? w : 0.f;
+        if (outside(range, pk.limit, pk.least, v, pk.f_out)) {
+            // this tile (again) on the fp32 instruction
+            const int gc = ln >> 5, form = pk.weights, behind = lay.behind() / 16;
+            float x[XS];
+            gather_inputs<KS1>(maps(), rank_in, n_points, windowed, pairs, b, gc, x);
+#pragma unroll
+            for (int s = 0; s < XS; ++s)
+                x[s] = 2 * s + gc < F ? x[s] : 0.f;
+            auto step = [&](int hm, u32x4 lw, const float *xs, floatx16 acc) __attribute__((always_inline)) {
+                u32x4 f[2];
+                if (form == kPlainBehind) {
+                    f[0] = gl[behind + hm / 16];
+                    f[1] = gl[behind + hm / 16 + 64];
+                } else {
+                    f[0] = fl[hm / 16];
+                    f[1] = fl[hm / 16 + 64];
+                }
+                return mfma_plain(f[0], f[1], lw, form, xs, acc);
             };
             auto plain1 = [&](int j) __attribute__((always_inline)) {
                 floatx16 acc;
-                load_bias<1>(reinterpret_cast<const float *>(lds + lay.bias1() + j * 128), g, &acc);
-#pragma unroll 1
-                for (int s = 0; s < pairs; ++s) {
-                    const int f = 2 * s + g;
-                    const uint32_t raw[1] = {tab.raw8[f]};
-                    int32_t idx[1] = {pt.pe};
-                    fix_lds<1>(tab.in, pt, 15u, raw, idx);
-                    const float x = ldg(tab.fptr[f] + idx[0]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(0, 32 * j, f), f < F ? x : 0.f, acc, 0, 0, 0);
-                }
-                activate_plain<1>(&acc, pk.relu & 1, j, g, pk.dims[1]);
+                load_bias<1>(reinterpret_cast<const float *>(lds + lay.bias1() + j * 128), gc, &acc);
+#pragma unroll
+                for (int s = 0; s < KS1; ++s)
+                    acc = step(lay.l1(j, s), fl[lay.l1(j, s) / 16 + 128], x + 8 * s, acc);
+                activate_plain<1>(&acc, pk.relu & 1, j, gc, pk.dims[1]);
                 return acc;
             };
             y[0] = y[1] = floatx4{};
@@ -308,15 +312,20 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
 #pragma unroll 1
                 for (int p = 0; p < pk.nb2; ++p) {
                     floatx16 acc;
-                    load_bias<1>(reinterpret_cast<const float *>(lds + lay.bias2() + p * 128), g, &acc);
+                    load_bias<1>(reinterpret_cast<const float *>(lds + lay.bias2() + p * 128), gc, &acc);
 #pragma unroll 1
                     for (int j = 0; j < pk.nb1; ++j) {
-                        const floatx16 x = plain1(j);
+                        const floatx16 h = plain1(j);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(1, 32 * p, crow(j, r, g)), x[r], acc, 0, 0, 0);
+                        for (int t = 0; t < 2; ++t) {
+                            float xt[8];
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                xt[e] = h[8 * t + e];
+                            acc = step(lay.l2(j, t, p), (LOG ? gl : fl)[lay.l2_lo(j, t, p) / 16], xt, acc);
+                        }
                     }
-                    activate_plain<1>(&acc, pk.relu >> 1 & 1, p, g, pk.dims[2]);
+                    activate_plain<1>(&acc, pk.relu >> 1 & 1, p, gc, pk.dims[2]);
                     out_add(acc, p);
                 }
             }
@@ -375,16 +384,23 @@ bool f32w_supported(int n_layers, const int32_t *dims, int compute) {
     return lay.nb1 <= 128 && lay.nb2 <= 128 && lay.lds(true) <= kLdsMax;
 }
 
-size_t f32w_image_floats(int n_layers, const int32_t *dims) { return (size_t)wide_layout(n_layers, dims).total() / 4; }
-
-void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, float *image,
+void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, std::vector<float> &image,
                F32WPacked *pk) {
     const WideLayout lay = wide_layout(n_layers, dims);
     pk->nb1 = lay.nb1;
     pk->nb2 = lay.nb2;
     pk->f_out = lay.f_out;
-    char *img = reinterpret_cast<char *>(image);
-    std::fill(image, image + lay.total() / 4, 0.f);
+    // (the output layer is on the fp32 instruction)
+    LayerRows rows[2];
+    for (int l = 0; l + 1 < n_layers; ++l)
+        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
+    SplitRange range;
+    const bool fine = split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range);
+    pk->weights = !fine ? kPlainWeights : range.tiny ? kPlainBehind : kSplitWeights;
+    pk->limit = range.limit;
+    pk->least = range.least;
+    image.assign((lay.total() + (range.tiny ? lay.l2_lo(0, 0, 0) - lay.l1(0, 0) : 0)) / 4, 0.f);
+    char *img = reinterpret_cast<char *>(image.data());
     auto put_bias = [&](int off, const float *bias, int n, int blocks) {
         float *d = reinterpret_cast<float *>(img + off);
         for (int mb = 0; mb < blocks; ++mb)
@@ -392,15 +408,17 @@ void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
                 for (int r = 0; r < 16; ++r)
                     d[(mb * 2 + g) * 16 + r] = crow(mb, r, g) < n ? bias[crow(mb, r, g)] : 0.f;
     };
+    auto put = [&](int l, int steps, int blocks, auto &&hm, auto &&lo, auto &&feature) {
+        put_layer(img, W[l], dims[l + 1], dims[l], steps, blocks, !fine, hm, lo, feature);
+        if (fine && range.tiny)
+            put_layer(img + lay.behind(), W[l], dims[l + 1], dims[l], steps, blocks, true, hm, lo, feature);
+    };
     put_bias(lay.bias1(), b[0], dims[1], lay.nb1);
-    bool fine = put_layer(
-        img, W[0], dims[1], dims[0], lay.ks, lay.nb1, [&](int s, int j) { return lay.l1(j, s); },
-        [&](int s, int j) { return lay.l1(j, s) + 2 * kFragBytes; },
+    put(0, lay.ks, lay.nb1, [&](int s, int j) { return lay.l1(j, s); }, [&](int s, int j) { return lay.l1(j, s) + 2 * kFragBytes; },
         [](int s, int g, int j) { return 2 * (8 * s + j) + g; });
     if (n_layers == 3) {
         put_bias(lay.bias2(), b[1], dims[2], lay.nb2);
-        fine &= put_layer(
-            img, W[1], dims[2], dims[1], 2 * lay.nb1, lay.nb2, [&](int s, int mb) { return lay.l2(s / 2, s % 2, mb); },
+        put(1, 2 * lay.nb1, lay.nb2, [&](int s, int mb) { return lay.l2(s / 2, s % 2, mb); },
             [&](int s, int mb) { return lay.l2_lo(s / 2, s % 2, mb); },
             [](int s, int g, int j) { return crow(s / 2, 8 * (s % 2) + j, g); });
     }
@@ -415,16 +433,8 @@ void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
                         d[(32 * g + 4 * q + o % 4) * 2 + i] = k < K ? W[n_layers - 1][(size_t)o * K + k] : 0.f;
                     }
         }
-    for (int o = 0; o < O; ++o)
-        reinterpret_cast<float *>(img + lay.out_b())[o] = b[n_layers - 1][o];
-    // (the output layer is on the fp32 instruction)
-    LayerRows rows[HPACML_MAX_LAYERS];
-    for (int l = 0; l + 1 < n_layers; ++l)
-        rows[l] = LayerRows{W[l], b[l], dims[l + 1], dims[l]};
-    SplitRange range;
-    pk->plain = !split_range(rows, n_layers - 1, largest_row_sum(W[n_layers - 1], dims[n_layers], dims[n_layers - 1]), &range) || !fine;
-    pk->limit = range.limit;
-    pk->least = range.least;
+    for (int o = 0; o < kFoutMax; ++o)
+        reinterpret_cast<float *>(img + lay.out_b())[o] = o < O ? b[n_layers - 1][o] : FLT_MAX;   // (never below `least`)
 }
 
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

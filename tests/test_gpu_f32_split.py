@@ -221,3 +221,30 @@ def test_infinities_through_identity_layers(dims):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     fine = np.isfinite(want).all(1)
     assert parity_stats(got[fine], want[fine])[0] <= 1e-5
+
+
+@pytest.mark.parametrize("form", ["split", "plain", "behind"])
+@pytest.mark.parametrize("dims", [
+    [9, 128, 128, 128, 1], [36, 128, 128, 4], [64, 128, 1], [17, 64, 64, 5], [36, 64, 64, 64, 64, 64, 64, 8], [5, 50, 30, 1],
+    [5, 300, 6], [48, 300, 1], [9, 200, 30, 1], [17, 160, 64, 5], [9, 400, 64, 1], [20, 129, 65, 3]])
+def test_fp32_path_in_each_weight_form(dims, form):
+    """Every tile on the fp32 instruction: a point with an infinite input in each
+    (weights put together from their parts), a weight that has no split (fp32
+    weights in the image), a tiny weight that meets a large input (fp32 weights
+    behind it)."""
+    n = 500
+    g = np.random.default_rng(sum(dims))
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    if form == "split":
+        w.inputs[1][::17] = np.inf
+    elif form == "plain":
+        w.inputs[2][:] = (w.inputs[2] * np.float32(2.0 ** -126)).astype(np.float32)
+        w.model["W"][0][11, 2] = 2.0 ** 127
+    else:
+        w.inputs[2][:] = (w.inputs[2] * np.float32(2.0 ** 122)).astype(np.float32)
+        w.model["W"][0][:, 2] = (w.model["W"][0][:, 2] * np.float32(2.0 ** -122)).astype(np.float32)
+    got, want = _run(w, "mlp_")
+    rows = np.isfinite(w.inputs[1])
+    w.inputs = [x[rows] for x in w.inputs]
+    w.in_spec = wl.pointwise_spec(int(rows.sum()))
+    assert _fp32_error(w, got[rows], want[rows]) <= 4
