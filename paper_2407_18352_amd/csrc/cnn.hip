@@ -70,13 +70,13 @@ __device__ __forceinline__ int wrap(int v, int n) {
 
 // Layer 0's input region from the `to` map: pixel (y, x) of image s is
 // composed point (s * H + y) * W + x; channel f is its feature f.
-template <int CI>
+template <int CI, int NT>
 __device__ __forceinline__ void gather_region(const FusedArgs &a, const TabLds &tab, int s, int y0, int x0,
                                               float *dst) {
     const int rh = a.rh[0], rw = a.rw[0], n = rh * rw;
     const int mode = a.L[0].mode;
     const int vy0 = y0 - a.rt[0], vx0 = x0 - a.rl[0];
-    for (int i = threadIdx.x; i < n; i += (int)blockDim.x) {
+    for (int i = threadIdx.x; i < n; i += NT) {
         const int ry = div_region(i, a.rw_magic[0]), rx = i - ry * rw;
         int y = vy0 + ry, x = vx0 + rx;
         bool zero = false;
@@ -138,10 +138,10 @@ __device__ __forceinline__ LayerRun layer_run(const FusedArgs &a) {
 
 // One layer over its output region (the next layer's input region, or the
 // tile for the last layer) into LDS.  Each thread takes kPix pixels per pass
-// (i, i + kThreads, ...): a weight loaded once feeds kPix FMAs.  Pixels
+// (i, i + NT, ...): a weight loaded once feeds kPix FMAs.  Pixels
 // outside the image get what the next layer's padding reads there (the last
 // layer's are never stored).
-template <int CIN4, int COUT4>
+template <int CIN4, int COUT4, int NT>
 __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab, const LayerRun &r,
                                           const float *__restrict__ wts, const float *src, float *dst, int s, int y0,
                                           int x0) {
@@ -154,13 +154,12 @@ __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab,
     const float *bl = wts + Ly.boff;
     const int kh = Ly.kh, kw = Ly.kw;
     const int n = oh * ow;
-    const int nt = (int)blockDim.x;
-    for (int base = 0; base < n; base += nt * kPix) {
+    for (int base = 0; base < n; base += NT * kPix) {
         int off[kPix];          // LDS float offset of each pixel's window origin
         bool valid[kPix], zero[kPix];
 #pragma unroll
         for (int j = 0; j < kPix; ++j) {
-            const int i = base + j * nt + (int)threadIdx.x;
+            const int i = base + j * NT + (int)threadIdx.x;
             valid[j] = i < n;
             const int ic = valid[j] ? i : n - 1;
             int ry = div_region(ic, r.ow_magic), rx = ic - ry * ow;
@@ -224,7 +223,7 @@ __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab,
                 }
                 if (!valid[j])
                     continue;
-                const int i = base + j * nt + (int)threadIdx.x;
+                const int i = base + j * NT + (int)threadIdx.x;
                 reinterpret_cast<float4 *>(dst + (size_t)i * CO)[og] =
                     zero[j] ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
             }
@@ -234,11 +233,12 @@ __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab,
 
 // The last layer's tile (LDS, [pixel][4 * cout4]) through the `from` map:
 // pixel (y, x) of image s is point (s * H + y) * W + x, channel g its feature g.
+template <int NT>
 __device__ __forceinline__ void scatter_tile(const FusedArgs &a, const TabLds &tab, const float *src, int s, int y0,
                                              int x0) {
     const int CO = a.co_last_pad;
     const int n = a.ty * kTX;
-    for (int i = threadIdx.x; i < n; i += (int)blockDim.x) {
+    for (int i = threadIdx.x; i < n; i += NT) {
         const int ry = i / kTX, rx = i % kTX;
         const int y = y0 + ry, x = x0 + rx;
         if (y >= a.H || x >= a.W)
@@ -253,15 +253,15 @@ __device__ __forceinline__ void scatter_tile(const FusedArgs &a, const TabLds &t
     }
 }
 
-template <int CIN4>
+template <int CIN4, int NT>
 __device__ __forceinline__ void conv_dispatch_out(const FusedArgs &a, const TabLds &tab, const LayerRun &r,
                                                   const float *__restrict__ wts, const float *src, float *dst, int s,
                                                   int y0, int x0) {
     switch (r.Ly.cout4) {
-    case 1: conv_pass<CIN4, 1>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    case 2: conv_pass<CIN4, 2>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    case 3: conv_pass<CIN4, 3>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    default: conv_pass<CIN4, 4>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 1: conv_pass<CIN4, 1, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 2: conv_pass<CIN4, 2, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 3: conv_pass<CIN4, 3, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    default: conv_pass<CIN4, 4, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
     }
 }
 
@@ -275,15 +275,16 @@ __device__ __forceinline__ void stage_tab(const FusedArgs &a, TabLds &tab) {
     }
 }
 
-// One tile by the vector ALU: gather, every layer, scatter.
+// One tile by the vector ALU and NT threads: gather, every layer, scatter.
+template <int NT>
 __device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, const float *__restrict__ wts,
                                          float *buf0, int s, int y0, int x0) {
     float *const buf1 = buf0 + a.buf1;
     switch (a.L[0].cin4) {
-    case 1: gather_region<4>(a, tab, s, y0, x0, buf0); break;
-    case 2: gather_region<8>(a, tab, s, y0, x0, buf0); break;
-    case 3: gather_region<12>(a, tab, s, y0, x0, buf0); break;
-    default: gather_region<16>(a, tab, s, y0, x0, buf0); break;
+    case 1: gather_region<4, NT>(a, tab, s, y0, x0, buf0); break;
+    case 2: gather_region<8, NT>(a, tab, s, y0, x0, buf0); break;
+    case 3: gather_region<12, NT>(a, tab, s, y0, x0, buf0); break;
+    default: gather_region<16, NT>(a, tab, s, y0, x0, buf0); break;
     }
     __syncthreads();
     for (int l = 0; l < a.n_layers; ++l) {
@@ -297,14 +298,14 @@ __device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, 
         const float *src = (l & 1) ? buf1 : buf0;
         float *dst = (l & 1) ? buf0 : buf1;
         switch (r.Ly.cin4) {
-        case 1: conv_dispatch_out<1>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        case 2: conv_dispatch_out<2>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        case 3: conv_dispatch_out<3>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        default: conv_dispatch_out<4>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 1: conv_dispatch_out<1, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 2: conv_dispatch_out<2, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 3: conv_dispatch_out<3, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        default: conv_dispatch_out<4, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
         }
         __syncthreads();
     }
-    scatter_tile(a, tab, (a.n_layers & 1) ? buf1 : buf0, s, y0, x0);
+    scatter_tile<NT>(a, tab, (a.n_layers & 1) ? buf1 : buf0, s, y0, x0);
 }
 
 __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const float *__restrict__ wts) {
@@ -325,7 +326,7 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
     const int ty_i = rem / a.tiles_x;
     const int y0 = ty_i * a.ty, x0 = (rem - ty_i * a.tiles_x) * kTX;
 
-    run_tile(a, tab, wts, buf0, s, y0, x0);
+    run_tile<kThreads>(a, tab, wts, buf0, s, y0, x0);
 }
 
 // ------------------------------------------------------------------ fused, matrix cores
@@ -907,7 +908,7 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         if ((all & 1u) || (all & 6u) == 6u) {
             // values that the split products can't take
             const MfmaArgs &m = mfma_args();
-            run_tile(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
+            run_tile<kMThreads>(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
             __syncthreads();
             clear(m.planes_off, m.planes_bytes);
             __syncthreads();
