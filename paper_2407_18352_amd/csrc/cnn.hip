@@ -34,7 +34,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTX = 64;   // tile columns
-constexpr int kPix = 1;   // pixels per thread per pass
 
 // ------------------------------------------------------------------ fused, vector ALU
 struct FusedArgs {
@@ -141,7 +140,7 @@ __device__ __forceinline__ LayerRun layer_run(const FusedArgs &a) {
 // (i, i + NT, ...): a weight loaded once feeds kPix FMAs.  Pixels
 // outside the image get what the next layer's padding reads there (the last
 // layer's are never stored).
-template <int CIN4, int COUT4, int NT>
+template <int CIN4, int COUT4, int NT, int kPix>
 __device__ __forceinline__ void conv_pass(const FusedArgs &a, const TabLds &tab, const LayerRun &r,
                                           const float *__restrict__ wts, const float *src, float *dst, int s, int y0,
                                           int x0) {
@@ -253,15 +252,15 @@ __device__ __forceinline__ void scatter_tile(const FusedArgs &a, const TabLds &t
     }
 }
 
-template <int CIN4, int NT>
+template <int CIN4, int NT, int kPix>
 __device__ __forceinline__ void conv_dispatch_out(const FusedArgs &a, const TabLds &tab, const LayerRun &r,
                                                   const float *__restrict__ wts, const float *src, float *dst, int s,
                                                   int y0, int x0) {
     switch (r.Ly.cout4) {
-    case 1: conv_pass<CIN4, 1, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    case 2: conv_pass<CIN4, 2, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    case 3: conv_pass<CIN4, 3, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-    default: conv_pass<CIN4, 4, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 1: conv_pass<CIN4, 1, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 2: conv_pass<CIN4, 2, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    case 3: conv_pass<CIN4, 3, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+    default: conv_pass<CIN4, 4, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
     }
 }
 
@@ -275,17 +274,23 @@ __device__ __forceinline__ void stage_tab(const FusedArgs &a, TabLds &tab) {
     }
 }
 
-// One tile by the vector ALU and NT threads: gather, every layer, scatter.
+// Layer 0's input region of a tile.
 template <int NT>
-__device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, const float *__restrict__ wts,
-                                         float *buf0, int s, int y0, int x0) {
-    float *const buf1 = buf0 + a.buf1;
+__device__ __forceinline__ void gather_tile(const FusedArgs &a, const TabLds &tab, float *buf0, int s, int y0, int x0) {
     switch (a.L[0].cin4) {
     case 1: gather_region<4, NT>(a, tab, s, y0, x0, buf0); break;
     case 2: gather_region<8, NT>(a, tab, s, y0, x0, buf0); break;
     case 3: gather_region<12, NT>(a, tab, s, y0, x0, buf0); break;
     default: gather_region<16, NT>(a, tab, s, y0, x0, buf0); break;
     }
+}
+
+// One gathered tile by the vector ALU and NT threads, kPix pixels each at a time:
+// every layer, scatter.
+template <int NT, int kPix>
+__device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, const float *__restrict__ wts,
+                                         float *buf0, int s, int y0, int x0) {
+    float *const buf1 = buf0 + a.buf1;
     __syncthreads();
     for (int l = 0; l < a.n_layers; ++l) {
         LayerRun r;
@@ -298,10 +303,10 @@ __device__ __forceinline__ void run_tile(const FusedArgs &a, const TabLds &tab, 
         const float *src = (l & 1) ? buf1 : buf0;
         float *dst = (l & 1) ? buf0 : buf1;
         switch (r.Ly.cin4) {
-        case 1: conv_dispatch_out<1, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        case 2: conv_dispatch_out<2, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        case 3: conv_dispatch_out<3, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
-        default: conv_dispatch_out<4, NT>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 1: conv_dispatch_out<1, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 2: conv_dispatch_out<2, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        case 3: conv_dispatch_out<3, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
+        default: conv_dispatch_out<4, NT, kPix>(a, tab, r, wts, src, dst, s, y0, x0); break;
         }
         __syncthreads();
     }
@@ -326,7 +331,8 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
     const int ty_i = rem / a.tiles_x;
     const int y0 = ty_i * a.ty, x0 = (rem - ty_i * a.tiles_x) * kTX;
 
-    run_tile<kThreads>(a, tab, wts, buf0, s, y0, x0);
+    gather_tile<kThreads>(a, tab, buf0, s, y0, x0);
+    run_tile<kThreads, 1>(a, tab, wts, buf0, s, y0, x0);
 }
 
 // ------------------------------------------------------------------ fused, matrix cores
@@ -357,9 +363,17 @@ __global__ void __launch_bounds__(kThreads) cnn_fused_kernel(FusedArgs a, const 
 // it: of 26 thousand cycles a tile of 16 rows the first layer's column tiles take 8
 // (matrix instructions 3.8 of them, LDS reads as much), the second's 6, and the
 // gather's address arithmetic, splits and barriers most of the rest.
+//
+// NaN pixels (a land mask) go on in this form: 0 in the planes and a bit a pixel,
+// and the outputs whose window reaches one are put right after the first layer.
+// 2048 x 2048 as above with a NaN in every tile: 227 us, on 1024 x 1024 with 2 x 2 and
+// 2 x 2 on 4 channels 47 (each such tile on the vector ALU after the matrix cores: 570,
+// 64).  A tile with other values outside the range takes 2 to 2.4 times as long.
 constexpr int kMThreads = 512, kMWaves = 8;
 constexpr size_t kMStatic = 2048;        // LDS beside the image and the planes (tables, arguments, flags)
 constexpr int kPre = 4;                  // pixels per thread requested ahead
+constexpr int kFallPix = 3;              // pixels per thread at a time where a tile goes to the vector ALU
+constexpr int kNanWords = 5;             // words of a row of NaN bits: 128 columns, and one to read past them
 struct ConvM {
     int32_t cout, m16, P, ci, co;        // output channels; 16-row form; pixels per group; padded channels in, out
     int32_t steps, rch, chunks;          // K-steps; 8-value chunks per window row, and in all
@@ -375,6 +389,7 @@ struct ConvM {
     uint32_t ng_magic;                   // i / ng == (i * ng_magic) >> 24
     int32_t relu, next_mode, rt, rl;     // what the next layer's padding reads outside; region origin
     int32_t tab_off;                     // this layer's chunk offsets in LDS (steps x chunks a step)
+    int32_t kh, kw;
 };
 struct MfmaArgs {
     FusedArgs f;
@@ -382,7 +397,9 @@ struct MfmaArgs {
     const void *image;                   // device: biases and fragments of every layer
     float limit, least;                  // of the layers' inputs and the outputs (see split_range)
     int32_t tiny;                        // a weight loses bits
-    int32_t image_bytes, planes_off, planes_bytes;   // LDS: image, then planes
+    int32_t image_bytes, planes_off, planes_bytes;   // LDS: image, then planes,
+    int32_t clear_bytes;                 // then NaN bits (with the planes)
+    int32_t nan_off, nan_bytes;          // LDS: the gathered region's NaN bits (0: a NaN sends the tile to the vector ALU)
     int32_t pre;                         // the next tile is requested ahead
     int32_t in_rank, out_rank, in_offsets, out_offsets;
     int32_t imaged;                      // the sweep's last two dimensions are the image's (a snapshot record's are not)
@@ -406,7 +423,7 @@ __device__ __forceinline__ const MfmaArgs &mfma_args() {
     return *(const MfmaArgs *)(const __attribute__((address_space(4))) MfmaArgs *)p;
 }
 
-static_assert(sizeof(MfmaArgs) + sizeof(TabLds) + 2 * kMWaves * 4 <= kMStatic, "static LDS");
+static_assert(sizeof(MfmaArgs) + sizeof(TabLds) + 3 * kMWaves * 4 <= kMStatic, "static LDS");
 
 // v0..v3 split into the three planes at byte `at` (four bf16 each).
 __device__ __forceinline__ void put4(char *base, int plane, int at, float v0, float v1, float v2, float v3) {
@@ -491,17 +508,28 @@ __device__ __forceinline__ floatx4 mma(u32x4 a, u32x4 b, floatx4 c) {
 // What a lane met in a tile.
 struct Seen {
     Range hidden;                  // the layers' inputs but the first's
-    uint32_t in2 = 0;              // the first's largest: bits shifted past the sign (infinities and NaN above all)
+    uint32_t in2 = 0;              // the first's largest: bits shifted past the sign (infinities and NaN above all); tested apart
     uint32_t low = 0xFFFFFFFFu;    // the least input of any layer but 0: the same bits, less 1 (0 comes last)
     float out = FLT_MAX;           // the least output
     __device__ __forceinline__ void add_low(float v) { low = min(low, (__float_as_uint(v) << 1) - 1u); }
     // bit 0: the matrix form may not serve this tile; bit 1: nor if bit 2 (a
     // value lost bits) is set as well, in any wave of the block
     __device__ __forceinline__ uint32_t flags(float limit, float least) const {
-        return (__any(hidden.outside(limit) || in2 >= __float_as_uint(limit) << 1) ? 1u : 0u) | (__any(out < least) ? 2u : 0u) |
+        return (__any(hidden.outside(limit)) ? 1u : 0u) | (__any(out < least) ? 2u : 0u) |
                (__any(low < (__float_as_uint(kLeast) << 1) - 1u) ? 4u : 0u);
     }
 };
+
+// Whether a window of the first layer, at the gathered region's row and column,
+// holds a NaN pixel.
+__device__ __forceinline__ bool window_nan(const uint32_t *rows, int row, int col, int kh, int kw) {
+    uint32_t any = 0;
+    for (int ky = 0; ky < kh; ++ky) {
+        const uint32_t *r = rows + (row + ky) * kNanWords + (col >> 5);
+        any |= __builtin_amdgcn_alignbit(r[1], r[0], col & 31);
+    }
+    return (any & ((1u << kw) - 1u)) != 0;
+}
 
 // One layer of the tile: this wave's share of the groups.
 template <bool M16, bool LAST>
@@ -684,6 +712,37 @@ __device__ __forceinline__ void replicate_edges(const MfmaArgs &m, const ConvM &
     }
 }
 
+// NaN pixels among a tile's inputs are 0 in the planes: after the first layer the
+// outputs that they reach become what they are, 0 after a ReLU ahead of another
+// layer (the planes), NaN or 0 in the last (the arrays).
+__device__ __forceinline__ void nan_outputs(const MfmaArgs &m, const TabLds &tab, char *lds, int s, int y0, int x0) {
+    const FusedArgs &a = m.f;
+    const ConvM &c = m.c[0];
+    const uint32_t *rows = reinterpret_cast<const uint32_t *>(lds + m.nan_off);
+    const bool last = a.n_layers == 1;
+    const int cols = a.rw[1], n = c.oh * cols;
+    for (int i = threadIdx.x; i < n; i += kMThreads) {
+        const int ry = div_region(i, a.rw_magic[1]), rx = i - ry * cols;
+        const int y = y0 + ry, x = x0 + rx;
+        if (!window_nan(rows, ry, rx, c.kh, c.kw) || (last && (y >= a.H || x >= a.W)))
+            continue;
+        if (!last) {
+            for (int e = 0; e < c.co / 4; ++e) {
+                const int d = c.out_off + ry * c.out_row_b + row_spot(rx * c.co * 2 + 8 * e, c.out_S, c.out_inv, c.out_sub);
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<uint2 *>(lds + d + p * c.out_plane) = make_uint2(0u, 0u);
+            }
+            continue;
+        }
+        const Pt32 pt = locate32(a.out, (s * a.H + y) * a.W + x);
+        const uint32_t edge = edge_dims32(a.out, pt);
+        for (int g = 0; g < a.cout_last; ++g) {
+            const int fix = edge ? edge_fix32(a.out, pt, tab.out_raw8[g], edge) : 0;
+            stg(tab.out[g] + (pt.pe + fix), c.relu ? 0.f : __builtin_nanf(""));
+        }
+    }
+}
+
 __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, const float *__restrict__ wts) {
     extern __shared__ float4 lds4[];
     char *lds = reinterpret_cast<char *>(lds4);
@@ -694,14 +753,15 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         asm volatile("" : "+v"(z));   // read where it is used, not held in registers
         return *reinterpret_cast<const MfmaArgs *>(reinterpret_cast<const char *>(&args_lds) + z);
     };
-    __shared__ uint32_t flags[2][kMWaves];   // per tile (in turn) and wave (see Seen)
-    int tile_no = 0;
+    __shared__ uint32_t flags[3][kMWaves];   // after a tile's gather, after its layers (see Seen) and after a second look at its inputs, per wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto clear = [&](int off, int bytes) {
         for (int i = tid; i < bytes / 16; i += kMThreads)
             reinterpret_cast<u32x4 *>(lds + off)[i] = u32x4{0u, 0u, 0u, 0u};
     };
-    int n_tiles, n_layers, n_pix, grid_x, pre_on;
+    int n_tiles, n_layers, n_pix, grid_x, pre_on, nan_off;
+    uint32_t limit2, tiny;
+    float limit, least;
     {
         const MfmaArgs &m = mfma_args();
         for (int i = tid; i < (int)(sizeof(MfmaArgs) / 4); i += kMThreads)
@@ -722,8 +782,13 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
         n_pix = m.f.rh[0] * m.f.rw[0];
         grid_x = m.grid_x;
         pre_on = m.pre;
+        nan_off = m.nan_off;
+        limit = m.limit;
+        least = m.least;
+        limit2 = __float_as_uint(limit) << 1;
+        tiny = m.tiny ? 4u : 0u;
     }
-    clear(mfma_args().planes_off, mfma_args().planes_bytes);   // columns past the gathered ones are read (with zero weights): they must be finite
+    clear(mfma_args().planes_off, mfma_args().clear_bytes);   // columns past the gathered ones are read (with zero weights): they must be finite (NaN bits behind them)
     __syncthreads();
 
     // each XCD takes a contiguous range of tiles, its blocks adjacent ones
@@ -831,21 +896,11 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
     for (int tile = first; tile < t_end; tile += grid_x) {
         int s, y0, x0;
         Seen seen;
-        {
+        locate_tile(local().f, tile, s, y0, x0);
+        // the tile's pixels: f(byte of the planes, bytes of one plane, region pixel, four channels)
+        auto pixels = [&](auto &&f) __attribute__((always_inline)) {
             const MfmaArgs &m = local();
-            locate_tile(m.f, tile, s, y0, x0);
-            const int in_off = uni(m.c[0].in_off), plane = uni(m.c[0].in_plane), row_b = uni(m.c[0].row_b), ci = uni(m.c[0].ci);
-            const uint32_t rw_magic = (uint32_t)uni((const int32_t &)m.f.rw_magic[0]);
-            const int rw = uni(m.f.rw[0]), ch = uni(m.f.c0);
-            const int S0 = uni(m.c[0].S), inv0 = uni(m.c[0].inv), sub0 = uni(m.c[0].sub);
-            auto put = [&](int at, const float (&v)[4]) __attribute__((always_inline)) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    seen.in2 = max(seen.in2, __float_as_uint(v[e]) << 1);
-                    seen.add_low(v[e]);
-                }
-                put4(lds, plane, at, v[0], v[1], v[2], v[3]);
-            };
+            const int plane = uni(m.c[0].in_plane), ch = uni(m.f.c0);
             if (pre_on) {
 #pragma unroll
                 for (int u = 0; u < kPre; ++u) {
@@ -854,10 +909,13 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             v[e] = (zeros >> u & 1u) || e >= ch ? 0.f : pre[u][e];
-                        put(place[u], v);
+                        f(place[u], plane, tid + u * kMThreads, v);
                     }
                 }
             } else {
+                const int in_off = uni(m.c[0].in_off), row_b = uni(m.c[0].row_b), ci = uni(m.c[0].ci), rw = uni(m.f.rw[0]);
+                const uint32_t rw_magic = (uint32_t)uni((const int32_t &)m.f.rw_magic[0]);
+                const int S0 = uni(m.c[0].S), inv0 = uni(m.c[0].inv), sub0 = uni(m.c[0].sub);
                 int32_t lead[2];
                 const int32_t pe = lead_of(m, s, lead);
                 const bool inside = inside_of(m.f, y0, x0);
@@ -867,50 +925,107 @@ __global__ void __launch_bounds__(kMThreads, 2) cnn_fused_mfma_kernel(MfmaArgs, 
                     for (int c4 = 0; c4 < ci / 4; ++c4) {
                         float v[4];
                         load4(m, g, c4, v);
-                        put(in_off + ry * row_b + row_spot((rx * ci + 4 * c4) * 2, S0, inv0, sub0), v);
+                        f(in_off + ry * row_b + row_spot((rx * ci + 4 * c4) * 2, S0, inv0, sub0), plane, i, v);
                     }
                 }
             }
-        }
-        __syncthreads();
-        if (pre_on && tile + grid_x < t_end)
-            request(tile + grid_x);
-        for (int l = 0; l + 1 < n_layers; ++l) {
-            const MfmaArgs &m = local();
-            if (uni(m.c[l].m16))
-                conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
-            else
-                conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
+        };
+        pixels([&](int at, int plane, int, float (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                seen.in2 = max(seen.in2, __float_as_uint(v[e]) << 1);
+                seen.add_low(v[e]);
+            }
+            put4(lds, plane, at, v[0], v[1], v[2], v[3]);
+        });
+        // the block's flags: each wave writes its own ahead of a barrier
+        auto collect = [&](uint32_t (&f)[kMWaves], uint32_t mine) __attribute__((always_inline)) {
+            if (lane == 0)
+                f[wave] = mine;
             __syncthreads();
-            if (uni(m.c[l].next_mode) == HPACML_PADMODE_REPLICATE) {
-                replicate_edges(m, m.c[l], lds, y0, x0);
-                __syncthreads();
+            uint32_t all = 0;
+#pragma unroll
+            for (int w = 0; w < kMWaves; ++w)
+                all |= f[w];
+            return (uint32_t)__builtin_amdgcn_readfirstlane(all);
+        };
+        uint32_t met = collect(flags[0], __any(seen.in2 >= limit2) ? 1u : 0u);
+        bool vector = false, gathered = false;
+        if (met) {
+            // an input too large for the split products, or a NaN: these become 0
+            // in the planes, and a bit; with the others, or without the bits, the
+            // tile goes to the vector ALU at once, its requested pixels with it
+            seen.in2 = 0;
+            bool nan = false;
+            pixels([&](int at, int plane, int i, float (&v)[4]) __attribute__((always_inline)) {
+                bool here = false;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    here = here || v[e] != v[e];
+                    v[e] = v[e] != v[e] ? 0.f : v[e];
+                    seen.in2 = max(seen.in2, __float_as_uint(v[e]) << 1);
+                }
+                if (here && nan_off) {
+                    put4(lds, plane, at, v[0], v[1], v[2], v[3]);
+                    const FusedArgs &a = local().f;
+                    const int ry = div_region(i, a.rw_magic[0]), rx = i - ry * a.rw[0];
+                    atomicOr(reinterpret_cast<uint32_t *>(lds + nan_off) + ry * kNanWords + (rx >> 5), 1u << (rx & 31));
+                }
+                nan = nan || here;
+            });
+            met = collect(flags[2], (__any(seen.in2 >= limit2) ? 1u : 0u) | (__any(nan) ? 2u : 0u));
+            vector = (met & 1u) || !nan_off;
+            gathered = vector && pre_on;
+            if (gathered) {
+                float4 *buf0 = reinterpret_cast<float4 *>(lds + mfma_args().planes_off);
+                pixels([&](int, int, int i, float (&v)[4]) __attribute__((always_inline)) { buf0[i] = make_float4(v[0], v[1], v[2], v[3]); });
             }
         }
-        {
-            const MfmaArgs &m = local();
-            if (uni(m.c[n_layers - 1].m16))
-                conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
-            else
-                conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
+        if (pre_on && tile + grid_x < t_end)
+            request(tile + grid_x);
+        if (!vector) {
+            for (int l = 0; l + 1 < n_layers; ++l) {
+                const MfmaArgs &m = local();
+                if (uni(m.c[l].m16))
+                    conv_mfma<true, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
+                else
+                    conv_mfma<false, false>(m, l, lds, tab, wave, lane, s, y0, x0, seen);
+                __syncthreads();
+                if (l == 0 && met) {
+                    nan_outputs(mfma_args(), tab, lds, s, y0, x0);
+                    __syncthreads();
+                }
+                if (uni(m.c[l].next_mode) == HPACML_PADMODE_REPLICATE) {
+                    replicate_edges(m, m.c[l], lds, y0, x0);
+                    __syncthreads();
+                }
+            }
+            {
+                const MfmaArgs &m = local();
+                if (uni(m.c[n_layers - 1].m16))
+                    conv_mfma<true, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
+                else
+                    conv_mfma<false, true>(m, n_layers - 1, lds, tab, wave, lane, s, y0, x0, seen);
+            }
+            // (also the barrier after the last reads of this tile's planes)
+            const uint32_t all = collect(flags[1], seen.flags(limit, least) | tiny);
+            vector = (all & 1u) || (all & 6u) == 6u;
+            if (n_layers == 1 && met && !vector)
+                nan_outputs(mfma_args(), tab, lds, s, y0, x0);
         }
-        // (also the barrier after the last reads of this tile's planes)
-        const uint32_t mine = seen.flags(local().limit, local().least) | (local().tiny ? 4u : 0u);
-        if (lane == 0)
-            flags[tile_no & 1][wave] = mine;
-        __syncthreads();
-        uint32_t all = 0;
-#pragma unroll
-        for (int w = 0; w < kMWaves; ++w)
-            all |= flags[tile_no & 1][w];
-        ++tile_no;
-        all = __builtin_amdgcn_readfirstlane(all);
-        if ((all & 1u) || (all & 6u) == 6u) {
-            // values that the split products can't take
+        if (vector) {
             const MfmaArgs &m = mfma_args();
-            run_tile<kMThreads>(m.f, tab, wts, reinterpret_cast<float *>(lds + m.planes_off), s, y0, x0);
+            float *buf0 = reinterpret_cast<float *>(lds + m.planes_off);
+            if (!gathered)
+                gather_tile<kMThreads>(m.f, tab, buf0, s, y0, x0);
+            run_tile<kMThreads, kFallPix>(m.f, tab, wts, buf0, s, y0, x0);
             __syncthreads();
             clear(m.planes_off, m.planes_bytes);
+            __syncthreads();
+        }
+        if ((met & 2u) && nan_off) {
+            __syncthreads();
+            clear(nan_off, uni(local().nan_bytes));
             __syncthreads();
         }
     }
@@ -1770,6 +1885,8 @@ static size_t mfma_layout(const CnnFused &f, int ty, MfmaArgs *m) {
         c.groups = c.oh * c.ng;
         c.ng_magic = (uint32_t)(((1u << 24) + c.ng - 1) / c.ng);
         c.relu = y.act == HPACML_ACT_RELU;
+        c.kh = y.kh;
+        c.kw = y.kw;
         c.next_mode = l + 1 < f.n_layers ? f.L[l + 1].mode : HPACML_PADMODE_ZEROS;
         c.rt = a.rt[l + 1];
         c.rl = a.rl[l + 1];
@@ -1859,7 +1976,16 @@ hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 
     if (ty == 0)
         return hipErrorInvalidValue;
     MfmaArgs m{};
-    const size_t lds = mfma_layout(f, ty, &m);
+    size_t lds = mfma_layout(f, ty, &m);
+    // NaN bits where there is room and only the first layer can meet one (a ReLU
+    // makes 0 of it)
+    const int nan_bytes = (m.f.rh[0] * kNanWords * 4 + 15) / 16 * 16;
+    if ((f.n_layers == 1 || f.L[0].act == HPACML_ACT_RELU) && lds + nan_bytes + kMStatic <= kLdsOneBlock) {
+        m.nan_off = (int32_t)lds;
+        m.nan_bytes = nan_bytes;
+        lds += nan_bytes;
+    }
+    m.clear_bytes = m.planes_bytes + m.nan_bytes;
     FusedArgs &a = m.f;
     a.in = in;
     a.out = out;

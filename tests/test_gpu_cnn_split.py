@@ -176,3 +176,28 @@ def test_tiny_factors_beside_normal_ones(tiny):
         L[0]["W"][:, 2] /= by
     got, want = _both(w)
     assert _fp32_error(w, got, want) <= 4
+
+
+@pytest.mark.parametrize("cin, layers, acts", [
+    (4, [(8, 5, 5), (4, 3, 3)], None), (4, [(8, 5, 5), (4, 3, 3)], [0, 0]), (3, [(4, 3, 2)], [0]), (4, [(4, 8, 8)], [1]),
+    (4, [(12, 2, 7)], [0]), (8, [(8, 3, 3), (6, 2, 2), (16, 1, 1)], None), (4, [(4, 1, 1), (4, 3, 3)], [1, 1])])
+@pytest.mark.parametrize("mode", ["circular", "zeros", "replicate"])
+@pytest.mark.parametrize("S, H, W", [(1, 50, 140), (2, 5, 9)])
+@pytest.mark.parametrize("where", ["points", "land", "with infinities"])
+def test_nan_pixels(cin, layers, acts, mode, S, H, W, where):
+    """NaN in single pixels, corners among them, in a third of the image, and
+    beside infinities: NaN, or 0 after a ReLU, wherever a window reaches one, and
+    everywhere else the usual accuracy."""
+    w = _workload(cin, layers, mode, S, H, W, seed=9, acts=acts)
+    if where == "land":
+        w.inputs[1 % cin][:, : H // 3 + 1, : W - 3] = np.nan
+    else:
+        for s, y, x in ((0, 0, 0), (0, H - 1, W - 1), (0, H // 2, W // 2), (S - 1, 1, W - 2)):
+            w.inputs[(y + x) % cin][s, y, x] = np.nan
+    if where == "with infinities":
+        w.inputs[0][S - 1, H // 2, 2] = np.inf
+    got, want = _both(w)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    got, want = np.where(np.isfinite(want), got, 0), np.where(np.isfinite(want), want, 0)
+    assert parity_stats(got, want)[0] <= 1e-5
