@@ -1527,7 +1527,8 @@ __global__ void __launch_bounds__(256) cnn_linear_mfma_kernel(CnnLayerDev L, con
 // order, so a K range is four times as long as a 128-image block's for as many
 // blocks, and a quarter as many partial sums go through memory.  What bounds
 // it is the latency of one round of blocks, not the matrix cores.  VEC: rows of
-// whole, aligned float4s.
+// whole, aligned float4s (others read theirs unaligned: 1024 x 4095 -> 256 35 us; one
+// by one they took 49, the 128-image kernel 42).
 constexpr int kFewS = 32, kFewRows = kFewS + kMfO;
 constexpr int kFewPad = kMfK + 4;   // floats a staged row: 16 rows read at once lie in 64 different banks
 template <bool VEC>
@@ -1550,23 +1551,34 @@ __global__ void __launch_bounds__(256) cnn_linear_few_kernel(CnnLayerDev L, cons
     const int lr = lane >> 3, lk = 4 * (lane & 7);
     float *mine = lds + w * kFewRows * kFewPad;
     float4 pre[kFewRows / 8];
+    auto row = [&](int m, int64_t k) __attribute__((always_inline)) {
+        if (8 * m < kFewS) {
+            const int64_t r = s0 + 8 * m + lr;
+            return in + (r < S ? r : S - 1) * K + k;
+        }
+        const int r = o0 + 8 * m - kFewS + lr;
+        return L.W + (int64_t)(r < O ? r : O - 1) * K + k;
+    };
+    // (a 16-byte load needs 4-byte alignment only)
+    typedef float rowx4 __attribute__((ext_vector_type(4), aligned(4)));
     auto fetch = [&](int64_t k0) {
         const int64_t k = k0 + lk;
+        if (VEC || k + 3 < ke) {
 #pragma unroll
-        for (int m = 0; m < kFewRows / 8; ++m) {
-            const float *p;
-            if (8 * m < kFewS) {
-                const int64_t r = s0 + 8 * m + lr;
-                p = in + (r < S ? r : S - 1) * K + k;
-            } else {
-                const int r = o0 + 8 * m - kFewS + lr;
-                p = L.W + (int64_t)(r < O ? r : O - 1) * K + k;
+            for (int m = 0; m < kFewRows / 8; ++m) {
+                if (VEC) {
+                    pre[m] = k < ke ? *reinterpret_cast<const float4 *>(row(m, k)) : make_float4(0.f, 0.f, 0.f, 0.f);
+                } else {
+                    const rowx4 v = *reinterpret_cast<const rowx4 *>(row(m, k));
+                    pre[m] = make_float4(v[0], v[1], v[2], v[3]);
+                }
             }
-            if (VEC)
-                pre[m] = k < ke ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
-            else
-                pre[m] = make_float4(k < ke ? p[0] : 0.f, k + 1 < ke ? p[1] : 0.f, k + 2 < ke ? p[2] : 0.f,
-                                     k + 3 < ke ? p[3] : 0.f);
+        } else {
+#pragma unroll
+            for (int m = 0; m < kFewRows / 8; ++m) {
+                const float *p = row(m, k);
+                pre[m] = make_float4(k < ke ? p[0] : 0.f, k + 1 < ke ? p[1] : 0.f, k + 2 < ke ? p[2] : 0.f, 0.f);
+            }
         }
     };
     floatx16 acc[2];
