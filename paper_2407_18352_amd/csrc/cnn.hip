@@ -2162,10 +2162,12 @@ int linear_splits(const CnnLayerDev &L, int64_t S) {
     const int64_t K = (int64_t)L.h * L.w * L.cin;
     const int64_t T = linear_tile(L);
     if (split_few(L, S)) {
-        // about 256 blocks, each at least one 32-k step per wave (more ranges for a
-        // long K, 1024 each: 32768 -> 33 on 1024 images 104 us against 99)
+        // at most 256 blocks, one round of them (a few more: 4096 -> 128 on 1400
+        // images 39.7 us in 264 blocks, 33.5 in 176; on 2000 42.0 in 378, 34.7 in
+        // 252), each at least one 32-k step per wave (more ranges for a long K, 1024
+        // each: 32768 -> 33 on 1024 images 104 us against 99)
         const int64_t tiles = few_tiles(L, S);
-        return (int)std::min<int64_t>(std::min<int64_t>((256 + tiles - 1) / tiles, K / 128), kLinSplit);
+        return (int)std::min<int64_t>(std::min<int64_t>(256 / tiles, K / 128), kLinSplit);
     }
     // split products of layers with more than 16 outputs run on the MFMA
     // kernel's 128 x 64 tiles
@@ -2182,10 +2184,10 @@ int64_t linear_part_rows(const CnnLayerDev &L, int64_t S) {
         return 0;
     if (!split_few(L, S))
         return z * S;
-    // z S < 256 S / tiles + S and S / tiles <= 32 / (output tiles): growing with S,
-    // so a workspace made for more images serves fewer
+    // z S <= 256 S / tiles and S / tiles <= 32 / (output tiles): growing with S, so a
+    // workspace made for more images serves fewer
     const int64_t K = (int64_t)L.h * L.w * L.cin, to = (L.cout + kMfO - 1) / kMfO;
-    return std::min<int64_t>(std::min<int64_t>(K / 128, kLinSplit) * S, 256 * kFewS / to + 1 + S);
+    return std::min<int64_t>(std::min<int64_t>(K / 128, kLinSplit) * S, 256 * kFewS / to);
 }
 
 // pooled pixels take groups of 2^qshift lanes: windows of at most 16

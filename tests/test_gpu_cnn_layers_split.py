@@ -33,7 +33,7 @@ def _both(S, H, W, layers, n_out, seed):
 
 @pytest.mark.parametrize("S, H, W, out", [
     (1, 16, 16, 17), (31, 16, 16, 64), (33, 16, 17, 65), (100, 17, 19, 33), (1, 29, 40, 256), (1024, 17, 19, 33),
-    (100, 29, 40, 256), (4096, 16, 16, 17), (4097, 16, 16, 17)])   # the last by the 128-image kernel
+    (100, 29, 40, 256), (1400, 16, 31, 128), (2720, 13, 21, 64), (4096, 16, 16, 17), (4097, 16, 16, 17)])   # the last by the 128-image kernel
 def test_linear(S, H, W, out):
     layers = [wl.linear_layer(61, 0, H * W, out), wl.linear_layer(62, 0, out, 3, act=0)]
     got, want = _both(S, H, W, layers, 3, seed=S + out)
