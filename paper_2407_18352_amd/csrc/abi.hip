@@ -1033,7 +1033,7 @@ const char *kernel_name(const hpacml_model *model, bool fast, int64_t n_points) 
     if (fast && model->variant != Variant::Generic)
         return model->fast_name.c_str();
     // (the layer-by-layer path's name too where all layers run in one kernel)
-    if ((fast && model->wide) || layers_ready(model->layers, n_points))
+    if ((fast && model->wide && f32w_serves(model->f32w, n_points)) || layers_ready(model->layers, n_points))
         return layers_name(model->layers);
     return model->compute == HPACML_BF16 ? "mlp_generic_bf16" : "mlp_generic_f32";
 }
@@ -1180,8 +1180,9 @@ hpacml_status hpacml_infer(const hpacml_model *model, const hpacml_map *in, cons
     case Variant::BF16: e = launch_mlp_bf16(in->m32, out->m32, in->tab, out->tab, model->bf16, st); break;
     case Variant::BF16R: e = launch_mlp_bf16r(in->m32, out->m32, in->tab, out->tab, model->bf16r, st); break;
     default:
-        e = fast && model->wide ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
-                                : launch_general(model, in->dev, out->dev, st);
+        e = fast && model->wide && f32w_serves(model->f32w, in->plan.n_points)
+                ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
+                : launch_general(model, in->dev, out->dev, st);
         break;
     }
     return hip_status(e);

@@ -88,8 +88,18 @@ __global__ void __launch_bounds__(512, 2) mlp_f32w_kernel(Map32 in, Map32 out, F
     {
         const u32x4 *src = reinterpret_cast<const u32x4 *>(pk.image);
         const int n4 = lay.image_lds(LOG) / 16;
-        for (int i = threadIdx.x; i < n4; i += blockDim.x)
-            lds4[i] = src[i];
+        // eight loads in flight: few points wait for this (9-256-128-1 on 200: 20.0 -> 18.0 us,
+        // 9-200-1 7.1 -> 6.6)
+        for (int i = threadIdx.x; i < n4; i += 8 * blockDim.x) {
+            u32x4 q[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                q[k] = src[min(i + k * (int)blockDim.x, n4 - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i + k * (int)blockDim.x < n4)
+                    lds4[i + k * blockDim.x] = q[k];
+        }
     }
     __syncthreads();
 
@@ -435,6 +445,15 @@ void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
         }
     for (int o = 0; o < kFoutMax; ++o)
         reinterpret_cast<float *>(img + lay.out_b())[o] = o < O ? b[n_layers - 1][o] : FLT_MAX;   // (never below `least`)
+}
+
+// Few points wait for one tile's chain of passes, each with the first layer again:
+// from eight passes over two blocks on the layer-by-layer path is shorter, where
+// its library product takes the few inputs in one step (1,000 points, layer by
+// layer / here: 9-64-448-1 20.8 / 20.8 us, 9-40-512-1 20.6 / 23.5, 12-40-512-1 20.7 /
+// 23.4, 14-64-448-1 29.9 / 21; 8,000 points of 9-33-512-1 26.1 / 23.5).
+bool f32w_serves(const F32WPacked &pk, int64_t n_points) {
+    return pk.nb1 < 2 || pk.nb2 <= 14 || pk.dims[0] >= 14 || n_points > 4096;
 }
 
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,

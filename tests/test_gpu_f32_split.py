@@ -55,8 +55,9 @@ def test_shapes_against_64_bits(dims, n):
     [5, 129, 1], [16, 1000, 5], [48, 300, 8],                 # one hidden layer: one and three K-steps, two output groups
     [9, 200, 50, 1], [16, 257, 32, 4], [17, 160, 64, 5],      # two: one and two blocks of the second a pass
     [9, 5, 300, 2], [1, 33, 225, 1],                          # several passes, the last with an empty block
-    [9, 400, 64, 1], [20, 129, 65, 3]])                       # lo parts in global memory
-@pytest.mark.parametrize("n", [1, 33, 3001, 70001])
+    [9, 400, 64, 1], [20, 129, 65, 3],                        # lo parts in global memory
+    [9, 40, 512, 1], [14, 64, 512, 1]])                       # eight passes: the first layer by layer on up to 4096 points
+@pytest.mark.parametrize("n", [1, 33, 3001, 4096, 4097, 70001])
 def test_any_widths_against_64_bits(dims, n):
     g = np.random.default_rng(sum(dims) + n)
     w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
