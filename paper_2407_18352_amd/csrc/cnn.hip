@@ -1834,6 +1834,8 @@ static void mfma_shape(const CnnFusedLayer &y, ConvM *c) {
     c->steps = (c->chunks + kc - 1) / kc;
 }
 
+static double mfma_tile_cycles(const CnnFused &f, int ty);
+
 bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *b, CnnFused &f,
                    std::vector<uint8_t> &buf) {
     buf.clear();
@@ -1846,6 +1848,8 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
     f.limit = range.limit;
     f.least = range.least;
     f.tiny = range.tiny;
+    for (int ty = 1; ty <= kMaxTileRows; ++ty)
+        f.cycles[ty] = mfma_tile_cycles(f, ty);
     for (int l = 0; l < f.n_layers; ++l) {
         ConvM c{};
         mfma_shape(f.L[l], &c);
@@ -1939,6 +1943,24 @@ static size_t mfma_layout(const CnnFused &f, int ty, MfmaArgs *m) {
     return (size_t)off + m->planes_bytes;
 }
 
+// Cycles of a tile of `ty` rows (see cnn_mfma_tile_rows), 0 where it doesn't fit.
+static double mfma_tile_cycles(const CnnFused &f, int ty) {
+    MfmaArgs m{};
+    if (mfma_layout(f, ty, &m) + kMStatic > kLdsOneBlock)
+        return 0;
+    for (int l = 0; l <= f.n_layers; ++l)   // the divisions' ranges (see launch_cnn_fused)
+        if (m.f.rh[l] >= 256 || m.f.rw[l] > 256)
+            return 0;
+    double cycles = 9500 + 8.2 * m.f.rh[0] * m.f.rw[0];
+    for (int l = 0; l < f.n_layers; ++l) {
+        const ConvM &c = m.c[l];
+        const int n = c.m16 ? 16 : 32, each = c.m16 ? 2 : 1;   // columns of a tile, tiles at a time
+        const int rounds = ((c.groups + n * each - 1) / (n * each) + kMWaves - 1) / kMWaves;
+        cycles += (double)rounds * each * c.steps * 6 * n;
+    }
+    return cycles;
+}
+
 // Tile rows of the matrix-core form for S images, or 0 where the vector ALU
 // kernel serves: no tile fits the LDS, or a large image and a stack with so few
 // multiplications that both wait for memory (2048 x 2048, 2 x 2 + 2 x 2 on 4
@@ -1950,31 +1972,14 @@ int cnn_mfma_tile_rows(const CnnFused &f, int32_t S, int32_t H, int32_t W) {
     int64_t taps = 0;   // multiplications per pixel
     for (int l = 0; l < f.n_layers; ++l)
         taps += 16 * f.L[l].kh * f.L[l].kw * f.L[l].cin4 * f.L[l].cout4;
-    if (taps <= 208 && (int64_t)S * H * W >= 3 << 20)
+    if (!f.image || (taps <= 208 && (int64_t)S * H * W >= 3 << 20))
         return 0;
     int best = 0;
     double least = 0;
-    for (int ty = 1; ty <= 32; ++ty) {
-        if (ty > 1 && ty > H)
-            break;
-        MfmaArgs m{};
-        if (mfma_layout(f, ty, &m) + kMStatic > kLdsOneBlock)
-            continue;
-        bool fits = true;   // the divisions' ranges (see launch_cnn_fused)
-        for (int l = 0; l <= f.n_layers; ++l)
-            fits = fits && m.f.rh[l] < 256 && m.f.rw[l] <= 256;
-        if (!fits)
-            continue;
-        double cycles = 9500 + 8.2 * m.f.rh[0] * m.f.rw[0];
-        for (int l = 0; l < f.n_layers; ++l) {
-            const ConvM &c = m.c[l];
-            const int n = c.m16 ? 16 : 32, each = c.m16 ? 2 : 1;   // columns of a tile, tiles at a time
-            const int rounds = ((c.groups + n * each - 1) / (n * each) + kMWaves - 1) / kMWaves;
-            cycles += (double)rounds * each * c.steps * 6 * n;
-        }
+    for (int ty = 1; ty <= kMaxTileRows && (ty == 1 || ty <= H); ++ty) {
         const double tiles = (double)S * ((H + ty - 1) / ty) * ((W + kTX - 1) / kTX);
-        const double t = std::ceil(tiles / 256) * cycles;
-        if (!best || t < least) {
+        const double t = std::ceil(tiles / 256) * f.cycles[ty];
+        if (f.cycles[ty] > 0 && (!best || t < least)) {
             best = ty;
             least = t;
         }
@@ -1983,10 +1988,7 @@ int cnn_mfma_tile_rows(const CnnFused &f, int32_t S, int32_t H, int32_t W) {
 }
 
 hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 *tin, const FeatTable32 *tout,
-                           const CnnFused &f, int32_t S, int32_t H, int32_t W, hipStream_t stream) {
-    const int ty = cnn_mfma_tile_rows(f, S, H, W);
-    if (ty == 0)
-        return hipErrorInvalidValue;
+                           const CnnFused &f, int32_t S, int32_t H, int32_t W, int ty, hipStream_t stream) {
     MfmaArgs m{};
     size_t lds = mfma_layout(f, ty, &m);
     // NaN bits where there is room and only the first layer can meet one (a ReLU
@@ -2064,8 +2066,9 @@ hipError_t launch_cnn_mfma(const Map32 &in, const Map32 &out, const FeatTable32 
 
 hipError_t launch_cnn_fused(const Map32 &in, const Map32 &out, const FeatTable32 *tin, const FeatTable32 *tout,
                             const CnnFused &f, int32_t S, int32_t H, int32_t W, hipStream_t stream) {
-    if (f.image && cnn_mfma_tile_rows(f, S, H, W) > 0)
-        return launch_cnn_mfma(in, out, tin, tout, f, S, H, W, stream);
+    const int rows = cnn_mfma_tile_rows(f, S, H, W);
+    if (rows > 0)
+        return launch_cnn_mfma(in, out, tin, tout, f, S, H, W, rows, stream);
     const int ty = cnn_fused_tile_rows(f, H);
     if (ty == 0)
         return hipErrorInvalidValue;

@@ -70,6 +70,7 @@ struct CnnFusedLayer {
     int32_t mode;                  // padding mode of this layer's input
     int32_t woff, boff;            // float offsets of the packed weights / biases
 };
+constexpr int kMaxTileRows = 32;
 struct CnnFused {
     int32_t n_layers = 0, c0 = 0, cout_last = 0, circular = 0;
     CnnFusedLayer L[kCnnFusedMaxLayers]{};
@@ -77,6 +78,7 @@ struct CnnFused {
     // ... a layer's inputs from `limit` on: the tile on the vector ALU; also outputs below `least` where a value (`tiny`: a weight) lost bits
     float limit = 0, least = 0;
     int32_t tiny = 0;
+    double cycles[kMaxTileRows + 1]{};  // ... of a tile by its rows (0: doesn't fit)
     const float *wts = nullptr;    // device: per layer [cout4][ky][kx][cin4*4][4], then bias [cout4*4]
 };
 bool cnn_fused_supported(const CnnPlan &p);
