@@ -417,8 +417,11 @@ hpacml_status hpacml_infer_noalloc(const hpacml_model *model, const hpacml_map *
 
 /* Name of the kernel hpacml_infer would launch for these handles (a static
  * string, prefixed "snapshot+" when the inputs are copied first; the
- * layer-by-layer path is "mlp_layers_f32" / "mlp_layers_bf16"), or NULL when
- * the arguments are invalid.  Allocates no device buffer; for a model that
+ * layer-by-layer path is "mlp_layers_f32" / "mlp_layers_bf16", the fp32 kernel
+ * for one or two hidden layers of other widths "mlp_f32w", the fused
+ * convolution kernel "cnn_fused_f32" on the matrix cores and
+ * "cnn_fused_valu_f32" on the vector ALU), or NULL when the arguments are
+ * invalid.  Allocates no device buffer; for a model that
  * runs layer by layer it selects the matmul library's algorithms for this
  * point count (host work, cached with the model). */
 const char *hpacml_infer_variant(const hpacml_model *model, const hpacml_map *in,

@@ -1032,8 +1032,9 @@ bool snapshot_t32(const hpacml_map *in) {
 const char *kernel_name(const hpacml_model *model, bool fast, int64_t n_points) {
     if (fast && model->variant != Variant::Generic)
         return model->fast_name.c_str();
-    // (the layer-by-layer path's name too where all layers run in one kernel)
-    if ((fast && model->wide && f32w_serves(model->f32w, n_points)) || layers_ready(model->layers, n_points))
+    if (fast && model->wide && f32w_serves(model->f32w, n_points))
+        return "mlp_f32w";
+    if (layers_ready(model->layers, n_points))
         return layers_name(model->layers);
     return model->compute == HPACML_BF16 ? "mlp_generic_bf16" : "mlp_generic_f32";
 }
@@ -1062,6 +1063,13 @@ hpacml_status take_snapshot(const hpacml_map *in, hipStream_t st, const hpacml_m
         return hip_status(launch_collect32(&j, 1, st));
     }
     return hpacml_collect(in, in->snap, in->plan.n_features, st);
+}
+
+// the form of the fused convolution kernel: matrix cores or vector ALU
+const char *cnn_fused_name(const hpacml_model *model, const hpacml_map *in) {
+    const CnnPlan &c = model->cnnp;
+    const int64_t S = in->plan.n_points / ((int64_t)c.height * c.width);
+    return cnn_mfma_tile_rows(model->fused, (int32_t)S, c.height, c.width) > 0 ? "cnn_fused_f32" : "cnn_fused_valu_f32";
 }
 
 // "snapshot+" prefixed names, kept for the life of the process
@@ -1144,8 +1152,8 @@ const char *hpacml_infer_variant(const hpacml_model *model, const hpacml_map *in
     if (check_infer(model, in, out, &snapshot) != HPACML_OK)
         return nullptr;
     if (model->cnn)
-        return cnn_use_fused(model, in, out)           ? "cnn_fused_f32"
-               : cnn_fused_on_snapshot(model, in, out) ? "snapshot+cnn_fused_f32"
+        return cnn_use_fused(model, in, out)           ? cnn_fused_name(model, in)
+               : cnn_fused_on_snapshot(model, in, out) ? snapshot_name(cnn_fused_name(model, in))
                                                        : "cnn_layers_f32";
     if (!snapshot)
         return kernel_name(model, in->t32 && out->t32, in->plan.n_points);

@@ -103,7 +103,7 @@ def test_fused_random_stacks(case):
     outputs = [wl.sentinel_like((S, H, W)) for _ in range(cout)]
     w = wl.Workload("random", 0, "f32", [cin, cout], spec, spec, inputs, outputs, model)
     got, var = _run(w)
-    assert var == "cnn_fused_f32", var
+    assert var in ("cnn_fused_f32", "cnn_fused_valu_f32"), var   # wide stacks: weights beyond the LDS
     _compare(got, _expected(w), "case %d (%s, %d layers, %dx%dx%d)" % (case, family, n_layers, S, H, W),
              _rtol_for(model))
 

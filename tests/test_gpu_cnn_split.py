@@ -34,9 +34,9 @@ def _workload(cin, layers, mode, S, H, W, seed=0, acts=None):
                        [wl.sentinel_like((S, H, W)) for _ in range(c)], model)
 
 
-def _both(w):
+def _both(w, path="cnn_fused_f32"):
     got, var = _run(w)
-    assert var == "cnn_fused_f32", var
+    assert var == path, var
     exp = [a.copy() for a in w.outputs]
     oracle.infer(w.in_spec, w.inputs, w.out_spec, exp, w.model)
     return np.stack([a.reshape(-1) for a in got], 1), np.stack([a.reshape(-1) for a in exp], 1)
@@ -96,11 +96,26 @@ def test_tiny_images(exponent):
     assert nan == 0 and worst <= 1e-5, worst
 
 
-def test_weight_without_a_split():
-    w = _workload(4, [(8, 3, 3), (4, 3, 3)], "circular", 1, 40, 70, seed=3)
-    w.model["layers"][0]["W"][3, 1, 1, 2] = 2.0 ** 127
+@pytest.mark.parametrize("layers, mode", [
+    ([(8, 3, 3), (4, 3, 3)], "circular"), ([(8, 3, 3), (4, 3, 3)], "zeros"), ([(8, 3, 3), (4, 3, 3)], "replicate"),
+    ([(6, 4, 2), (13, 3, 3), (7, 2, 2), (2, 3, 1)], "zeros"), ([(9, 2, 3), (4, 1, 5), (3, 3, 3)], ["zeros", "replicate", "zeros"])])
+def test_weight_without_a_split(layers, mode):
+    """The vector ALU form."""
+    w = _workload(4, layers, mode, 2, 40, 70, seed=3)
+    w.model["layers"][0]["W"][3, 1, 0, 1] = 2.0 ** 127
     w.inputs[1] *= np.float32(2.0 ** -126)
-    got, want = _both(w)
+    got, want = _both(w, "cnn_fused_valu_f32")
+    assert parity_stats(got, want)[0] <= 1e-5
+
+
+@pytest.mark.parametrize("layers, H, W, path", [
+    ([(4, 3, 3), (4, 2, 2)], 1536, 2048, "cnn_fused_valu_f32"), ([(4, 3, 3), (4, 2, 2)], 1535, 2048, "cnn_fused_f32"),
+    ([(4, 3, 3), (4, 2, 2), (4, 1, 1)], 1536, 2048, "cnn_fused_f32")])
+def test_large_images_with_few_multiplications(layers, H, W, path):
+    """The vector ALU serves from 3 x 2^20 pixels on and up to 208 multiplications a
+    pixel (13 x 16): both sides of the line."""
+    w = _workload(4, layers, "circular", 1, H, W, seed=4)
+    got, want = _both(w, path)
     assert parity_stats(got, want)[0] <= 1e-5
 
 

@@ -61,7 +61,8 @@ def test_shapes_against_64_bits(dims, n):
 def test_any_widths_against_64_bits(dims, n):
     g = np.random.default_rng(sum(dims) + n)
     w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
-    got, want = _run(w, "mlp_layers_f32")
+    few = dims[1] > 32 and dims[-2] > 448 and len(dims) == 4 and dims[0] < 14 and n <= 4096
+    got, want = _run(w, "mlp_layers_f32" if few else "mlp_f32w")
     worst, norm, nan = parity_stats(got, want)
     assert nan == 0 and worst <= 4 * 4 * _bound(dims), (dims, worst, _bound(dims))
     if n > 1000:
@@ -249,3 +250,37 @@ def test_fp32_path_in_each_weight_form(dims, form):
     w.inputs = [x[rows] for x in w.inputs]
     w.in_spec = wl.pointwise_spec(int(rows.sum()))
     assert _fp32_error(w, got[rows], want[rows]) <= 4
+
+
+@pytest.mark.parametrize("dims", [[9, 300, 40, 2], [12, 160, 7], [9, 40, 512, 1]])
+def test_any_widths_without_allocation(dims):
+    """The same kernel, and the same bits, through hpacml_infer_noalloc; on maps
+    outside the 32-bit form (one input strided) both take the other paths."""
+    import torch
+    from paper_2407_18352_amd import _abi, api
+    n = 5000
+    g = np.random.default_rng(dims[1])
+    w = _workload(dims, n, [g.uniform(-1, 1, n).astype(np.float32) for _ in range(dims[0])])
+    want = oracle.infer_rows(w.in_spec, w.inputs, w.model)
+    m = api.Model(w.model)
+    for strided in (False, True):
+        ins = [torch.from_numpy(a).cuda() for a in w.inputs]
+        if strided:
+            ins[1] = torch.stack([ins[1], ins[1]], 1)[:, 0]
+        got = []
+        for noalloc in (False, True):
+            outs = [torch.zeros(n, device="cuda") for _ in range(dims[-1])]
+            mi, mo = api.Map(w.in_spec, ins, _abi.TO), api.Map(w.out_spec, outs, _abi.FROM)
+            assert api.variant(m, mi, mo) == ("mlp_layers_f32" if strided else "mlp_f32w")
+            if noalloc:
+                st = torch.cuda.current_stream().cuda_stream
+                assert _abi.lib().hpacml_infer_noalloc(m.handle, mi.handle, mo.handle, st) == _abi.OK
+            else:
+                api.infer(m, mi, mo)
+            torch.cuda.synchronize()
+            got.append(np.stack([o.cpu().numpy() for o in outs], 1))
+            assert parity_stats(got[-1], want)[0] <= 1e-5
+            mi.close(), mo.close()
+        if not strided:
+            assert np.array_equal(got[0].view(np.uint32), got[1].view(np.uint32))
+    m.close()
