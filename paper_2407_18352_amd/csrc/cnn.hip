@@ -428,18 +428,8 @@ static_assert(sizeof(MfmaArgs) + sizeof(TabLds) + 3 * kMWaves * 4 <= kMStatic, "
 // v0..v3 split into the three planes at byte `at` (four bf16 each).
 __device__ __forceinline__ void put4(char *base, int plane, int at, float v0, float v1, float v2, float v3) {
     uint32_t q[3][2];
-    const float v[4] = {v0, v1, v2, v3};
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
-        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
-        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
-        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
-        q[0][i] = h;
-        q[1][i] = m;
-        q[2][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
-    }
+    split2(v0, v1, q[0][0], q[1][0], q[2][0]);
+    split2(v2, v3, q[0][1], q[1][1], q[2][1]);
 #pragma unroll
     for (int p = 0; p < 3; ++p)
         *reinterpret_cast<uint2 *>(base + at + p * plane) = make_uint2(q[p][0], q[p][1]);
@@ -1872,10 +1862,7 @@ bool cnn_mfma_pack(const CnnPlan &p, const float *const *W, const float *const *
                         continue;
                     const float w = W[l][(((size_t)o * cin + i) * kh + ky) * kw + kx];
                     uint16_t *d = reinterpret_cast<uint16_t *>(&buf[at + 64 + (size_t)st * 3 * kFragBytes]) + lane * 8 + j;
-                    d[0] = rne(w);
-                    const float r = w - bf16_float(d[0]);
-                    d[kFragBytes / 2] = rne(r);
-                    d[kFragBytes] = rne(r - bf16_float(d[kFragBytes / 2]));
+                    split_parts(w, d[0], d[kFragBytes / 2], d[kFragBytes]);
                 }
             }
     }

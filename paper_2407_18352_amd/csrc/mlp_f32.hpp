@@ -133,7 +133,17 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
     }
 }
 
-// Eight floats as three B fragments, v = hi + mid + lo exactly (see above).
+// Two floats in three bf16 parts each (a in the lower halves), v = hi + mid + lo
+// (exactly, see mlp_f32.hip).
+__device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+    m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
+    const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
+}
+
+// Eight floats as three B fragments.
 struct Split {
     u32x4 hi, mid, lo;
 };
@@ -141,14 +151,11 @@ __device__ __forceinline__ Split split8(floatx8 v) {
     Split f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
-        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
-        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-        const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){ra, rb}, bf16x2));
-        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+        uint32_t h, m, l;
+        split2(v[2 * i], v[2 * i + 1], h, m, l);
         f.hi[i] = h;
         f.mid[i] = m;
-        f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){la, lb}, bf16x2));
+        f.lo[i] = l;
     }
     return f;
 }
@@ -445,6 +452,12 @@ inline uint16_t rne(float x) {
     return (uint16_t)((u + 0x7FFFu + (u >> 16 & 1u)) >> 16);
 }
 inline float bf16_float(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
+inline void split_parts(float w, uint16_t &h, uint16_t &m, uint16_t &l) {
+    h = rne(w);
+    const float r = w - bf16_float(h);
+    m = rne(r);
+    l = rne(r - bf16_float(m));
+}
 
 // One layer's A fragments: K-step s, m-block mb, lane l, element j is weight
 // [32 mb + l % 32][feature(s, l / 32, j)] (zero past N rows and K columns), its
@@ -458,13 +471,8 @@ inline void put_layer(char *img, const float *W, int N, int K, int steps, int bl
     const size_t n = (size_t)N * K;
     std::vector<uint16_t> q(plain ? 0 : 3 * n);
     uint16_t *qh = q.data(), *qm = qh + n, *ql = qm + n;
-    for (size_t i = 0; !plain && i < n; ++i) {
-        const float w = W[i];
-        qh[i] = rne(w);
-        const float r = w - bf16_float(qh[i]);
-        qm[i] = rne(r);
-        ql[i] = rne(r - bf16_float(qm[i]));
-    }
+    for (size_t i = 0; !plain && i < n; ++i)
+        split_parts(W[i], qh[i], qm[i], ql[i]);
     for (int s = 0; s < steps; ++s) {
         int at[2][8];
         for (int g = 0; g < 2; ++g)
