@@ -37,6 +37,7 @@ sys.path.insert(0, ROOT)
 
 PEAK = {"f32": 157.3e12, "bf16": 2.5e15}   # dense MFMA peaks of MI355X, flop/s
 VALU_F32_PEAK = 157.3e12                   # published fp32 vector peak (packed FMA; see the design notes)
+SPLIT_F32_PEAK = PEAK["bf16"] / 6          # fp32 products as six bf16 products of three-way splits
 HBM_PEAK = 8.0e12                          # bytes/s
 IC_BYTES = 256 << 20                       # Infinity Cache
 HEADLINE = "stencil3d"
@@ -61,13 +62,14 @@ DESCRIPTION = {
 
 KERNEL_SOURCES = {
     "collect": ["collect.hip", "device.hpp", "kernels.hpp"],
-    "mlp_f32": ["mlp_f32.hip", "device.hpp", "kernels.hpp"],
+    "mlp_f32w": ["mlp_f32w.hip", "mlp_f32.hpp", "device.hpp", "kernels.hpp"],   # (the first prefix that fits counts)
+    "mlp_f32": ["mlp_f32.hip", "mlp_f32.hpp", "device.hpp", "kernels.hpp"],
     "mlp_bf16r": ["mlp_bf16r.hip", "mlp_bf16r.hpp", "mlp_bf16r_h256_nh1.hip", "mlp_bf16r_h256_nh2.hip",
                   "mlp_bf16r_h256_nh3.hip", "device.hpp", "kernels.hpp"],
     "mlp_bf16": ["mlp_bf16.hip", "device.hpp", "kernels.hpp"],
     "mlp_generic": ["mlp_generic.hip", "device.hpp", "kernels.hpp"],
     "mlp_layers": ["mlp_layers.hip", "layers.hpp", "device.hpp"],
-    "cnn_": ["cnn.hip", "cnn.hpp", "device.hpp", "kernels.hpp"],
+    "cnn_": ["cnn.hip", "cnn.hpp", "mlp_f32.hpp", "device.hpp", "kernels.hpp"],
 }
 
 
@@ -257,10 +259,12 @@ class Run:
         if self.is_cnn:
             H, W = w.model["image"]
             flop_launch = wl.cnn_flops_per_image(w.model) * (B // (H * W))
-            peak, bound = VALU_F32_PEAK, "alu"
+            split = self.variant.endswith("cnn_fused_f32")
+            peak, bound = (SPLIT_F32_PEAK, "mfma") if split else (VALU_F32_PEAK, "alu")
         else:
             flop_launch = w.flops_per_point * B
-            peak, bound = PEAK[w.compute], "mfma"
+            split = "mlp_f32" in self.variant
+            peak, bound = SPLIT_F32_PEAK if split else PEAK[w.compute], "mfma"
         achieved = flop_launch / (self.infer_avg * 1e-3)
         if self.hbm_bound:
             peak, bound = HBM_PEAK, "hbm"

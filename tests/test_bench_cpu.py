@@ -61,3 +61,19 @@ def test_profiles_name_their_commands_and_parse():
                 kernels.add((kv["kernel"], kv["workload"]))
     for name in ("bonds", "options", "stencil2d", "poses", "stencil3d", "weather_cnn", "particle_cnn"):
         assert ("collect", name) in kernels, name
+
+
+def test_every_kernel_source_belongs_to_a_family():
+    """A kernel's counters count as current while its sources' hash holds: each
+    family names the source of its kernels and the headers these include from
+    the same folder."""
+    import re
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_2407_18352_amd", "csrc")
+    for family, files in bench.KERNEL_SOURCES.items():
+        for f in files:
+            for inc in re.findall(r'^#include "(\w+\.hpp)"', open(os.path.join(csrc, f)).read(), re.M):
+                assert inc in files or inc == "plan.hpp", (family, f, inc)
+    assert bench.source_sha("mlp_f32w") != bench.source_sha("mlp_f32_h64_k16")
+    assert bench.source_sha("cnn_fused_valu_f32") == bench.source_sha("cnn_fused_f32") is not None
