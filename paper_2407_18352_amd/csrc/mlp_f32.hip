@@ -22,9 +22,10 @@
 // fp32 instruction: 9-128-128-128-1 on 1,048,576 points 537 -> 315 us,
 // 36-128-128-4 on 2048 x 2048 windows 1680 -> 862 us, 5-64-64-1 on 65,536
 // points 10.2 -> 7.3 us; error against 64 bits (2-norm) 1.6e-7 -> 0.8e-7,
-// 3.0e-7 -> 1.4e-7, 2.4e-7 -> 1.5e-7.  What bounds it: bf16 matrix operations
-// at the power limit (the two larger ones run 1.36 PFLOP/s of them; a 16384^3
-// bf16 product runs 1.32).
+// 3.0e-7 -> 1.4e-7, 2.4e-7 -> 1.5e-7.  What bounds it: bf16 matrix operations (the
+// two larger ones run 1.36 PFLOP/s of them, a 16384^3 bf16 product 1.32; counters:
+// matrix cores busy 60 and 62% of the cycles at a clock that the load lowers to 2.1
+// and 1.9 GHz).
 //
 // Layouts: in the 32x32 C layout lane l holds point l % 32 and, in register r
 // of m-block mb, feature 32 mb + 8 (r / 4) + 4 (l / 32) + r % 4.  Registers 8t ..

@@ -9,14 +9,17 @@
 // multiplied into the accumulators of the second (two K-steps of it), or, with
 // one hidden layer, into the output sums; so its width costs time but no
 // registers.  The second layer's neurons go in passes of 32 G (G = 1 or 2)
-// for which the first layer is computed again (a sixth of the work where
-// it has one K-step), so its width costs no registers either.
+// for which the first layer is computed again (6 of the 30 matrix instructions
+// per block and pass where it has one K-step, 6 of 18 with G = 1), so its width
+// costs no registers either.
 //
 // The block of neurons j + 1 is computed between the split of block j and its
 // products, so that its activation and split (vector ALU) can run beside the
-// products of block j.  Measured, 9-200-50-1 on 1,048,576 points: 761 us layer
-// by layer (three launches, the rows of both hidden layers through memory) ->
-// see the launch rule below.
+// products of block j.  Measured, 9-200-50-1 on 1,048,576 points: 758 us layer
+// by layer (three launches, the rows of both hidden layers through memory), 167
+// here; 9-200-1 471 / 73, 48-160-96-8 1402 / 422, 9-32-512-1 1147 / 330; on 65,536
+// points 9-200-50-1 50 / 14.1.  What bounds it: matrix operations, a fifth of them
+// padding, and the splits' vector instructions beside them.
 #include "mlp_f32.hpp"
 
 namespace hpacml {
