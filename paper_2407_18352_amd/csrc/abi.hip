@@ -1032,7 +1032,7 @@ bool snapshot_t32(const hpacml_map *in) {
 const char *kernel_name(const hpacml_model *model, bool fast, int64_t n_points) {
     if (fast && model->variant != Variant::Generic)
         return model->fast_name.c_str();
-    if (fast && model->wide && f32w_serves(model->f32w, n_points))
+    if (fast && model->wide)
         return "mlp_f32w";
     if (layers_ready(model->layers, n_points))
         return layers_name(model->layers);
@@ -1188,9 +1188,8 @@ hpacml_status hpacml_infer(const hpacml_model *model, const hpacml_map *in, cons
     case Variant::BF16: e = launch_mlp_bf16(in->m32, out->m32, in->tab, out->tab, model->bf16, st); break;
     case Variant::BF16R: e = launch_mlp_bf16r(in->m32, out->m32, in->tab, out->tab, model->bf16r, st); break;
     default:
-        e = fast && model->wide && f32w_serves(model->f32w, in->plan.n_points)
-                ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
-                : launch_general(model, in->dev, out->dev, st);
+        e = fast && model->wide ? launch_mlp_f32w(in->m32, out->m32, in->tab, out->tab, model->f32w, st)
+                                : launch_general(model, in->dev, out->dev, st);
         break;
     }
     return hip_status(e);

@@ -98,8 +98,6 @@ bool f32w_supported(int n_layers, const int32_t *dims, int compute);
 // Packs the image and sets nb1, nb2, f_out, limit, least and weights.
 void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const float *const *b, std::vector<float> &image,
                F32WPacked *pk);
-// Whether it is the faster one for this many points (it takes any).
-bool f32w_serves(const F32WPacked &pk, int64_t n_points);
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
                            const F32WPacked &pk, hipStream_t stream);
 

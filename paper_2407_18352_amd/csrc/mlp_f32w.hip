@@ -18,7 +18,10 @@
 // products of block j.  Measured, 9-200-50-1 on 1,048,576 points: 758 us layer
 // by layer (three launches, the rows of both hidden layers through memory), 167
 // here; 9-200-1 471 / 73, 48-160-96-8 1402 / 422, 9-32-512-1 1147 / 330; on 65,536
-// points 9-200-50-1 50 / 14.1.  What bounds it: matrix operations, a fifth of them
+// points 9-200-50-1 50 / 14.1.  Few points wait for one tile's chain of passes: from
+// eight passes over two blocks on (9-40-512-1 on up to 4096 points) two library calls
+// are shorter, 20.6 / 23.4 us; the kernel serves there too, since it needs no
+// workspace (a call's route, and its bits, don't depend on the points).  What bounds it: matrix operations, a fifth of them
 // padding, and the splits' vector instructions beside them.
 #include "mlp_f32.hpp"
 
@@ -448,15 +451,6 @@ void f32w_pack(int n_layers, const int32_t *dims, const float *const *W, const f
         }
     for (int o = 0; o < kFoutMax; ++o)
         reinterpret_cast<float *>(img + lay.out_b())[o] = o < O ? b[n_layers - 1][o] : FLT_MAX;   // (never below `least`)
-}
-
-// Few points wait for one tile's chain of passes, each with the first layer again:
-// from eight passes over two blocks on the layer-by-layer path is shorter, where
-// its library product takes the few inputs in one step (1,000 points, layer by
-// layer / here: 9-64-448-1 20.8 / 20.8 us, 9-40-512-1 20.6 / 23.5, 12-40-512-1 20.7 /
-// 23.4, 14-64-448-1 29.9 / 21; 8,000 points of 9-33-512-1 26.1 / 23.5).
-bool f32w_serves(const F32WPacked &pk, int64_t n_points) {
-    return pk.nb1 < 2 || pk.nb2 <= 14 || pk.dims[0] >= 14 || n_points > 4096;
 }
 
 hipError_t launch_mlp_f32w(const Map32 &in, const Map32 &out, const FeatTable32 &tin, const FeatTable32 &tout,
